@@ -48,36 +48,10 @@
 //    triplet split over many waves, whose faces travel through HBM as
 //    (value, run-tag) pairs with device-coherent accesses (see the
 //    hand-over notes below).
-#include "internal.h"
+#include "device.h"
 
 namespace trioseq {
 namespace {
-
-constexpr int kBufFlags = 0x00020000;       // raw buffer, gfx9 family
-constexpr uint32_t kOob = 0xF0000000u;      // voffset outside every buffer
-
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-
-__device__ __forceinline__ Rsrc make_rsrc(const void* p, uint64_t bytes) {
-  const uint32_t n = bytes > 0x7FFFFFFFull ? 0x7FFFFFFFu : (uint32_t)bytes;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)n, kBufFlags);
-}
-
-__device__ __forceinline__ uint32_t residue_at(const uint32_t* __restrict__ words, uint64_t off,
-                                               uint32_t p) {
-  return (words[off + (p >> 4)] >> ((p & 15u) << 1)) & 3u;
-}
-
-__device__ __forceinline__ int sbyte(uint32_t tab, uint32_t sh) {
-  return __builtin_amdgcn_sbfe((int)tab, sh, 8);
-}
-
-__device__ __forceinline__ int max3i(int a, int b, int c) { return max(max(a, b), c); }
-
-__device__ __forceinline__ uint32_t pick4(uint32_t code, uint32_t t0, uint32_t t1, uint32_t t2,
-                                          uint32_t t3) {
-  return code == 0 ? t0 : code == 1 ? t1 : code == 2 ? t2 : t3;
-}
 
 template <int RJ, int RK>
 struct Lds {
@@ -121,28 +95,6 @@ struct PanelIO {
   const int* cons_done = nullptr;
 };
 
-// A wait that gave up: the run's error flag is raised, and the release fence
-// orders it before every store the wave issues afterwards. A panel that gave
-// up goes on with whatever its faces hold, so the flag must become visible
-// no later than the faces it writes from then on: a downstream panel that
-// consumes them (and the panel that publishes the score after it) then sees
-// the flag too.
-__device__ __forceinline__ void raise_error(int* err) {
-  if ((threadIdx.x & 63) == 0) __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-}
-
-// The score of a split triplet, published by its last panel once the sweep is
-// over: INT32_MIN if any wait of the run gave up. The acquire fence orders the
-// flag's load after the face loads that the panel's result depends on.
-__device__ __forceinline__ void publish_score(int32_t* so, int v, const int* err) {
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  const bool bad = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  // System scope: the score may live in mapped host memory (serving), where
-  // the host picks it up while the kernel is still running.
-  __hip_atomic_store(so, bad ? INT32_MIN : v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Cross-wavefront hand-over in the wide engine. Every face entry is a
 // (value, tag) pair written by one 64-bit store, tag = the run's generation
 // number, so a consumer knows an entry is current without any flag or
@@ -154,38 +106,6 @@ __device__ __forceinline__ void publish_score(int32_t* so, int v, const int* err
 // kTagAlways, valid in every run.
 // Step of a chunk at which panel jobs issue the next chunk's staging loads.
 constexpr int kWideStageAt = 7;
-
-constexpr int kCohNone = 0;
-constexpr int kCohDevice = 16;              // SC1
-constexpr int kTagAlways = 0x7FFFFFFF;
-
-// A zero the compiler cannot see through. Re-reads of stale face entries add
-// it to their scalar offset, so each retry is a distinct load that is neither
-// merged with nor hoisted above an earlier one, while staying an ordinary
-// (non-volatile) device-coherent load: all re-reads of a chunk are in flight
-// together and share one wait.
-__device__ __forceinline__ uint32_t opaque_zero() {
-  uint32_t z;
-  asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-  return z;
-}
-
-// Every wait for another wavefront is bounded (PanelIO::wait_ticks, 2 s by
-// default, in ticks of the 100 MHz wall clock): past the limit the wave
-// raises the error flag and proceeds (the score is then marked invalid), so a
-// lost producer cannot hang the GPU.
-
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-// Four consecutive ints of LDS starting on a 16-byte boundary, read as one
-// 128-bit access. A lane's halo row is either a ring row or a neighbour's
-// slot row; both are 16-byte aligned, but the compiler cannot see that
-// through the choice and would split the read into 8-byte halves, whose
-// 16-byte lane stride makes lanes 8 apart collide on one LDS bank.
-__device__ __forceinline__ v4i lds_v4(const int* p) {
-  return *reinterpret_cast<const v4i*>(__builtin_assume_aligned(p, 16));
-}
 
 // Per-slice lookup shifts: shb[i + kShiftPre] = 8 * code(S0[i-1]) for slices
 // 1..n0, 0 elsewhere; covers slices -kShiftPre .. n0 + 47.
@@ -240,13 +160,6 @@ struct SplitLds {
   // wave back only when it falls kRingR + 7 steps behind.
   __device__ int* out_right(int t) { return &out[kRing * W + ((t - (kGK - 1)) & (kRingR - 1)) * RR]; }
 };
-
-__device__ __forceinline__ int lds_get(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void lds_put(int* p, int v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
 
 // Global scoring: the lane owning cell (n0, n1, n2) writes the score to
 // score_out (non-null for the triplet's last panel only); returns 0.
@@ -1362,605 +1275,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) 
   }
 }
 
-// ---- Packed pairs: two triplets per lane, one 16-bit half each. ----------
-//
-// Two triplets of a batch are swept together by one wavefront over a common
-// panel grid (each axis padded to the longer of the two), every register
-// holding the pair's two values of one cell, one per 16-bit half. A cell
-// takes 5 packed additions (v_pk_add_u16) and 3 packed three-input maxima
-// (v_pk_maximum3_f16), 4 instructions per cell update against 7 in int32.
-//
-// The maximum is a half-precision instruction used on integers, exactly:
-// every value a lane ever holds is an integer in [1024, 31743], whose bit
-// patterns are positive normal half-precision numbers (0x0400 .. 0x7BFF:
-// no zero, no subnormal, no infinity, no NaN), and for those the float
-// order of the bit patterns is the integer order; a maximum returns one of
-// its inputs unchanged. The additions are plain 16-bit integer additions.
-// What keeps every value in range (checked on the host per batch, otherwise
-// the batch takes the int32 kernels):
-//  * every substitution term s - 2*gap is >= 0, so no addition lowers a
-//    value and the lookups need no sign extension;
-//  * predecessors outside the tensor (the virtual faces, and the slices
-//    before 0 that skewed lanes compute while filling) start at kSentP =
-//    1024 and grow only along their own paths, by at most maxA per residue
-//    of the path (maxA = the largest term), to below base - 512;
-//  * a real cell holds base + M', with base above every such value and
-//    M' >= 0, so a move from outside the tensor never wins (this also
-//    replaces the -128 row and column tables of the int32 kernels); the one
-//    real start, M'(0,0,0) = 0, is set explicitly;
-//  * base + maxA * (the longest path in the padded box, drain included)
-//    stays at or below 31743.
-typedef _Float16 h2v __attribute__((ext_vector_type(2)));
-typedef unsigned short u2v __attribute__((ext_vector_type(2)));
-constexpr uint32_t kSentP = 0x0400u;  // 1024 in both halves (see above)
-
-__device__ __forceinline__ uint32_t padd(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u2v, a) + __builtin_bit_cast(u2v, b));
-}
-__device__ __forceinline__ uint32_t pmax3(uint32_t a, uint32_t b, uint32_t c) {
-  const h2v x = __builtin_bit_cast(h2v, a), y = __builtin_bit_cast(h2v, b), z = __builtin_bit_cast(h2v, c);
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z));
-}
-__device__ __forceinline__ uint32_t pmax2(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t,
-                            __builtin_elementwise_maximum(__builtin_bit_cast(h2v, a), __builtin_bit_cast(h2v, b)));
-}
-// Integer forms, for differences that need not be normal half patterns.
-__device__ __forceinline__ uint32_t psub(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u2v, a) - __builtin_bit_cast(u2v, b));
-}
-__device__ __forceinline__ uint32_t umax2(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u2v, a), __builtin_bit_cast(u2v, b)));
-}
-
-// Per-slice byte selectors of a pair, for v_perm_b32: slice i of the common
-// sweep picks byte code_a(i) of triplet a's table into the low half and byte
-// code_b(i) of b's table into the high half (codes of S0[i-1] for 1 <= i <=
-// n0 of that triplet, 0 elsewhere); covers slices -kShiftPre .. n0 + 47.
-__device__ __forceinline__ void stage_selectors(uint32_t* sel, const uint32_t* __restrict__ words,
-                                                const TripletDesc& ta, const TripletDesc& tb, int n0) {
-  const int total = n0 + 64;
-  for (int q = threadIdx.x & 63; q < total; q += 64) {
-    const int i = q - kShiftPre;
-    const uint32_t ca = (i >= 1 && i <= (int)ta.len[0]) ? residue_at(words, ta.off[0], (uint32_t)(i - 1)) : 0u;
-    const uint32_t cb = (i >= 1 && i <= (int)tb.len[0]) ? residue_at(words, tb.off[0], (uint32_t)(i - 1)) : 0u;
-    sel[q] = ca | 0x0C00u | ((cb + 4u) << 16) | 0x0C000000u;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-}
-
-// LDS of a packed wavefront: the lanes' edge slots and the capture tile
-// (one object), and the halo rings, one object per chunk half. Staging of
-// chunk c + 1 goes to the half that chunk c does not read. Kept as two
-// objects, each a fixed object in its copy of the chunk body, the halves
-// take static addresses. (The compiler still makes a chunk's first halo
-// read wait for the loads in flight, since a lane's read picks between a
-// ring row and a slot; the other wave on the SIMD covers that wait.)
-template <int RJ, int RK>
-struct PkLds {
-  __attribute__((aligned(16))) int sR[64][RJ];  // right column of each lane
-  __attribute__((aligned(16))) int sB[64][RK];  // bottom row of each lane
-  int sX[64];                                   // bottom of each lane's left halo
-  int cap[RJ * RK];                             // tile of triplet a's score cell
-  int wsync;
-};
-template <int RJ, int RK>
-struct PkRing {
-  static constexpr int H = kGJ * RJ, W = kGK * RK;
-  __attribute__((aligned(16))) int T[kChunk][W];    // top face rows of the chunk
-  __attribute__((aligned(16))) int C[kChunk][kGK];  // corners of the top-edge lanes
-  __attribute__((aligned(16))) int L[kChunk][H];    // left face rows of the chunk
-};
-
-// One panel of a pair (plain faces in the wave's workspace, one 32-bit word
-// per entry holding both halves). Global scoring captures each triplet's
-// cell (n0, n1, n2) when the panel holds it: triplet a's tile into L.cap,
-// b's into capb. Semi-global and local scoring fold the panel's cells into
-// the lane's running best (both halves; see k_sweep_pk for its meaning).
-template <int RJ, int RK, int KIND, bool FUSED, int XCH, bool DMA>
-__device__ void sweep_panel_pk(PkLds<RJ, RK>& L, PkRing<RJ, RK>& R0, PkRing<RJ, RK>& R1, int* capb,
-                               const uint32_t* sel, const DevScoring& sc,
-                               const uint32_t* __restrict__ words, const TripletDesc& ta,
-                               const TripletDesc& tb, int n0, int pj, int pk, const int* top, const int* left,
-                               int* bot, int* right, uint32_t base2, uint32_t& best, uint32_t kc) {
-  constexpr int H = kGJ * RJ, W = kGK * RK, RR = H + 4;
-  constexpr bool PAD = KIND != kGlobal;
-  const int lane = threadIdx.x & 63;
-  const int y = lane >> 3, x = lane & 7;
-  const int j0 = pj * H + y * RJ, k0 = pk * W + x * RK;
-  const int n1a = (int)ta.len[1], n1b = (int)tb.len[1], n2a = (int)ta.len[2], n2b = (int)tb.len[2];
-  const uint32_t* bt = sc.byte_tab;
-  // Row and column tables of both triplets (code 0 outside a sequence).
-  // Semi-global and local scoring take all-zero tables, per triplet, on
-  // row 0, column 0 and past the triplet's own last row and column: a move
-  // that consumes a residue which is not there then scores no better than
-  // the gaps it replaces, so those cells never beat a cell of the triplet
-  // itself (the padding argument of the int32 kernels, with 0 for -128,
-  // as no term may be negative here).
-  uint32_t TBa[RJ], TBb[RJ], TCa[RK], TCb[RK], C2[RJ][RK];
-  uint32_t cca[RK], ccb[RK];
-  bool za[RK], zb[RK];
-#pragma unroll
-  for (int r = 0; r < RJ; ++r) {
-    const int j = j0 + r;
-    const uint32_t ba = (j >= 1 && j <= n1a) ? residue_at(words, ta.off[1], (uint32_t)(j - 1)) : 0u;
-    const uint32_t bb = (j >= 1 && j <= n1b) ? residue_at(words, tb.off[1], (uint32_t)(j - 1)) : 0u;
-    TBa[r] = (PAD && (j == 0 || j > n1a)) ? 0u : pick4(ba, bt[0], bt[1], bt[2], bt[3]);
-    TBb[r] = (PAD && (j == 0 || j > n1b)) ? 0u : pick4(bb, bt[0], bt[1], bt[2], bt[3]);
-  }
-#pragma unroll
-  for (int c = 0; c < RK; ++c) {
-    const int k = k0 + c;
-    cca[c] = (k >= 1 && k <= n2a) ? residue_at(words, ta.off[2], (uint32_t)(k - 1)) : 0u;
-    ccb[c] = (k >= 1 && k <= n2b) ? residue_at(words, tb.off[2], (uint32_t)(k - 1)) : 0u;
-    za[c] = PAD && (k == 0 || k > n2a);
-    zb[c] = PAD && (k == 0 || k > n2b);
-    TCa[c] = za[c] ? 0u : pick4(cca[c], bt[0], bt[1], bt[2], bt[3]);
-    TCb[c] = zb[c] ? 0u : pick4(ccb[c], bt[0], bt[1], bt[2], bt[3]);
-  }
-#pragma unroll
-  for (int r = 0; r < RJ; ++r)
-#pragma unroll
-    for (int c = 0; c < RK; ++c)
-      C2[r][c] = (za[c] ? 0u : ((TBa[r] >> (cca[c] << 3)) & 0xFFu)) |
-                 ((zb[c] ? 0u : ((TBb[r] >> (ccb[c] << 3)) & 0xFFu)) << 16);
-
-  uint32_t P[RJ][RK], D[RJ][RK], Lp[RJ], Tp[RK];
-#pragma unroll
-  for (int r = 0; r < RJ; ++r) {
-    Lp[r] = kSentP * 0x10001u;
-#pragma unroll
-    for (int c = 0; c < RK; ++c) P[r][c] = D[r][c] = kSentP * 0x10001u;
-  }
-#pragma unroll
-  for (int c = 0; c < RK; ++c) Tp[c] = kSentP * 0x10001u;
-
-  const int nsteps = n0 + 1 + kSkew;
-  const int nchunks = (nsteps + kChunk - 1) / kChunk;
-  // Capture: the lane holding cell (n1, n2) of a triplet in this panel keeps
-  // its tile at that triplet's slice n0.
-  const int rsa = n1a - j0, csa = n2a - k0;
-  const int rsb = n1b - j0, csb = n2b - k0;
-  const bool own_a = rsa >= 0 && rsa < RJ && csa >= 0 && csa < RK;
-  const bool own_b = rsb >= 0 && rsb < RJ && csb >= 0 && csb < RK;
-  const int n0a = (int)ta.len[0], n0b = (int)tb.len[0];
-
-  // Semi-global and local scoring (g = -2*gap >= 0). fi = g*(i + j0 + k0)
-  // for the lane's slice i of the current step; a cell of anti-diagonal
-  // class d = r + c of the tile lies at index sum i + j0 + k0 + d.
-  constexpr int ND = RJ + RK - 1;
-  const int g = -sc.gap2;
-  const uint32_t g2 = (uint32_t)g * 0x10001u;
-  int fi = g * (j0 + k0 - y - x);
-  // Semi-global: the halves of the rows and columns that are a triplet's
-  // last row n1 or last column n2 (masks of both halves).
-  uint32_t RM[RJ], CM[RK], rcany = 0;
-#pragma unroll
-  for (int r = 0; r < RJ; ++r) {
-    RM[r] = (r == rsa ? 0xFFFFu : 0u) | (r == rsb ? 0xFFFF0000u : 0u);
-    rcany |= RM[r];
-  }
-#pragma unroll
-  for (int c = 0; c < RK; ++c) {
-    CM[c] = (c == csa ? 0xFFFFu : 0u) | (c == csb ? 0xFFFF0000u : 0u);
-    rcany |= CM[c];
-  }
-  const bool axis_panel = pj == 0 || pk == 0;
-
-  const uint32_t frows = face_rows((uint32_t)n0);
-  constexpr uint32_t ts = W * 4u, RRB = RR * 4u;
-  const Rsrc r_top = make_rsrc(top, (uint64_t)frows * ts);
-  const Rsrc r_left = make_rsrc(left, (uint64_t)frows * RRB);
-  const Rsrc r_bot = make_rsrc(bot ? bot : top, bot ? (uint64_t)frows * ts : 0);
-  const Rsrc r_right = make_rsrc(right ? right : left, right ? (uint64_t)frows * RRB : 0);
-
-  // Staging, as in sweep_panel (plain faces): value q of a chunk is entry
-  // lane + 64 q of the top, corner or left ring.
-  constexpr int QT = kChunk * W / 64, QC = kChunk * kGK / 64, QL = kChunk * H / 64;
-  constexpr int NPF = QT + QC + QL;
-  constexpr int RT = 64 / W, RL = 64 / H;
-  static_assert(64 % W == 0 && 64 % H == 0 && QC == 1, "ring widths must divide 64");
-  const int eT = lane % W;
-  const uint32_t offT = (uint32_t)((kGJ - 1 + lane / W) * (int)ts + eT * 4);
-  const int eC = lane % kGK;
-  const bool corner_from_left = eC == 0;
-  const uint32_t offC = corner_from_left ? (uint32_t)((kGK - 1 + lane / kGK) * (int)RRB)
-                                         : (uint32_t)((kGJ - 2 + lane / kGK) * (int)ts + (eC * RK - 1) * 4);
-  const int eL = lane % H;
-  const uint32_t offL = (uint32_t)((kGK - 1 + lane / H) * (int)RRB + (4 + eL) * 4);
-  int pf[DMA ? 1 : NPF];
-  auto stage_load = [&](int c, PkRing<RJ, RK>& dst) {
-    const uint32_t cb0 = (uint32_t)(c * kChunk);
-    if (DMA) {
-      // Straight into the ring half of chunk c (lane l's word of each load
-      // lands at the destination + 4 l, which is where it belongs); the
-      // corner loads go to the same slots from the top or the left face,
-      // so each lane takes only one of them.
-      typedef __attribute__((address_space(3))) void* LdsPtr;
-#pragma unroll
-      for (int q = 0; q < QT; ++q)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_top, (LdsPtr)(&dst.T[0][0] + 64 * q), 4, offT,
-                                                 (cb0 + q * RT) * ts, 0, 0);
-      if (corner_from_left)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_left, (LdsPtr)&dst.C[0][0], 4, offC, cb0 * RRB, 0, 0);
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_top, (LdsPtr)&dst.C[0][0], 4, offC, cb0 * ts, 0, 0);
-#pragma unroll
-      for (int q = 0; q < QL; ++q)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r_left, (LdsPtr)(&dst.L[0][0] + 64 * q), 4, offL,
-                                                 (cb0 + q * RL) * RRB, 0, 0);
-      return;
-    }
-#pragma unroll
-    for (int q = 0; q < NPF; ++q) {
-      if (q < QT) {
-        pf[q] = (int)__builtin_amdgcn_raw_buffer_load_b32(r_top, offT, (cb0 + q * RT) * ts, 0);
-      } else if (q < QT + QC) {
-        const uint32_t ot = corner_from_left ? kOob : offC, ol = corner_from_left ? offC : kOob;
-        pf[q] = (int)(__builtin_amdgcn_raw_buffer_load_b32(r_top, ot, cb0 * ts, 0) |
-                      __builtin_amdgcn_raw_buffer_load_b32(r_left, ol, cb0 * RRB, 0));
-      } else {
-        pf[q] = (int)__builtin_amdgcn_raw_buffer_load_b32(r_left, offL, (cb0 + (q - QT - QC) * RL) * RRB, 0);
-      }
-    }
-  };
-  auto stage_finish = [&](int c, PkRing<RJ, RK>& dst) {
-    if (DMA) {
-      // The loads of chunk c were issued at the first step of chunk c - 1,
-      // ahead of that chunk's face stores (kStores per step); vector memory
-      // operations complete in issue order, so once no more than those
-      // stores are outstanding the loads are done, and the stores need not
-      // be waited for. Chunk 0's loads were issued just before, with no
-      // store after them.
-      constexpr int kStores = RK / 4 + RJ / 4 + 1;
-      constexpr int kAfter = kStores * kChunk;
-      static_assert(kAfter < 64, "vmcnt holds at most 63");
-      constexpr int kWaitAfter = (kAfter & 15) | ((kAfter >> 4) << 14) | (0x7 << 4) | (0xF << 8);
-      if (c == 0)
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-      else
-        __builtin_amdgcn_s_waitcnt(kWaitAfter);  // vmcnt(kAfter)
-      return;
-    }
-#pragma unroll
-    for (int q = 0; q < NPF; ++q) {
-      if (q < QT)
-        (&dst.T[0][0])[lane + 64 * q] = pf[q];
-      else if (q < QT + QC)
-        dst.C[0][lane] = pf[q];
-      else
-        (&dst.L[0][0])[lane + 64 * (q - QT - QC)] = pf[q];
-    }
-  };
-  stage_load(0, R0);
-#pragma unroll
-  for (int r = 0; r < RJ; ++r) L.sR[lane][r] = (int)(kSentP * 0x10001u);
-#pragma unroll
-  for (int c = 0; c < RK; ++c) L.sB[lane][c] = (int)(kSentP * 0x10001u);
-  L.sX[lane] = (int)(kSentP * 0x10001u);
-
-  const bool y0 = y == 0, x0 = x == 0;
-  const bool tring = XCH || y0, lring = XCH || x0;
-  // Halo rows: edge lanes read the chunk's ring half, inner lanes their
-  // neighbour's slot (the same every step).
-  const int* t_slot = &L.sB[y0 ? 0 : lane - 8][0];
-  const int t_str = tring ? W : 0;
-  const int* c_slot = &L.sX[y0 ? 0 : lane - 8];
-  const int c_str = tring ? kGK : 0;
-  const int* l_slot = &L.sR[x0 ? 0 : lane - 1][0];
-  const int l_str = lring ? H : 0;
-  const int up_addr = ((lane + 64 - kGK) & 63) << 2;
-  const uint32_t vo_bot = (y == kGJ - 1) ? (uint32_t)(x * RK * 4) : kOob;
-  const uint32_t vo_right = (x == kGK - 1) ? (uint32_t)((4 + y * RJ) * 4) : kOob;
-  const uint32_t vo_corner = (x == kGK - 1 && y == 0) ? 0u : kOob;
-  const int sl_base = kShiftPre - y - x;
-  const bool seed_lane = pj == 0 && pk == 0 && lane == 0;
-
-  // Chunk c reads ring half cur and stages chunk c + 1 into nxt. With loads
-  // straight to LDS the loop below takes two chunks per turn, so that both
-  // halves are fixed objects in each copy of the body.
-  auto run_chunk = [&](int c, PkRing<RJ, RK>& cur, PkRing<RJ, RK>& nxt) __attribute__((always_inline)) {
-    stage_finish(c, cur);
-    const bool more = c + 1 < nchunks;
-    const int cb0 = c * kChunk;
-    const bool cap_chunk = (n0a >= cb0 - kSkew && n0a <= cb0 + kChunk - 1) ||
-                           (n0b >= cb0 - kSkew && n0b <= cb0 + kChunk - 1);
-    const uint32_t vb = vo_bot + (uint32_t)cb0 * ts, vr = vo_right + (uint32_t)cb0 * RRB,
-                   vc = vo_corner + (uint32_t)cb0 * RRB;
-    const int* tb = tring ? &cur.T[0][x * RK] : t_slot;
-    const int* cbp = tring ? &cur.C[0][x] : c_slot;
-    const int* lb = lring ? &cur.L[0][y * RJ] : l_slot;
-    const uint32_t* sp = sel + sl_base + cb0;
-    uint32_t selv[kChunk];
-#pragma unroll
-    for (int s = 0; s < kChunk; ++s) selv[s] = sp[s];
-#pragma unroll
-    for (int s = 0; s < kChunk; ++s) {
-      if (s == 0 && more) stage_load(c + 1, nxt);
-      const int t = cb0 + s;
-      const uint32_t sv = selv[s];
-      uint32_t A[RJ], B[RK];
-#pragma unroll
-      for (int r = 0; r < RJ; ++r) A[r] = __builtin_amdgcn_perm(TBb[r], TBa[r], sv);
-#pragma unroll
-      for (int cc = 0; cc < RK; ++cc) B[cc] = __builtin_amdgcn_perm(TCb[cc], TCa[cc], sv);
-      uint32_t T[RK], Lh[RJ];
-#pragma unroll
-      for (int cc = 0; cc < RK; cc += 4) {
-        const v4i v = lds_v4(tb + s * t_str + cc);
-        T[cc] = (uint32_t)v.x, T[cc + 1] = (uint32_t)v.y, T[cc + 2] = (uint32_t)v.z, T[cc + 3] = (uint32_t)v.w;
-      }
-#pragma unroll
-      for (int r = 0; r < RJ; r += 4) {
-        const v4i v = lds_v4(lb + s * l_str + r);
-        Lh[r] = (uint32_t)v.x, Lh[r + 1] = (uint32_t)v.y, Lh[r + 2] = (uint32_t)v.z, Lh[r + 3] = (uint32_t)v.w;
-      }
-      uint32_t corner = (uint32_t)cbp[s * c_str];
-      if (XCH) {
-        // As in sweep_panel: inner lanes take their upper neighbour's row
-        // and corner through ds_bpermute and their left neighbour's column
-        // through a DPP row shift, from its previous-step registers.
-#pragma unroll
-        for (int cc = 0; cc < RK; ++cc) {
-          const uint32_t nb = (uint32_t)__builtin_amdgcn_ds_bpermute(up_addr, (int)P[RJ - 1][cc]);
-          T[cc] = y0 ? T[cc] : nb;
-        }
-        {
-          const uint32_t nb = (uint32_t)__builtin_amdgcn_ds_bpermute(up_addr, (int)Lp[RJ - 1]);
-          corner = y0 ? corner : nb;
-        }
-#pragma unroll
-        for (int r = 0; r < RJ; ++r) {
-          const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)P[r][RK - 1], 0x111, 0xF, 0xF, true);
-          Lh[r] = x0 ? Lh[r] : nb;
-        }
-      }
-      const int i = t - y - x;  // this lane's slice
-      if (KIND == kSemiGlobal && axis_panel) {
-        // The axes hold 0 (stored base + g*index, both halves): at slice 0
-        // the virtual row above the first panel row holds base + g*k and the
-        // virtual column left of the first panel column base + g*j, and at
-        // k = 0 the virtual row holds base + g*i; the single move (+0)
-        // copies them in. Other moves from there take the zero row/column-0
-        // tables and give values the single moves already reach.
-        if (j0 == 0) {
-#pragma unroll
-          for (int cc = 0; cc < RK; ++cc) T[cc] = i == 0 ? base2 + (uint32_t)(g * (k0 + cc)) * 0x10001u : T[cc];
-          if (k0 == 0) T[0] = i >= 0 ? base2 + (uint32_t)(g * i) * 0x10001u : T[0];
-        }
-        if (k0 == 0) {
-#pragma unroll
-          for (int r = 0; r < RJ; ++r) Lh[r] = i == 0 ? base2 + (uint32_t)(g * (j0 + r)) * 0x10001u : Lh[r];
-        }
-      }
-      // Local floors per anti-diagonal class, F_d = base + fi + g*d in both
-      // halves (M >= 0); none before slice 0 (0 there, below every value).
-      uint32_t F[ND];
-      if (KIND == kLocal) {
-        asm volatile("" : "+v"(fi));  // one step's floors live at a time
-        const uint32_t f0 = i >= 0 ? base2 + (uint32_t)fi * 0x10001u : 0u;
-#pragma unroll
-        for (int d = 0; d < ND; ++d) F[d] = f0 + (uint32_t)d * g2;
-      }
-      // Terms of the previous slice first (formed while the halo reads are
-      // in flight): Q = best of the single move along S0 and its two double
-      // moves, X7 the triple move. The fused form computes them cell by cell
-      // instead (no registers held for them across the tile). Local scoring
-      // folds X7 and the floor into Q.
-      uint32_t Q[RJ][RK], X7[RJ][RK], N[RJ][RK];
-      auto prev_terms = [&](int r, int cc) {
-        const uint32_t up_prev = r ? P[r - 1][cc] : Tp[cc];
-        const uint32_t left_prev = cc ? P[r][cc - 1] : Lp[r];
-        Q[r][cc] = pmax3(P[r][cc], padd(up_prev, A[r]), padd(left_prev, B[cc]));
-        X7[r][cc] = padd(D[r][cc], padd(A[r], B[cc]));
-        if (KIND == kLocal) Q[r][cc] = pmax3(Q[r][cc], X7[r][cc], F[r + cc]);
-      };
-      if (!FUSED) {
-#pragma unroll
-        for (int r = 0; r < RJ; ++r)
-#pragma unroll
-          for (int cc = 0; cc < RK; ++cc) prev_terms(r, cc);
-      }
-#pragma unroll
-      for (int r = 0; r < RJ; ++r)
-#pragma unroll
-        for (int cc = 0; cc < RK; ++cc) {
-          if (FUSED) prev_terms(r, cc);
-          const uint32_t up_cur = r ? N[r - 1][cc] : T[cc];
-          const uint32_t left_cur = cc ? N[r][cc - 1] : Lh[r];
-          const uint32_t diag_cur = r ? (cc ? N[r - 1][cc - 1] : Lh[r - 1]) : (cc ? T[cc - 1] : corner);
-          const uint32_t x6 = padd(diag_cur, C2[r][cc]);
-          if (KIND == kLocal)
-            N[r][cc] = pmax3(pmax2(Q[r][cc], x6), up_cur, left_cur);
-          else
-            N[r][cc] = pmax3(pmax3(Q[r][cc], X7[r][cc], x6), up_cur, left_cur);
-          // Global M'(0,0,0) = 0: the one real start, cell (0,0) of lane 0
-          // of the first panel at step 0, set before any other cell reads it.
-          if (KIND == kGlobal && r == 0 && cc == 0) N[0][0] = (t == 0 && seed_lane) ? base2 : N[0][0];
-          D[r][cc] = x6;
-        }
-
-      // Masks of the halves whose triplet has this slice (0 <= i <= its n0)
-      // and of those whose last slice it is.
-      const uint32_t vm = ((uint32_t)i <= (uint32_t)n0a ? 0xFFFFu : 0u) | ((uint32_t)i <= (uint32_t)n0b ? 0xFFFF0000u : 0u);
-      if (KIND == kLocal) {
-        // M = stored value - F_d, never negative on slices from 0 (every
-        // cell is floored); the best class maximum minus its floor.
-        uint32_t sb = 0;
-#pragma unroll
-        for (int d = 0; d < ND; ++d) {
-          uint32_t m = 0, hold = 0;
-          int cnt = 0;
-#pragma unroll
-          for (int r = 0; r < RJ; ++r) {
-            if (d - r < 0 || d - r >= RK) continue;
-            const uint32_t v = N[r][d - r];
-            if (cnt == 0) m = v;
-            else if (cnt & 1) hold = v;
-            else m = pmax3(m, hold, v);
-            ++cnt;
-          }
-          if (!(cnt & 1)) m = pmax2(m, hold);
-          sb = umax2(sb, psub(m, F[d]));
-        }
-        best = umax2(best, sb & vm);
-      } else if (KIND == kSemiGlobal) {
-        // Cells of a triplet's last slice, row or column (on its slices 0
-        // .. n0), as M + kc = stored - base - g*(i + j + k) + kc, which the
-        // host keeps within [1, 0xFFFF]; masked cells give 0.
-        const uint32_t sm = (i == n0a ? 0xFFFFu : 0u) | (i == n0b ? 0xFFFF0000u : 0u);
-        if (((rcany | sm) & vm) != 0u) {
-          const uint32_t off0 = ((uint32_t)(kc - (base2 & 0xFFFFu) - (uint32_t)fi) & 0xFFFFu) * 0x10001u;
-          uint32_t sb = 0;
-#pragma unroll
-          for (int r = 0; r < RJ; ++r)
-#pragma unroll
-            for (int cc = 0; cc < RK; ++cc)
-              sb = umax2(sb, padd(N[r][cc], psub(off0, (uint32_t)(r + cc) * g2)) & (RM[r] | CM[cc] | sm));
-          best = umax2(best, sb & vm);
-        }
-      }
-      fi += g;
-
-      if (!XCH) {
-#pragma unroll
-        for (int r = 0; r < RJ; ++r) L.sR[lane][r] = (int)N[r][RK - 1];
-#pragma unroll
-        for (int cc = 0; cc < RK; ++cc) L.sB[lane][cc] = (int)N[RJ - 1][cc];
-        L.sX[lane] = (int)Lh[RJ - 1];
-      }
-#pragma unroll
-      for (int cc = 0; cc < RK; cc += 4)
-        __builtin_amdgcn_raw_buffer_store_b128(
-            (v4i){(int)N[RJ - 1][cc], (int)N[RJ - 1][cc + 1], (int)N[RJ - 1][cc + 2], (int)N[RJ - 1][cc + 3]},
-            r_bot, vb + (s * ts + cc * 4), 0, 0);
-#pragma unroll
-      for (int r = 0; r < RJ; r += 4)
-        __builtin_amdgcn_raw_buffer_store_b128(
-            (v4i){(int)N[r][RK - 1], (int)N[r + 1][RK - 1], (int)N[r + 2][RK - 1], (int)N[r + 3][RK - 1]},
-            r_right, vr + (s * RRB + r * 4), 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b32((int)T[RK - 1], r_right, vc + s * RRB, 0, 0);
-      if (KIND == kGlobal && cap_chunk) {
-        if (own_a && i == n0a) {
-#pragma unroll
-          for (int r = 0; r < RJ; ++r)
-#pragma unroll
-            for (int cc = 0; cc < RK; ++cc) L.cap[r * RK + cc] = (int)N[r][cc];
-        }
-        if (own_b && i == n0b) {
-#pragma unroll
-          for (int r = 0; r < RJ; ++r)
-#pragma unroll
-            for (int cc = 0; cc < RK; ++cc) capb[r * RK + cc] = (int)N[r][cc];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < RJ; ++r) {
-        Lp[r] = Lh[r];
-#pragma unroll
-        for (int cc = 0; cc < RK; ++cc) P[r][cc] = N[r][cc];
-      }
-#pragma unroll
-      for (int cc = 0; cc < RK; ++cc) Tp[cc] = T[cc];
-    }
-  };
-  if constexpr (DMA) {
-    for (int c = 0; c < nchunks; c += 2) {
-      run_chunk(c, R0, R1);
-      if (c + 1 < nchunks) run_chunk(c + 1, R1, R0);
-    }
-  } else {
-    // Staged through registers, the rings are written by LDS stores, which
-    // need no such care; one copy of the body keeps register pressure down.
-    for (int c = 0; c < nchunks; ++c) run_chunk(c, (c & 1) ? R1 : R0, (c & 1) ? R0 : R1);
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-}
-
-// Persistent kernel of a packed plan: every job is a pair of whole triplets
-// (descriptors 2p and 2p + 1; a lone last triplet is paired with itself),
-// swept by one wavefront over all panels of the common grid, row by row, in
-// the wave's own face workspace. pk_top / pk_left: plain sentinel faces
-// holding kSentP in both halves. base: the stored value of M' = 0. Local
-// scoring keeps each lane's best M per half, semi-global its best M + kc
-// (kc > 0 keeps every candidate positive); the wave's maxima are the scores.
-template <int RJ, int RK, int WPE, int KIND, bool FUSED, int XCH, bool DMA>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE)))
-k_sweep_pk(SweepArgs a, const int* pk_top, const int* pk_left, uint32_t base, uint32_t kc) {
-  constexpr int H = kGJ * RJ, W = kGK * RK;
-  __shared__ PkLds<RJ, RK> L;
-  __shared__ PkRing<RJ, RK> R0, R1;
-  __shared__ int capb[RJ * RK];
-  extern __shared__ uint32_t selw[];
-  int* face = a.face + (uint64_t)blockIdx.x * a.face_stride;
-  const uint32_t base2 = base * 0x10001u;
-  for (;;) {
-    if (threadIdx.x == 0) L.wsync = atomicAdd(a.counter, 1);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    const int idx = __builtin_amdgcn_readfirstlane(L.wsync);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    if (idx >= (int)a.njobs) break;
-    const JobDesc jd = a.jobs[idx];
-    const TripletDesc ta = a.desc[jd.trip], tb = a.desc[jd.trip + 1];
-    const int n0 = (int)max(ta.len[0], tb.len[0]);
-    const int n1 = (int)max(ta.len[1], tb.len[1]), n2 = (int)max(ta.len[2], tb.len[2]);
-    stage_selectors(selw, a.words, ta, tb, n0);
-    const int PJ = n1 / H + 1, PK = n2 / W + 1;
-    const uint64_t rows = face_rows((uint32_t)n0);
-    int* fb = face;
-    int* fr = face + rows * (uint64_t)(PK * W);
-    const int pja = (int)ta.len[1] / H, pka = (int)ta.len[2] / W;
-    const int pjb = (int)tb.len[1] / H, pkb = (int)tb.len[2] / W;
-    uint32_t best = 0;
-    for (int pj = 0; pj < PJ; ++pj) {
-      for (int pk = 0; pk < PK; ++pk) {
-        int* col = fb + (uint64_t)pk * rows * W;
-        sweep_panel_pk<RJ, RK, KIND, FUSED, XCH, DMA>(L, R0, R1, capb, selw, a.sc, a.words, ta, tb, n0, pj, pk,
-                                                      pj ? col : pk_top, pk ? fr : pk_left,
-                                                      pj + 1 < PJ ? col : nullptr, pk + 1 < PK ? fr : nullptr,
-                                                      base2, best, kc);
-        // Scores of the triplets whose last cell this panel held (the owner
-        // lane's tile is in LDS; lane 0 reads the cell and stores the score).
-        if (KIND == kGlobal && (threadIdx.x & 63) == 0) {
-          if (pj == pja && pk == pka) {
-            const int r = (int)ta.len[1] - pja * H, cc = (int)ta.len[2] - pka * W;
-            const int v = L.cap[(r % RJ) * RK + (cc % RK)] & 0xFFFF;
-            __hip_atomic_store(a.scores + ta.out,
-                               v - (int)base + a.sc.gap2 * (int)(ta.len[0] + ta.len[1] + ta.len[2]),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-          }
-          if (pj == pjb && pk == pkb) {
-            const int r = (int)tb.len[1] - pjb * H, cc = (int)tb.len[2] - pkb * W;
-            const int v = (int)((uint32_t)capb[(r % RJ) * RK + (cc % RK)] >> 16);
-            __hip_atomic_store(a.scores + tb.out,
-                               v - (int)base + a.sc.gap2 * (int)(tb.len[0] + tb.len[1] + tb.len[2]),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-      }
-    }
-    if (KIND != kGlobal) {
-      // The wave's best per half; lane 0 stores both scores.
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) best = umax2(best, (uint32_t)__shfl_xor((int)best, o));
-      if ((threadIdx.x & 63) == 0) {
-        const int off = KIND == kSemiGlobal ? (int)kc : 0;
-        __hip_atomic_store(a.scores + ta.out, (int)(best & 0xFFFFu) - off, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(a.scores + tb.out, (int)(best >> 16) - off, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-      }
-    }
-  }
-}
-
-// Plain sentinel faces of the packed kernels: kSentP in both halves.
-__global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
 // Sentinel faces for panels on the tensor edge, in the plain layout (one
 // int per entry) and the tagged layout (value, kTagAlways). Every value is
 // kSent except the seeded top faces' entry for k = 0 at slice 0, which is 0
@@ -2008,59 +1322,6 @@ __global__ void k_prepare(int* ctl, int* counter, int* red, uint32_t nred) {
 #define TRIOSEQ_MODES(X, r, c, w, k, p, x) X(r, c, w, 1, k, p, x) X(r, c, w, 2, k, p, x) X(r, c, w, 3, k, p, x)
 
 }  // namespace
-
-// Packed kernels: lane tile and register budget; the 4 x 4 two-wave form
-// holds the previous slice's terms for the whole tile, the others form them
-// cell by cell.
-// (rows, columns, waves per SIMD, kind, fused, lane exchange, LDS-direct
-// staging); semi-global and local scoring exist in the four plain forms.
-#define TRIOSEQ_PK_PLAIN(X, k)                                                                    \
-  X(4, 4, 2, k, false, 0, false) X(4, 4, 3, k, true, 0, false) X(8, 4, 2, k, true, 0, false)      \
-  X(4, 8, 2, k, true, 0, false)
-#define TRIOSEQ_PK_SHAPES(X)                                                                      \
-  TRIOSEQ_PK_PLAIN(X, 0) TRIOSEQ_PK_PLAIN(X, 1) TRIOSEQ_PK_PLAIN(X, 2)                            \
-  X(4, 4, 2, 0, false, 1, false) X(4, 4, 2, 0, false, 0, true) X(4, 4, 3, 0, true, 0, true)       \
-  X(8, 4, 2, 0, true, 0, true) X(4, 8, 2, 0, true, 0, true)
-#define TRIOSEQ_PK_MATCH(r, c, w, k, x, d) \
-  (ks.rj == r && ks.rk == c && ks.wpe == w && kind == k && ks.xch == x && ks.dma == d)
-
-bool pk_shape_supported(const KernelShape& ks, int kind) {
-#define X(r, c, w, k, f, x, d) \
-  if (TRIOSEQ_PK_MATCH(r, c, w, k, x, d)) return true;
-  TRIOSEQ_PK_SHAPES(X)
-#undef X
-  return false;
-}
-
-hipError_t launch_sweep_pk(const KernelShape& ks, int kind, const SweepArgs& a, const int* pk_top,
-                           const int* pk_left, uint32_t base, uint32_t kc, int grid, hipStream_t s) {
-  const size_t lds = (size_t)(a.lds_n0 + 64) * 4;
-#define X(r, c, w, k, f, x, d)                                                                     \
-  if (TRIOSEQ_PK_MATCH(r, c, w, k, x, d)) {                                                        \
-    hipLaunchKernelGGL((k_sweep_pk<r, c, w, k, f, x, d>), dim3(grid), dim3(64), lds, s, a, pk_top, \
-                       pk_left, base, kc);                                                         \
-    return hipGetLastError();                                                                      \
-  }
-  TRIOSEQ_PK_SHAPES(X)
-#undef X
-  return hipErrorInvalidValue;
-}
-
-hipError_t sweep_pk_occupancy(const KernelShape& ks, int kind, uint32_t lds_n0, int* blocks_per_cu) {
-#define X(r, c, w, k, f, x, d)                                                                     \
-  if (TRIOSEQ_PK_MATCH(r, c, w, k, x, d))                                                          \
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(                                           \
-        blocks_per_cu, k_sweep_pk<r, c, w, k, f, x, d>, 64, (size_t)(lds_n0 + 64) * 4);
-  TRIOSEQ_PK_SHAPES(X)
-#undef X
-  return hipErrorInvalidValue;
-}
-#undef TRIOSEQ_PK_MATCH
-
-hipError_t launch_fill_packed_sentinel(uint32_t* p, uint64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_u32, dim3(256), dim3(256), 0, s, p, n, kSentP * 0x10001u);
-  return hipGetLastError();
-}
 
 bool shape_supported(const KernelShape& ks, int kind) {
 #define X(a, b, w, k, p, x) \
