@@ -71,11 +71,12 @@ SweepArgs make_sweep_args(const uint32_t* words, const TripletDesc* desc, const 
 
 // Host-side plan of one batch: validation, per-triplet axis choice, the job
 // queue in dependency order, and the device memory the sweep needs.
+constexpr int kModePkPanel = 4;
 struct Layout {
   KernelShape ks{4, 4, 2};
   int kind = 0;    // alignment kind of the scoring
   bool planes = false;  // last-slice planes are written (traceback)
-  int modes = 1;   // bit 0 whole-triplet jobs, bit 1 panel jobs
+  int modes = 1;   // bit 0 whole-triplet jobs, bit 1 panel jobs; or kModePkPanel
   int engine = 0;  // 0 all whole, 1 all split, 2 mixed
   int panels = 0;
   uint32_t lds_n0 = 0;
@@ -86,13 +87,15 @@ struct Layout {
   uint64_t pool_ints = 0;    // ints of panel faces of split triplets
   // Packed pairs: desc holds pair p as entries 2p, 2p + 1 and every job is a
   // pair; pk_base is the stored value of M' = 0, pk_kc the offset of
-  // semi-global candidates (see sweep.hip).
+  // semi-global candidates (see packed.hip). modes == kModePkPanel: every job
+  // is a panel of a pair instead, pk_base the stored value of a panel's base
+  // (see packed_panel.hip).
   bool packed = false;
   uint32_t pk_base = 0;
   uint32_t pk_kc = 0;
   // Per-triplet reduction pairs the run needs (semi-global and local scoring
   // of split triplets): 2 * red_pairs ints.
-  uint32_t red_pairs() const { return kind != 0 && (modes & 2) ? (uint32_t)desc.size() : 0u; }
+  uint32_t red_pairs() const { return kind != 0 && (modes & (2 | kModePkPanel)) ? (uint32_t)desc.size() : 0u; }
 };
 
 // Validates and lays out n triplets (lens[3t+s], word offsets off[3t+s]).
@@ -102,6 +105,10 @@ struct Layout {
 trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
                             const trioseq_scoring& sc, const trioseq_plan_options& o, int waves_hint,
                             Layout* L, bool planes = false);
+// Lays out pairs (desc entries 2p, 2p + 1, axes assigned) as packed panel jobs
+// in dependency order; false if a pair's values could leave the 16-bit range
+// under this scoring.
+bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, Layout* L);
 // Pairs per workgroup of panel-only plans unless the options say otherwise.
 constexpr int kDefaultPanelGroup = 1;
 // Lane exchange (KernelShape::xch) unless the options say otherwise.
@@ -165,6 +172,7 @@ struct HalfSplit {
   uint32_t lens[6];
   uint64_t offs[6];      // word offsets in the gathered buffer
   GatherDesc gather[6];
+  TripletDesc pair[2];   // the same halves read from the caller's words in place
   uint32_t words = 0;    // gathered words
   uint32_t rows = 0, cols = 0;
 };

@@ -57,6 +57,10 @@ struct TripletDesc {
   uint32_t len[3];    // lengths on the sweep, row and column axes
   uint32_t out;       // index of this triplet's score in the caller's output
   uint64_t face_off;  // split triplets: ints from the panel-face pool base
+  // Packed panel jobs: the sequences are residues start[s] .. start[s] +
+  // len[s] - 1 of the packed ones, read from their ends if rev is set.
+  uint32_t start[3];
+  uint32_t rev;
 };
 
 // A queue entry: one triplet swept whole by one wave, or one panel of a
@@ -156,6 +160,18 @@ hipError_t sweep_pk_occupancy(const KernelShape& ks, int kind, uint32_t lds_n0, 
 // Whether a packed kernel of this lane tile, register budget and kind exists.
 bool pk_shape_supported(const KernelShape& ks, int kind);
 hipError_t launch_fill_packed_sentinel(uint32_t* p, uint64_t n, hipStream_t s);
+
+// Packed panel jobs (packed_panel.hip): pairs of triplets, descriptors 2p and
+// 2p + 1, swept panel by panel by many workgroups; 4 x 4 lane tiles. off: the
+// stored value of a panel's base. A plane run (a.plane set) also writes both
+// triplets' last slices (global and local kinds).
+constexpr int kPkPanel = 32;  // panel rows and columns
+// Steps (rows) of a pair's panel faces, and ints of one panel's faces: per
+// row kPkPanel bottom, kPkPanel right and one corner entry of (value, tag).
+__host__ __device__ inline uint64_t pk_face_rows(uint32_t n0) { return (face_rows(n0) + 7u) & ~7u; }
+__host__ __device__ inline uint64_t pk_panel_ints(uint32_t n0) { return pk_face_rows(n0) * (4 * kPkPanel + 2); }
+hipError_t launch_panel_pk(int kind, const SweepArgs& a, uint32_t off, uint32_t kc, int grid, hipStream_t s);
+hipError_t panel_pk_occupancy(int kind, bool plane, uint32_t lds_n0, int* blocks_per_cu);
 
 // Traceback (traceback.hip). A split box: the forward and reversed planes
 // (ints from the plane buffer base), rows x cols entries each, reduced in

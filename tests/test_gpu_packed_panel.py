@@ -1,0 +1,88 @@
+"""GPU parity of packed panel jobs: two triplets (or the halves of one) swept
+panel by panel, two 16-bit values per register, every panel's values relative
+to its own base. Scores are integers, so the bar is equality with the oracle.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2605_28400_amd as ts
+from paper_2605_28400_amd import synth
+
+pytestmark = pytest.mark.gpu
+OKIND = {ts.GLOBAL: oracle.GLOBAL, ts.SEMI_GLOBAL: oracle.SEMI_GLOBAL, ts.LOCAL: oracle.LOCAL}
+SCHEMES = [(1, -1, -2), (5, -4, -6), (2, 0, -1)]  # match, mismatch, gap
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def run(torch, trips, sc, reps=2, **opts):
+    lens, off, words = ts.pack_batch(trips)
+    plan = ts.Plan(lens, off, sc=sc, **opts)
+    d_words = torch.from_numpy(words.view(np.int32)).cuda()
+    outs = []
+    for _ in range(reps):
+        d_scores = torch.full((len(trips),), -7, dtype=torch.int32, device="cuda")
+        plan.run(d_words, d_scores)
+        torch.cuda.synchronize()
+        outs.append(d_scores.cpu().numpy().copy())
+    info = plan.info()
+    plan.close()
+    return outs, info
+
+
+def want_scores(trips, scheme, kind):
+    sub = [[scheme[0] if x == y else scheme[1] for y in range(4)] for x in range(4)]
+    return np.asarray(oracle.score_batch(trips, sub, scheme[2], kind=OKIND[kind]), dtype=np.int64)
+
+
+# Panel edges (31, 32, 33 and multiples), a lone row or column, empty axes,
+# halves of equal and unequal length.
+LONE = [(128, 31, 32), (129, 33, 63), (200, 64, 1), (257, 0, 40), (300, 0, 0), (190, 191, 188), (420, 95, 130)]
+
+
+@pytest.mark.parametrize("scheme", SCHEMES)
+@pytest.mark.parametrize("kind", [ts.GLOBAL, ts.LOCAL], ids=["global", "local"])
+def test_lone_halves_equal_oracle(torch_cuda, kind, scheme):
+    rng = np.random.default_rng(81)
+    sc = ts.scoring(*scheme, kind=kind)
+    for q, n in enumerate(LONE):
+        t = synth.mutated_triplet(rng, max(n), 0.1, lens=n) if q % 2 else tuple(synth.uniform_seq(rng, m) for m in n)
+        want = want_scores([t], scheme, kind)
+        print(f"lone halves kind={kind} scheme={scheme} lens={n}", flush=True)
+        for graph in (False, True):
+            outs, info = run(torch_cuda, [t], sc, reps=3, use_graph=graph)
+            assert info["packed"] == 1 and info["engine"] == 1
+            assert all((o == want).all() for o in outs), (n, outs, want)
+        outs, info = run(torch_cuda, [t], sc, packed=1)
+        assert info["packed"] == 0 and (outs[0] == want).all()
+
+
+@pytest.mark.parametrize("na,packed", [(1588, 1), (1594, 0)])
+@pytest.mark.parametrize("kind", [ts.GLOBAL, ts.LOCAL], ids=["global", "local"])
+def test_window_limit(torch_cuda, kind, na, packed):
+    # Terms of up to 17 per residue pair: a panel's window of a half of 794
+    # residues just fits 16 bits, one of 797 does not (int32 lanes). All-equal
+    # residues make the values grow as fast as they can.
+    sc = ts.scoring(5, -4, -6, kind=kind)
+    t = tuple(np.full(n, 1, np.uint8) for n in (na, 70, 65))
+    print(f"window kind={kind} na={na}", flush=True)
+    outs, info = run(torch_cuda, [t], sc)
+    assert info["packed"] == packed
+    assert (outs[0] == want_scores([t], (5, -4, -6), kind)).all()
+
+
+def test_largest_values(torch_cuda):
+    # 17 per residue pair and all-equal residues: a half's values reach 17 *
+    # (645 + 645 + 1290) of the 65535 that 16 bits recover.
+    for n in (1270, 1290):
+        x = np.full(n, 2, np.uint8)
+        print(f"values n={n}", flush=True)
+        outs, info = run(torch_cuda, [(x, x, x)], ts.scoring(5, -4, -6))
+        assert info["packed"] == 1 and int(outs[0][0]) == 15 * n  # 3 pairs of 5 per column
