@@ -206,7 +206,9 @@ typedef struct trioseq_plan_options {
                              trip); 0 = default */
   int32_t split_factor;   /* automatic engine: a triplet of a batch is split into panel
                              jobs when its cells exceed split_factor times the batch's
-                             mean cells per wavefront (or 2.5e8); 0 = default (4) */
+                             mean cells per wavefront (or 2.5e8); 0 = default (4).
+                             Int32 lanes only: a batch that qualifies for packed
+                             pairs under this engine runs as panel jobs throughout */
   int32_t half_split_min; /* automatic engine, one global or local triplet: scored by
                              two concurrent halves when its longest sequence has at
                              least this many residues; -1 = never; 0 = default (128,
@@ -216,14 +218,17 @@ typedef struct trioseq_plan_options {
                              terms sub - 2*gap are all >= 0 and whose values fit the
                              16-bit range; exact, like the int32 path; a batch that
                              does not qualify runs in int32); 0 = default (2 when the
-                             lane tile is left to the library, else 1) */
+                             lane tile is left to the library, else 1). Under the
+                             automatic engine the pairs (for a lone triplet its two
+                             halves) are swept as panel jobs */
   int32_t staging;        /* packed pairs: 1 = face rows staged through registers into
                              LDS; 2 = loaded straight into LDS (buffer loads to LDS);
                              0 = default */
 } trioseq_plan_options;
 
 typedef struct trioseq_plan_info {
-  int32_t engine;         /* 0 all whole, 1 all split, 2 mixed */
+  int32_t engine;         /* 0 all whole, 1 all split, 2 mixed, by the options' split
+                             rule (packed panel jobs sweep all of them in panels) */
   int32_t tile_rows, tile_cols, grid, waves_per_cu;
   int32_t panels;         /* panel jobs of split triplets */
   int32_t packed;         /* 1: two triplets per lane (16-bit halves); 0: int32 */

@@ -101,7 +101,7 @@ trioseq_status split_level(PlaneWorkspace& ws, const std::vector<Box>& boxes,
     poff[2 * q + 1] = pints;
     pints += (uint64_t)prow * pcol;
     const uint32_t nchunk = (uint32_t)(((uint64_t)prow * pcol + kSplitChunk - 1) / kSplitChunk);
-    sd[q] = SplitDesc{poff[2 * q], poff[2 * q + 1], prow, pcol, (uint32_t)chunk_box.size(), nchunk};
+    sd[q] = SplitDesc{poff[2 * q], poff[2 * q + 1], prow, pcol, (uint32_t)chunk_box.size(), nchunk, 0};
     chunk_box.insert(chunk_box.end(), nchunk, (uint32_t)q);
   }
   trioseq_status st = run_planes(ws, lens.data(), offs.data(), 2 * nb, words.data(), words.size(), sc,

@@ -261,10 +261,11 @@ struct trioseq_plan {
   TripletDesc* d_desc = nullptr;
   JobDesc* d_jobs = nullptr;
   int* d_counter = nullptr;  // job queue head
-  int* d_ctl = nullptr;      // [0] generation, [1] error flag, [2] meeting counter (0 between runs)
+  int* d_ctl = nullptr;      // [0] generation, [1] error flag, [2] meeting counter (0 between runs), [3] highest tag
   int* d_face = nullptr;     // per-wave workspace of whole-triplet jobs
   uint64_t face_stride = 0;
   int* d_pface = nullptr;    // panel-face pool of split triplets
+  uint64_t pool_ints = 0;    // its size (a borrowed plan's: the whole region's)
   int* d_bnd = nullptr;      // sentinel faces
   Boundary bnd{};
   int* d_red = nullptr;      // per-triplet reduction pairs (semi-global, local)
@@ -276,7 +277,9 @@ struct trioseq_plan {
   GatherDesc* d_gather = nullptr;   // 6 gather descriptors
   int* d_plane = nullptr;           // the two last-slice planes
   uint64_t* d_plane_off = nullptr;  // {0, plane ints}
-  SplitDesc* d_sdesc = nullptr;     // the meeting box
+  SplitDesc* d_sdesc = nullptr;     // the meeting boxes, the box of every chunk and a
+  uint32_t* d_chunk_box = nullptr;  // counter each (null for one box, which uses d_ctl[2])
+  int* d_meet = nullptr;
   int* d_partial = nullptr;         // per chunk: its best
   int32_t* d_hscores = nullptr;     // the halves' own scores (unused)
   // graph replay
@@ -291,6 +294,9 @@ struct trioseq_plan {
   // Packed pairs: sentinel faces (top, left) and the stored value of M' = 0.
   bool packed = false;
   uint32_t pk_base = 0, pk_kc = 0;
+  bool pk_self = false;
+  bool pk_reuse = false;
+  int tag_step = 1;
   int* d_pkbnd = nullptr;
   uint64_t pk_top_words = 0;
 };
@@ -315,7 +321,7 @@ static void plan_free(trioseq_plan* p) {
   (void)hipFree(p->d_red);
   (void)hipFree(p->d_pkbnd);
   for (void* q : {(void*)p->d_hwords, (void*)p->d_gather, (void*)p->d_plane, (void*)p->d_plane_off,
-                  (void*)p->d_sdesc, (void*)p->d_partial, (void*)p->d_hscores})
+                  (void*)p->d_sdesc, (void*)p->d_partial, (void*)p->d_hscores, (void*)p->d_chunk_box, (void*)p->d_meet})
     (void)hipFree(q);
   delete p;
 }
@@ -478,6 +484,24 @@ static bool pair_up(Layout* L, const trioseq_scoring& sc, const KernelShape& ks)
   return true;
 }
 
+// Estimated times of a layout's packed panel jobs (see pair_panel_layout).
+struct PkTime {
+  double single_us, wave_pair_us;
+};
+static PkTime pk_panel_time(const Layout& L) {
+  double steps = 0, chain = 0;
+  for (size_t p = 0; p + 1 < L.desc.size(); p += 2) {
+    const TripletDesc &a = L.desc[p], &b = L.desc[p + 1];
+    const double n0 = std::max(a.len[0], b.len[0]) + 1 + kSkew;
+    const double PJ = std::max(a.len[1], b.len[1]) / kPkPanel + 1, PK = std::max(a.len[2], b.len[2]) / kPkPanel + 1;
+    steps += PJ * PK * (n0 + 12);  // (a panel's start costs about 12 steps)
+    chain = std::max(chain, n0 + 21 * (PJ + PK));
+  }
+  // 256 compute units: 2048 single waves, 1024 wave pairs.
+  const double s1 = steps / 2048 * 0.66, c1 = chain * 24 / 21 * 0.4, s2 = steps / 1024 * 0.385, c2 = chain * 0.4;
+  return PkTime{std::max(s1, c1) + 0.4 * std::min(s1, c1), std::max(s2, c2) + 0.25 * std::min(s2, c2)};
+}
+
 // What a pair must keep to for its panels to run packed (the reasons are in
 // packed_panel.hip). With every term >= 0, M' grows by at most `step` per unit
 // of an index, so a panel's window is step * (slices + rows + columns); off
@@ -485,6 +509,8 @@ static bool pair_up(Layout* L, const trioseq_scoring& sc, const KernelShape& ks)
 // itself is recovered from 16 bits where it leaves the panel (score, plane), so
 // it must stay below 2^16: at most maxA per residue pair that two sequences can
 // form, or per residue with the semi-global axes and local floors.
+// Panels that a diagonal of a group of pairs has at least, on average.
+constexpr double kPkWidth = 2048;
 bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, Layout* L) {
   int mina = INT32_MAX, maxa = 0, maxs = 0;
   for (int x = 0; x < 4; ++x)
@@ -520,36 +546,73 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
   L->jobs.clear();
   std::vector<uint32_t> PJ(np), PK(np);
   std::vector<uint64_t> cost(np);
-  uint64_t pool = 0, jobs = 0;
-  uint32_t n0max = 0, diagonals = 0;
+  uint64_t jobs = 0;
+  uint32_t n0max = 0;
   double cells = 0;
   for (size_t p = 0; p < np; ++p) {
     TripletDesc &a = L->desc[2 * p], &b = L->desc[2 * p + 1];
     const uint32_t n0 = std::max(a.len[0], b.len[0]);
     PJ[p] = std::max(a.len[1], b.len[1]) / kPkPanel + 1;
     PK[p] = std::max(a.len[2], b.len[2]) / kPkPanel + 1;
-    a.face_off = b.face_off = pool;
-    pool += (uint64_t)PJ[p] * PK[p] * pk_panel_ints(n0);
     jobs += (uint64_t)PJ[p] * PK[p];
     cost[p] = (uint64_t)PJ[p] * PK[p] * (n0 + 1 + kSkew);
     n0max = std::max(n0max, n0);
-    diagonals = std::max(diagonals, PJ[p] + PK[p] - 1);
     cells += (double)a.len[0] * a.len[1] * a.len[2] + (double)b.len[0] * b.len[1] * b.len[2];
   }
   if (jobs > (uint64_t)INT32_MAX / 2) return false;
-  // By anti-diagonal across all pairs, the costlier pairs first within one:
-  // every panel comes after those it reads from, and the pairs' pipelines
-  // fill together.
+  // In groups of pairs, by anti-diagonal across a group's pairs (the costlier
+  // first): every panel comes after those it reads from, and a diagonal of a
+  // group has about as many panels as single waves fit the device, so that the
+  // panels of the next one rarely wait for them. (8192 triplets of 100-400
+  // residues: 27.8 ms with 512 panels a diagonal, 26.7 with 2048 and with all
+  // pairs in one group.) Two sets of face buffers serve the groups in turn: a
+  // group's panels start when all jobs of the group two before are finished,
+  // which is long before they are popped.
   std::vector<size_t> idx(np);
   std::iota(idx.begin(), idx.end(), 0);
   std::stable_sort(idx.begin(), idx.end(), [&](size_t x, size_t y) { return cost[x] > cost[y]; });
   L->jobs.reserve(jobs);
-  for (uint32_t d = 0; d < diagonals; ++d)
-    for (size_t p : idx) {
-      if (d + 1 >= PJ[p] + PK[p]) continue;
-      for (uint32_t pj = (d >= PK[p] ? d - PK[p] + 1 : 0); pj <= std::min(d, PJ[p] - 1); ++pj)
-        L->jobs.push_back(JobDesc{(uint32_t)(2 * p), pj * PK[p] + (d - pj)});
+  uint64_t region[2] = {0, 0}, done[2] = {0, 0};  // per set: ints of buffers, jobs of its groups so far
+  uint64_t tags = 0;
+  uint32_t group = 0;
+  std::vector<std::pair<size_t, size_t>> groups;
+  for (size_t g0 = 0; g0 < np; ++group) {
+    const size_t before = L->jobs.size();
+    double width = 0;
+    size_t g1 = g0;
+    uint32_t gd = 0, longest = 0;
+    uint64_t at = 0;
+    while (g1 < np && width < kPkWidth) {
+      const size_t p = idx[g1++];
+      width += (double)PJ[p] * PK[p] / (PJ[p] + PK[p] - 1);
+      gd = std::max(gd, PJ[p] + PK[p] - 1);
+      longest = std::max({longest, PJ[p], PK[p]});
+      TripletDesc &a = L->desc[2 * p], &b = L->desc[2 * p + 1];
+      a.face_off = at;
+      a.set = group & 1;
+      a.after = (uint32_t)done[group & 1];
+      a.tag0 = (uint32_t)tags;
+      at += pk_pair_ints(std::max(a.len[0], b.len[0]), PJ[p], PK[p]);
     }
+    for (uint32_t d = 0; d < gd; ++d)
+      for (size_t q = g0; q < g1; ++q) {
+        const size_t p = idx[q];
+        if (d + 1 >= PJ[p] + PK[p]) continue;
+        for (uint32_t pj = (d >= PK[p] ? d - PK[p] + 1 : 0); pj <= std::min(d, PJ[p] - 1); ++pj)
+          L->jobs.push_back(JobDesc{(uint32_t)(2 * p), pj * PK[p] + (d - pj)});
+      }
+    region[group & 1] = std::max(region[group & 1], at);
+    done[group & 1] += L->jobs.size() - before;
+    tags += longest + 1;
+    groups.emplace_back(g0, g1);
+    g0 = g1;
+  }
+  for (size_t g = 1; g < groups.size(); g += 2)
+    for (size_t q = groups[g].first; q < groups[g].second; ++q) L->desc[2 * idx[q]].face_off += region[0];
+  if (tags + 2 > (1u << 24)) return false;
+  const uint64_t pool = region[0] + region[1];
+  L->pk_reuse = groups.size() > 2;
+  L->tag_step = (int)tags + 2;
   L->ks = KernelShape{4, 4, 2};
   L->kind = sc.kind;
   L->planes = planes;
@@ -563,12 +626,118 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
   L->packed = true;
   L->pk_base = (uint32_t)off;
   L->pk_kc = (uint32_t)kc;
+  // Single-wave workgroups (two computing waves on a SIMD) or a computing and a
+  // memory wave each (shorter hops from panel to panel): whichever the batch's
+  // total work and its longest chain of panels make faster, at the steps both
+  // were measured to take: 0.66 us a step of a single wave (two share a SIMD),
+  // 0.385 us of a computing wave; a panel starts 24 or 21 steps after its
+  // neighbour. Lone 1024 x 1000 x 1048: 0.82 ms single, 0.62 ms in pairs; 2560 x
+  // 2500 x 2600: 3.49 and 3.48; 3072 x 3000 x 3120: 5.13 and 5.74; 4096 x 4000 x
+  // 4150: 10.9 and 12.9.
+  const PkTime t = pk_panel_time(*L);
+  L->pk_self = t.single_us < t.wave_pair_us;
+  return true;
+}
+
+// The halves of a triplet as two descriptors (the longest sequence cut in two,
+// the second half read backwards), and the size of their last slices.
+static void half_descs(const uint32_t* l, const uint64_t* off, TripletDesc d[2], SplitDesc* box) {
+  int ax = 0;
+  for (int q = 1; q < 3; ++q)
+    if (l[q] > l[ax]) ax = q;
+  const int order[3] = {ax, ax == 0 ? 1 : 0, ax == 2 ? 1 : 2};
+  const uint32_t mid = l[ax] / 2;
+  for (int h = 0; h < 2; ++h) {
+    d[h] = TripletDesc{};
+    for (int k = 0; k < 3; ++k) {
+      d[h].off[k] = off[order[k]];
+      d[h].len[k] = l[order[k]];
+      d[h].start[k] = 0;
+    }
+    d[h].len[0] = h ? l[ax] - mid : mid;
+    d[h].start[0] = h ? mid : 0;
+    d[h].rev = (uint32_t)h;
+  }
+  *box = SplitDesc{0, 0, l[order[1]] + 1, l[order[2]] + 1, 0, 0, 0};
+}
+
+bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L) {
+  std::vector<size_t> split(n);
+  std::iota(split.begin(), split.end(), 0);
+  std::vector<AxisChoice> ax(n);
+  for (size_t t = 0; t < n; ++t) ax[t] = choose_axes_wide(lens + 3 * t);
+
+  // Panel pairs: neighbours by size, or each triplet's own two halves (global
+  // and local scoring), whichever the times above make shorter.
+  Layout P, H;
+  bool have_p = false, have_h = false;
+  {
+    std::vector<TripletDesc> d;
+    // By the panels of the common grid, then by the slices.
+    const auto key = [&](size_t t) {
+      const uint32_t* l = lens + 3 * t;
+      const uint32_t pj = l[ax[t].perm[1]] / kPkPanel + 1, pk = l[ax[t].perm[2]] / kPkPanel + 1;
+      return std::make_tuple(pj * pk, pj, l[ax[t].perm[0]]);
+    };
+    std::stable_sort(split.begin(), split.end(), [&](size_t a, size_t b) { return key(a) > key(b); });
+    for (size_t q = 0; q < n + n % 2; ++q) {
+      const size_t t = split[std::min(q, n - 1)];
+      TripletDesc e{};
+      for (int k = 0; k < 3; ++k) {
+        e.off[k] = off[3 * t + ax[t].perm[k]];
+        e.len[k] = lens[3 * t + ax[t].perm[k]];
+      }
+      e.out = (uint32_t)t;
+      d.push_back(e);
+    }
+    have_p = pair_panel_layout(d, sc, false, &P);
+  }
+  if (sc.kind != kSemiGlobal) {
+    std::vector<TripletDesc> d;
+    uint64_t ints = 0;
+    uint32_t chunks = 0;
+    for (size_t t : split) {
+      TripletDesc h[2];
+      SplitDesc box;
+      half_descs(lens + 3 * t, off + 3 * t, h, &box);
+      h[0].out = h[1].out = box.out = (uint32_t)t;
+      const uint64_t cells = (uint64_t)box.rows * box.cols;
+      box.fwd = ints;
+      box.bwd = ints + cells;
+      box.chunk0 = chunks;
+      box.nchunk = (uint32_t)((cells + kSplitChunk - 1) / kSplitChunk);
+      H.plane_off.push_back(box.fwd);
+      H.plane_off.push_back(box.bwd);
+      H.chunk_box.insert(H.chunk_box.end(), box.nchunk, (uint32_t)H.boxes.size());
+      H.boxes.push_back(box);
+      ints += 2 * cells;
+      chunks += box.nchunk;
+      d.insert(d.end(), h, h + 2);
+    }
+    H.plane_ints = ints;
+    H.halves = true;
+    have_h = pair_panel_layout(d, sc, true, &H);
+  }
+  if (!have_p && !have_h) return false;
+  // (The halves' estimate leaves out their second start per panel and their
+  // meeting: measured, they had to be ahead by 3 % on single waves, 25 % on wave
+  // pairs. 16 triplets of 800-1200 residues: 2.84 ms by halves, 3.10 in pairs;
+  // four of 1000: 1.27 and 1.11; 2000 of 100-400: 8.5 and 6.6.)
+  bool use_h = have_h;
+  if (have_h && have_p) {
+    const PkTime h = pk_panel_time(H), p = pk_panel_time(P);
+    use_h = std::min(h.single_us * 1.03, h.wave_pair_us * 1.25) < std::min(p.single_us, p.wave_pair_us);
+  }
+  Layout& Q = use_h ? H : P;
+  Q.cells = L->cells;
+  Q.engine = L->engine;  // (reported: which triplets the split rule of the options calls split)
+  *L = std::move(Q);
   return true;
 }
 
 trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
                             const trioseq_scoring& sc, const trioseq_plan_options& o, int waves_hint,
-                            Layout* L, bool planes) {
+                            Layout* L, bool planes, bool packed_panels) {
   if (n && !lens) return fail(TRIOSEQ_ERR_INVALID_ARG, "lens is NULL");
   if (n > (size_t)INT32_MAX) return fail(TRIOSEQ_ERR_TOO_LARGE, "too many triplets");
   trioseq_status st = validate_scoring(&sc);
@@ -709,14 +878,20 @@ trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
   // or by default when the tile is left to the library (4 x 4, two waves per
   // SIMD); the batch keeps int32 lanes when it does not qualify (pair_up).
   L->packed = false;
+  const bool default_shape = (o.tile_rows == 0 || o.tile_rows == 4) && (o.tile_cols == 0 || o.tile_cols == 4) &&
+                             (o.waves_per_simd == 0 || o.waves_per_simd == 2) && o.lane_exchange != 2 && o.staging != 2;
+  const bool any_shape = o.tile_rows || o.tile_cols || o.waves_per_simd || o.lane_exchange || o.staging;
+  if (packed_panels && !planes && n > 1 && o.engine == -1 && !o.grid && ks.group == 1 &&
+      (o.packed == 2 ? default_shape : o.packed == 0 && !any_shape) &&
+      packed_batch_layout(lens, off, n, sc, L))
+    return TRIOSEQ_OK;
   if (o.packed == 2) {
     KernelShape pks{o.tile_rows ? o.tile_rows : 4, o.tile_cols ? o.tile_cols : 4,
                     o.waves_per_simd ? o.waves_per_simd : 2};
     pks.xch = o.lane_exchange == 2 ? 1 : 0;
     pks.dma = o.staging == 2 ? 1 : 0;
     pair_up(L, sc, pks);
-  } else if (o.packed == 0 && !o.tile_rows && !o.tile_cols && !o.waves_per_simd && !o.lane_exchange &&
-             !o.staging) {
+  } else if (o.packed == 0 && !any_shape) {
     pair_up(L, sc, KernelShape{4, 4, 2});
   }
   if (!L->packed && !int32_shape)
@@ -790,7 +965,7 @@ static hipError_t cached_occupancy(const Layout& L, int device, int* w) {
   const std::string key = std::to_string(device) + "/" + std::to_string(L.ks.rj) + "x" +
                           std::to_string(L.ks.rk) + "/" + std::to_string(L.ks.wpe) + "/" +
                           std::to_string(L.ks.group) + "/" + std::to_string(L.ks.xch) + "/" +
-                          std::to_string((int)L.packed) + "/" +
+                          std::to_string((int)L.packed + 2 * (int)L.pk_self) + "/" +
                           std::to_string(L.modes) + "/" + std::to_string(L.kind) + "/" +
                           std::to_string((int)L.planes) + "/" + std::to_string(shift_lds_bytes(L.lds_n0));
   {
@@ -801,7 +976,7 @@ static hipError_t cached_occupancy(const Layout& L, int device, int* w) {
         return hipSuccess;
       }
   }
-  hipError_t e = L.modes == kModePkPanel ? panel_pk_occupancy(L.kind, L.planes, L.lds_n0, w)
+  hipError_t e = L.modes == kModePkPanel ? panel_pk_occupancy(L.kind, L.planes, L.pk_self, L.lds_n0, w)
                  : L.packed ? sweep_pk_occupancy(L.ks, L.kind, L.lds_n0, w)
                          : sweep_occupancy(L.ks, L.modes, L.kind, L.planes, L.lds_n0, w);
   if (e == hipSuccess && L.modes == 2 && L.ks.group > 1) {
@@ -826,7 +1001,7 @@ trioseq_status layout_grid(const Layout& L, const DeviceProps& dp, int requested
   *grid = g;
   // Waves per compute unit: workgroups of 1 (whole triplets), 2 (panel jobs)
   // or 2 * kStripPanels (strip jobs) waves.
-  *waves_per_cu = w * (L.modes == 1 || L.modes == 3 ? 1 : L.ks.group > 1 ? 2 * kStripPanels : 2);
+  *waves_per_cu = w * (L.modes == 1 || L.modes == 3 || L.pk_self ? 1 : L.ks.group > 1 ? 2 * kStripPanels : 2);
   return TRIOSEQ_OK;
 }
 
@@ -862,15 +1037,10 @@ bool half_split_layout(const uint32_t* lens, const uint64_t* word_off, int32_t m
       h->lens[i] = len;
       h->offs[i] = w;
       h->gather[i] = GatherDesc{src[q], w, start, len, (uint32_t)half};
-      TripletDesc& pd = h->pair[half];
-      pd.off[k] = src[q];
-      pd.len[k] = len;
-      pd.start[k] = start;
-      pd.out = (uint32_t)half;
-      pd.face_off = 0;
-      pd.rev = (uint32_t)half;
       w += (len + 15) / 16;
     }
+  SplitDesc box;
+  half_descs(lens, src, h->pair, &box);
   h->words = (uint32_t)w;
   h->rows = lens[r] + 1;
   h->cols = lens[c] + 1;
@@ -908,13 +1078,14 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   // layout is redone if the device's size changes the split rule's hint.
   Layout L;
   int hint = 256 * kWavesPerCuHint;
-  trioseq_status st = build_layout(lens, word_off, n, *scp, o, hint, &L);
+  const bool panels = mem == nullptr;  // (a carved plan keeps to the int32 layout's memory limits)
+  trioseq_status st = build_layout(lens, word_off, n, *scp, o, hint, &L, false, panels);
   if (st != TRIOSEQ_OK) return st;
   // A lone global or local triplet under the automatic options is scored by
   // halves (local: the best of the two halves' own bests and of the paths
   // that cross the middle plane).
   HalfSplit hs;
-  const bool half = defaults && half_split_choice(lens, word_off, n, scp->kind, o, &hs);
+  bool half = defaults && half_split_choice(lens, word_off, n, scp->kind, o, &hs);
   const trioseq_plan_options ho{-1, 4, 4, 0, 0, 2, o.panel_group, o.lane_exchange};  // the plane kernels' shape
   DeviceProps dp;
   st = device_props(&dp);
@@ -922,7 +1093,7 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   if (half || dp.cus * kWavesPerCuHint != hint) {
     hint = dp.cus * kWavesPerCuHint;
     st = half ? build_layout(hs.lens, hs.offs, 2, *scp, ho, hint, &L, true)
-              : build_layout(lens, word_off, n, *scp, o, hint, &L);
+              : build_layout(lens, word_off, n, *scp, o, hint, &L, false, panels);
     if (st != TRIOSEQ_OK) return st;
   }
   // A batch carved from a region whose pool cannot hold its split triplets'
@@ -934,14 +1105,39 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   }
   // The halves run as one packed pair where their values fit 16 bits: one
   // sweep of 3.5 instructions per cell over both, against 7 in int32 (the
-  // 1024 x 1000 x 1048 triplet 975 -> 727 us, 4096 x 4000 x 4150 31.3 -> 15.5 ms).
-  if (half && o.packed != 1 && o.panel_group <= 1) {
+  // 1024 x 1000 x 1048 triplet 975 -> 620 us, 4096 x 4000 x 4150 31.3 -> 10.9 ms).
+  // Packed, they also beat the classic split on long local triplets, which
+  // stay on it in int32 (2048 x 2000 x 2080: 5.62 -> 2.58 ms, 4096 x 4000 x
+  // 4150: 38.8 -> 14.6 ms).
+  const bool may_pack = o.packed != 1 && o.panel_group <= 1;
+  const bool long_local = defaults && !half && n == 1 && !mem && may_pack && scp->kind == kLocal &&
+                          o.half_split_min == 0 && o.lane_exchange != 2 && L.cells >= kSplitCells &&
+                          half_split_layout(lens, word_off, 0, &hs);
+  if ((half && may_pack) || long_local) {
     const uint64_t int32_pool = L.pool_ints * sizeof(int);
     Layout P;
     if (pair_panel_layout({hs.pair[0], hs.pair[1]}, *scp, true, &P)) {
       if (mem && int32_pool > mem->pool_bytes)
         return fail(TRIOSEQ_ERR_TOO_LARGE,
                     "allocation-free scoring: panel faces of split triplets exceed the scratch array's face pool");
+      P.cells = L.cells;
+      const uint64_t cells = (uint64_t)hs.rows * hs.cols;
+      P.halves = true;
+      P.boxes = {SplitDesc{0, cells, hs.rows, hs.cols, 0, (uint32_t)((cells + kSplitChunk - 1) / kSplitChunk), 0}};
+      P.plane_off = {0, cells};
+      P.plane_ints = 2 * cells;
+      L = std::move(P);
+      half = true;
+    }
+  }
+  // A lone semi-global triplet runs as a pair with itself: per cell as many
+  // instructions as int32 lanes take, but the packed kernel's shorter hops and
+  // polls (723 x 651 x 698: 824 -> 721 us, 1024 x 1000 x 1048: 1.33 -> 1.15 ms).
+  if (n == 1 && scp->kind == kSemiGlobal && defaults && may_pack && !mem && o.lane_exchange != 2 && L.modes == 2) {
+    const TripletDesc& d = L.desc[0];
+    Layout P;
+    if (pair_panel_layout({d, d}, *scp, false, &P)) {
+      P.panels /= 2;
       P.cells = L.cells;
       L = std::move(P);
     }
@@ -1011,7 +1207,7 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
     p->d_ctl = mem->ctl;
     p->d_counter = mem->counter;
   } else {
-    if ((e = hipMalloc((void**)&p->d_counter, 256)) != hipSuccess) return hip_bail(e, "hipMalloc");
+    if ((e = hipMalloc((void**)&p->d_counter, kCounterBytes)) != hipSuccess) return hip_bail(e, "hipMalloc");
     if ((e = hipMalloc((void**)&p->d_ctl, 256)) != hipSuccess) return hip_bail(e, "hipMalloc");
     if ((e = hipMemsetAsync(p->d_ctl, 0, 256, is)) != hipSuccess) return hip_bail(e, "hipMemset");
   }
@@ -1027,14 +1223,18 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
                             hipMemcpyHostToDevice, is)) != hipSuccess)
       return hip_bail(e, "hipMemcpy jobs");
   }
+  if (mem) {
+    p->d_pface = mem->pool;
+    p->pool_ints = mem->pool_bytes / 4;
+  }
   if (pool_bytes) {
     if (mem) {
       // The region's pool part only ever holds (value, tag) pairs at even
       // offsets from its fixed base, or the zeros it started with.
       if (pool_bytes > mem->pool_bytes)
         return too_large("panel faces of split triplets exceed the scratch array's face pool");
-      p->d_pface = mem->pool;
     } else {
+      p->pool_ints = L.pool_ints;
       // Tagged faces start at tag 0, which no run uses, so nothing stale matches.
       if ((e = hipMalloc((void**)&p->d_pface, pool_bytes)) != hipSuccess)
         return hip_bail(e, "hipMalloc panel faces");
@@ -1049,6 +1249,9 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   p->packed = L.packed;
   p->pk_base = L.pk_base;
   p->pk_kc = L.pk_kc;
+  p->pk_self = L.pk_self;
+  p->pk_reuse = L.pk_reuse;
+  p->tag_step = L.tag_step;
   // (Packed panel jobs make their own edge values.)
   const uint64_t bnd_ints = pk_panel ? 0 : boundary_ints(L.ks, L.lds_n0);
   if (bnd_ints && (e = dalloc((void**)&p->d_bnd, bnd_ints * sizeof(int))) != hipSuccess)
@@ -1064,35 +1267,45 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
     if ((e = dalloc((void**)&p->d_pkbnd, words * 4)) != hipSuccess) return region_fail(e, "packed sentinel faces");
     if ((e = launch_fill_packed_sentinel((uint32_t*)p->d_pkbnd, words, is)) != hipSuccess)
       return hip_bail(e, "packed sentinel faces");
-    p->workspace_bytes += words * 4;
   }
-  p->workspace_bytes = pool_bytes + bnd_ints * sizeof(int) +
+  p->workspace_bytes = pool_bytes + (L.packed && !pk_panel ? (p->pk_top_words + face_rows(L.lds_n0) * right_face_row(L.ks)) * 4 : 0) + bnd_ints * sizeof(int) +
                        (uint64_t)p->red_pairs * 2 * sizeof(int) +
                        nd * sizeof(TripletDesc) + L.jobs.size() * sizeof(JobDesc) + 512;
-  if (half) {
+  if (half || L.halves) {
     p->half = true;
-    p->h_words_n = pk_panel ? 0 : hs.words;
-    const uint64_t pints = (uint64_t)hs.rows * hs.cols;
-    p->h_nchunk = (uint32_t)((pints + kSplitChunk - 1) / kSplitChunk);
-    const uint64_t plane_off[2] = {0, pints};
-    const SplitDesc box{0, pints, hs.rows, hs.cols, 0, p->h_nchunk};
-    if ((!pk_panel && ((e = dalloc((void**)&p->d_hwords, std::max<uint64_t>(hs.words, 1) * 4)) != hipSuccess ||
-                       (e = dalloc((void**)&p->d_gather, sizeof hs.gather)) != hipSuccess)) ||
-        (e = dalloc((void**)&p->d_plane, 2 * pints * 4)) != hipSuccess ||
-        (e = dalloc((void**)&p->d_plane_off, sizeof plane_off)) != hipSuccess ||
-        (e = dalloc((void**)&p->d_sdesc, sizeof box)) != hipSuccess ||
-        (e = dalloc((void**)&p->d_partial, p->h_nchunk * 4)) != hipSuccess ||
-        (e = dalloc((void**)&p->d_hscores, 8)) != hipSuccess)
+    if (!L.halves) {
+      // (int32 halves of a lone triplet, gathered in every run.)
+      const uint64_t cells = (uint64_t)hs.rows * hs.cols;
+      L.boxes = {SplitDesc{0, cells, hs.rows, hs.cols, 0, (uint32_t)((cells + kSplitChunk - 1) / kSplitChunk), 0}};
+      L.plane_off = {0, cells};
+      L.plane_ints = 2 * cells;
+      p->h_words_n = hs.words;
+      if ((e = dalloc((void**)&p->d_hwords, std::max<uint64_t>(hs.words, 1) * 4)) != hipSuccess ||
+          (e = dalloc((void**)&p->d_gather, sizeof hs.gather)) != hipSuccess ||
+          (e = dalloc((void**)&p->d_hscores, 8)) != hipSuccess)
+        return region_fail(e, "half-split buffers");
+      if ((e = hipMemcpyAsync(p->d_gather, hs.gather, sizeof hs.gather, hipMemcpyHostToDevice, is)) != hipSuccess)
+        return hip_bail(e, "half-split buffers");
+    }
+    const size_t nb = L.boxes.size();
+    p->h_nchunk = L.boxes.back().chunk0 + L.boxes.back().nchunk;
+    if ((e = dalloc((void**)&p->d_plane, L.plane_ints * 4)) != hipSuccess ||
+        (e = dalloc((void**)&p->d_plane_off, L.plane_off.size() * 8)) != hipSuccess ||
+        (e = dalloc((void**)&p->d_sdesc, nb * sizeof(SplitDesc))) != hipSuccess ||
+        (e = dalloc((void**)&p->d_partial, (uint64_t)p->h_nchunk * 4)) != hipSuccess ||
+        (nb > 1 && ((e = dalloc((void**)&p->d_chunk_box, (uint64_t)p->h_nchunk * 4)) != hipSuccess ||
+                    (e = dalloc((void**)&p->d_meet, nb * 4)) != hipSuccess)))
       return region_fail(e, "half-split buffers");
-    if ((!pk_panel &&
-         (e = hipMemcpyAsync(p->d_gather, hs.gather, sizeof hs.gather, hipMemcpyHostToDevice, is)) != hipSuccess) ||
-        (e = hipMemcpyAsync(p->d_plane_off, plane_off, sizeof plane_off, hipMemcpyHostToDevice, is)) !=
+    if ((e = hipMemcpyAsync(p->d_plane_off, L.plane_off.data(), L.plane_off.size() * 8, hipMemcpyHostToDevice, is)) !=
             hipSuccess ||
-        (e = hipMemcpyAsync(p->d_sdesc, &box, sizeof box, hipMemcpyHostToDevice, is)) != hipSuccess)
+        (e = hipMemcpyAsync(p->d_sdesc, L.boxes.data(), nb * sizeof(SplitDesc), hipMemcpyHostToDevice, is)) !=
+            hipSuccess ||
+        (nb > 1 && ((e = hipMemcpyAsync(p->d_chunk_box, L.chunk_box.data(), (uint64_t)p->h_nchunk * 4,
+                                        hipMemcpyHostToDevice, is)) != hipSuccess ||
+                    (e = hipMemsetAsync(p->d_meet, 0, nb * 4, is)) != hipSuccess)))
       return hip_bail(e, "half-split buffers");
-    p->workspace_bytes += 2 * pints * 4 + (uint64_t)p->h_words_n * 4 + p->h_nchunk * 4 + 256;
-    // The host sources of these copies live until this function returns.
-    if ((e = hipStreamSynchronize(is)) != hipSuccess) return hip_bail(e, "plan init");
+    p->workspace_bytes += L.plane_ints * 4 + (uint64_t)p->h_words_n * 4 + (uint64_t)p->h_nchunk * 8 +
+                          nb * (sizeof(SplitDesc) + 20);
   }
   // The whole-triplet workspace comes last: a carved plan launches no more
   // waves than the rest of the region holds workspaces for.
@@ -1173,9 +1386,9 @@ trioseq_status run_planes(PlaneWorkspace& ws, const uint32_t* lens, const uint64
     if ((e = (call)) != hipSuccess) return fail_hip(e, what); \
   } while (0)
   if (!ws.ctl.p) {
-    // [0] generation, [1] error flag, [64] queue head; the generation keeps
-    // growing across runs, so a zeroed pool's tags (0) are never current.
-    WS(ws_grow(ws.ctl, 512, true, s), "align: workspace");
+    // [0] generation, [1] error flag, [64] queue head and counters; the generation
+    // keeps growing across runs, so a zeroed pool's tags (0) are never current.
+    WS(ws_grow(ws.ctl, 256 + kCounterBytes, true, s), "align: workspace");
   }
   WS(ws_grow(ws.desc, n * sizeof(TripletDesc), false, s), "align: workspace");
   WS(ws_grow(ws.jobs, L.jobs.size() * sizeof(JobDesc), false, s), "align: workspace");
@@ -1205,7 +1418,7 @@ trioseq_status run_planes(PlaneWorkspace& ws, const uint32_t* lens, const uint64
   WS(hipMemcpyAsync(ws.plane_off.p, plane_off, n * 8, hipMemcpyHostToDevice, s), "align: upload");
   if (nwords) WS(hipMemcpyAsync(ws.words.p, words, nwords * 4, hipMemcpyHostToDevice, s), "align: upload");
   int* ctl = (int*)ws.ctl.p;
-  WS(launch_prepare(ctl, ctl + 64, nullptr, 0, s), "align: prepare");
+  WS(launch_prepare(ctl, ctl + 64, nullptr, 0, (int*)ws.pool.p, ws.pool.bytes / 4, L.tag_step, s), "align: prepare");
   SweepArgs a = make_sweep_args((const uint32_t*)ws.words.p, (const TripletDesc*)ws.desc.p,
                                 (const JobDesc*)ws.jobs.p, (uint32_t)ws.h_jobs.size(), L.lds_n0,
                                 (int32_t*)ws.scores.p, ctl + 64, ctl, (int*)ws.face.p, L.face_stride,
@@ -1231,37 +1444,39 @@ static hipError_t plan_enqueue(trioseq_plan* p, const uint32_t* d_words, int32_t
                                hipStream_t s) {
   if (p->n == 0) return hipSuccess;
   hipError_t e;
+  const bool pk_panel = p->modes == kModePkPanel;
+  // The int32 halves are gathered in every run (the gather kernel also prepares
+  // the run when there are no reduction pairs to reset); packed jobs read them
+  // from the caller's words in place.
+  const bool gather = p->half && !pk_panel;
+  if ((!gather || p->red_pairs) &&
+      (e = launch_prepare(p->d_ctl, p->d_counter, p->d_red, p->red_pairs, p->d_pface, p->pool_ints, p->tag_step, s)) != hipSuccess)
+    return e;
+  if (gather &&
+      (e = launch_gather(d_words, p->d_gather, 6, p->h_words_n, p->d_hwords, p->red_pairs ? nullptr : p->d_ctl,
+                         p->d_counter, p->d_pface, p->pool_ints, s)) != hipSuccess)
+    return e;
+  SweepArgs a = make_sweep_args(gather ? p->d_hwords : d_words, p->d_desc, p->d_jobs, p->njobs, p->lds_n0,
+                                gather ? p->d_hscores : d_scores, p->d_counter, p->d_ctl, p->d_face,
+                                p->face_stride, p->d_pface, p->bnd, p->d_red, p->sc);
+  const int* pk_left = p->d_pkbnd + p->pk_top_words;
   if (p->half) {
-    // Gather the halves (and prepare the run: the gather kernel does it when
-    // there are no reduction pairs to reset), sweep both (writing their last
-    // slices), meet. Under local scoring each half leaves its own best in
-    // d_hscores[0..1] and the meet takes them with the crossing paths' best.
-    // A packed pair reads both halves from the caller's words in place.
-    const bool pair = p->modes == kModePkPanel, red = p->red_pairs != 0;
-    if ((red || pair) && (e = launch_prepare(p->d_ctl, p->d_counter, p->d_red, p->red_pairs, s)) != hipSuccess) return e;
-    if (!pair && (e = launch_gather(d_words, p->d_gather, 6, p->h_words_n, p->d_hwords, red ? nullptr : p->d_ctl,
-                                    p->d_counter, s)) != hipSuccess)
-      return e;
-    SweepArgs a = make_sweep_args(pair ? d_words : p->d_hwords, p->d_desc, p->d_jobs, p->njobs, p->lds_n0, p->d_hscores,
-                                  p->d_counter, p->d_ctl, p->d_face, p->face_stride, p->d_pface, p->bnd,
-                                  p->d_red, p->sc);
     a.plane = p->d_plane;
     a.plane_off = p->d_plane_off;
-    e = pair ? launch_panel_pk(p->sc.kind, a, p->pk_base, p->pk_kc, p->grid, s)
-             : launch_sweep(p->ks, p->modes, a, p->grid, s);
-    if (e != hipSuccess) return e;
-    return launch_meet(p->d_sdesc, p->h_nchunk, p->d_plane, p->d_partial, p->d_ctl + 1,
-                       p->sc.kind == kLocal ? p->d_hscores : nullptr, p->d_ctl + 2, d_scores, s);
   }
-  if ((e = launch_prepare(p->d_ctl, p->d_counter, p->d_red, p->red_pairs, s)) != hipSuccess)
-    return e;
-  SweepArgs a = make_sweep_args(d_words, p->d_desc, p->d_jobs, p->njobs, p->lds_n0, d_scores,
-                                p->d_counter, p->d_ctl, p->d_face, p->face_stride, p->d_pface,
-                                p->bnd, p->d_red, p->sc);
-  if (p->packed)
-    return launch_sweep_pk(p->ks, p->sc.kind, a, p->d_pkbnd, p->d_pkbnd + p->pk_top_words, p->pk_base,
-                           p->pk_kc, p->grid, s);
-  return launch_sweep(p->ks, p->modes, a, p->grid, s);
+  if (pk_panel) {
+    e = launch_panel_pk(p->sc.kind, p->pk_self, a, p->pk_base, p->pk_kc, p->pk_reuse, p->grid, s);
+  } else if (p->packed) {
+    e = launch_sweep_pk(p->ks, p->sc.kind, a, p->d_pkbnd, pk_left, p->pk_base, p->pk_kc, p->grid, s);
+  } else {
+    e = launch_sweep(p->ks, p->modes, a, p->grid, s);
+  }
+  if (e != hipSuccess || !p->half) return e;
+  // The planes of the halves meet. Under local scoring the score is the best
+  // of the crossing paths and the halves' own bests.
+  const int* own = p->sc.kind != kLocal ? nullptr : pk_panel ? p->d_red : p->d_hscores;
+  return launch_meet(p->d_sdesc, p->d_chunk_box, p->h_nchunk, p->d_plane, p->d_partial, p->d_ctl + 1, own,
+                     pk_panel ? 2 : 1, p->d_meet ? p->d_meet : p->d_ctl + 2, d_scores, s);
 }
 
 trioseq_status trioseq_plan_run(trioseq_plan* p, const uint32_t* d_words, int32_t* d_scores,

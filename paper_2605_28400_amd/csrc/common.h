@@ -93,6 +93,16 @@ struct Layout {
   bool packed = false;
   uint32_t pk_base = 0;
   uint32_t pk_kc = 0;
+  bool pk_self = false;  // panel jobs by single-wave workgroups
+  bool pk_reuse = false; // pairs reuse face buffers (launch_panel_pk's count)
+  int tag_step = 1;      // tags a run uses
+  // Halves (panel pairs that are the two halves of one triplet): what the
+  // meeting of their planes needs.
+  bool halves = false;
+  std::vector<SplitDesc> boxes;      // one per triplet
+  std::vector<uint32_t> chunk_box;
+  std::vector<uint64_t> plane_off;   // two per box
+  uint64_t plane_ints = 0;
   // Per-triplet reduction pairs the run needs (semi-global and local scoring
   // of split triplets): 2 * red_pairs ints.
   uint32_t red_pairs() const { return kind != 0 && (modes & (2 | kModePkPanel)) ? (uint32_t)desc.size() : 0u; }
@@ -102,13 +112,17 @@ struct Layout {
 // Touches no device state.
 // waves_hint: wavefronts the launch will have (for the split rule).
 // planes: the layout of a traceback plane run (axes kept as given, S0 swept).
+// packed_panels: packed panel jobs may be used (packed_batch_layout).
 trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
                             const trioseq_scoring& sc, const trioseq_plan_options& o, int waves_hint,
-                            Layout* L, bool planes = false);
+                            Layout* L, bool planes = false, bool packed_panels = false);
 // Lays out pairs (desc entries 2p, 2p + 1, axes assigned) as packed panel jobs
 // in dependency order; false if a pair's values could leave the 16-bit range
 // under this scoring.
 bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, Layout* L);
+// Lays out a batch as packed panel jobs of pairs: neighbours by size, or the
+// halves of every triplet. False if a value could leave the 16-bit range.
+bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L);
 // Pairs per workgroup of panel-only plans unless the options say otherwise.
 constexpr int kDefaultPanelGroup = 1;
 // Lane exchange (KernelShape::xch) unless the options say otherwise.
@@ -127,7 +141,7 @@ trioseq_status layout_grid(const Layout& L, const DeviceProps& dp, int requested
 // allocation-free entry point). plain: any data, carved in order; pool: only
 // ever (value, tag) face pairs at even int offsets from its fixed base, or the
 // zeros it started with, so a tag slot never holds a value; ctl (generation
-// word, error flag, half-split meeting counter, at least 3 ints, zeroed
+// word, error flag, half-split meeting counter, highest tag; zeroed
 // before first use) and counter (queue head) persist from call to call, and
 // the generation only grows, so no stale tag ever looks current. stream:
 // where the plan's initialisation runs (the caller's).

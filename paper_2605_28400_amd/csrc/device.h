@@ -31,6 +31,8 @@ __device__ __forceinline__ uint32_t pick4(uint32_t code, uint32_t t0, uint32_t t
   return code == 0 ? t0 : code == 1 ? t1 : code == 2 ? t2 : t3;
 }
 
+constexpr int kTagAlways = 0x7FFFFFFF;
+
 // A wait that gave up: the run's error flag is raised, and the release fence
 // orders it before every store the wave issues afterwards. A panel that gave
 // up goes on with whatever its faces hold, so the flag must become visible
@@ -53,9 +55,30 @@ __device__ __forceinline__ void publish_score(int32_t* so, int v, const int* err
   __hip_atomic_store(so, bad ? INT32_MIN : v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Start of a run, by one workgroup: next generation, error flag, queue head and
+// finished counts cleared. A run takes `step` tags from its generation ctl[0]
+// on; ctl[3] is the highest tag of the runs so far. Before the tags leave 31
+// bits (after millions of runs) the pool of tagged faces is cleared, so that no
+// old tag can look current, and they start over.
+__device__ __forceinline__ void next_run(int* ctl, int* counter, int* pool, uint64_t pool_ints, int step) {
+  const int last = ctl[3];
+  const bool wrap = last >= kTagAlways - 2 * step;
+  __syncthreads();
+  if (wrap)
+    for (uint64_t q = threadIdx.x; q < pool_ints; q += blockDim.x) pool[q] = 0;
+  if (threadIdx.x == 0) {
+    const int gen = (wrap ? 0 : last) + 1;
+    ctl[0] = gen;
+    ctl[1] = 0;
+    ctl[3] = gen + step - 1;
+    counter[0] = 0;
+    counter[kFinished] = 0;
+    counter[2 * kFinished] = 0;
+  }
+}
+
 constexpr int kCohNone = 0;
 constexpr int kCohDevice = 16;              // SC1
-constexpr int kTagAlways = 0x7FFFFFFF;
 
 // A zero the compiler cannot see through. Re-reads of stale face entries add
 // it to their scalar offset, so each retry is a distinct load that is neither

@@ -61,6 +61,10 @@ struct TripletDesc {
   // len[s] - 1 of the packed ones, read from their ends if rev is set.
   uint32_t start[3];
   uint32_t rev;
+  // First descriptor of a pair: its face tags are the run's generation + tag0 +
+  // 1 + panel row or column; its faces are in buffer set `set` (0 or 1), which
+  // it may use once `after` jobs of that set are finished.
+  uint32_t tag0, set, after;
 };
 
 // A queue entry: one triplet swept whole by one wave, or one panel of a
@@ -80,6 +84,11 @@ struct Boundary {
   uint32_t rows;
 };
 
+// Counters of a run on cache lines of their own: the atomics and loads of all
+// workgroups on one line took turns (a batch of 8192: 31.5 ms against 26.6).
+constexpr int kFinished = 32;
+constexpr size_t kCounterBytes = 3 * kFinished * 4;
+
 struct SweepArgs {
   const uint32_t* words;
   const TripletDesc* desc;
@@ -87,8 +96,9 @@ struct SweepArgs {
   uint32_t njobs;
   uint32_t lds_n0;      // longest sweep length the dynamic LDS was sized for
   int32_t* scores;
-  int* counter;         // job queue head (zeroed by k_prepare)
-  int* ctl;             // [0] run generation, [1] error flag
+  int* counter;         // [0] job queue head, [kFinished], [2 kFinished] finished jobs per buffer
+                        // set (zeroed by k_prepare)
+  int* ctl;             // [0] run generation, [1] error flag, [3] highest tag so far
   int* face;            // per-wave workspace for whole-triplet jobs
   uint64_t face_stride; // ints per wave
   int* pface;           // panel-face pool of split triplets
@@ -133,7 +143,10 @@ struct KernelShape {
 hipError_t launch_init_boundary(const KernelShape& ks, const Boundary& b, hipStream_t s);
 // Next run generation, error flag and queue head cleared, and nred
 // per-triplet reduction pairs of red reset (red may be null when nred = 0).
-hipError_t launch_prepare(int* ctl, int* counter, int* red, uint32_t nred, hipStream_t s);
+// step: the tags the run uses; before they leave 31 bits the face pool,
+// pool_ints from pool, is cleared and they start over.
+hipError_t launch_prepare(int* ctl, int* counter, int* red, uint32_t nred, int* pool, uint64_t pool_ints, int step,
+                          hipStream_t s);
 // modes: bit 0 = whole-triplet jobs present, bit 1 = panel jobs present.
 // The kernel variant follows a.sc.kind.
 hipError_t launch_sweep(const KernelShape& ks, int modes, const SweepArgs& a, int grid,
@@ -163,15 +176,23 @@ hipError_t launch_fill_packed_sentinel(uint32_t* p, uint64_t n, hipStream_t s);
 
 // Packed panel jobs (packed_panel.hip): pairs of triplets, descriptors 2p and
 // 2p + 1, swept panel by panel by many workgroups; 4 x 4 lane tiles. off: the
-// stored value of a panel's base. A plane run (a.plane set) also writes both
+// stored value of a panel's base; kc: the offset of semi-global candidates. A
+// plane run (a.plane set) also writes both
 // triplets' last slices (global and local kinds).
 constexpr int kPkPanel = 32;  // panel rows and columns
-// Steps (rows) of a pair's panel faces, and ints of one panel's faces: per
-// row kPkPanel bottom, kPkPanel right and one corner entry of (value, tag).
+// Rows of a pair's panel faces, and ints of all its faces: two buffers per
+// panel column of kPkPanel bottom entries a row, two per panel row of kPkPanel
+// right entries and a corner a row, (value, tag) each.
 __host__ __device__ inline uint64_t pk_face_rows(uint32_t n0) { return (face_rows(n0) + 7u) & ~7u; }
-__host__ __device__ inline uint64_t pk_panel_ints(uint32_t n0) { return pk_face_rows(n0) * (4 * kPkPanel + 2); }
-hipError_t launch_panel_pk(int kind, const SweepArgs& a, uint32_t off, uint32_t kc, int grid, hipStream_t s);
-hipError_t panel_pk_occupancy(int kind, bool plane, uint32_t lds_n0, int* blocks_per_cu);
+inline uint64_t pk_pair_ints(uint32_t n0, uint64_t PJ, uint64_t PK) {
+  return 2 * pk_face_rows(n0) * (PK * 2 * kPkPanel + PJ * (2 * kPkPanel + 2));
+}
+// self: single-wave workgroups that move their own faces, instead of a
+// computing and a memory wave. count: finished
+// jobs are counted for pairs that wait for them.
+hipError_t launch_panel_pk(int kind, bool self, const SweepArgs& a, uint32_t off, uint32_t kc, bool count, int grid,
+                           hipStream_t s);
+hipError_t panel_pk_occupancy(int kind, bool plane, bool self, uint32_t lds_n0, int* blocks_per_cu);
 
 // Traceback (traceback.hip). A split box: the forward and reversed planes
 // (ints from the plane buffer base), rows x cols entries each, reduced in
@@ -181,6 +202,7 @@ struct SplitDesc {
   uint64_t fwd, bwd;
   uint32_t rows, cols;
   uint32_t chunk0, nchunk;
+  uint32_t out;  // half-split scoring: index of the triplet's score
 };
 // A leaf box: sequence s of the box is residues lo[s] .. lo[s] + len[s] - 1 of
 // the packed sequence at word offset off[s]; (len0+1)(len1+1)(len2+1) <=
@@ -215,14 +237,15 @@ struct GatherDesc {
   uint32_t start, len, reverse;
 };
 hipError_t launch_gather(const uint32_t* in, const GatherDesc* d, uint32_t n, uint32_t words_out,
-                         uint32_t* out, int* ctl, int* counter, hipStream_t s);
-// out[0] = the best F + R over box 0 of planes (its nchunks chunks of
-// kSplitChunk cells, numbered from 0), or INT32_MIN if err[0] is set (a wait
-// of the run gave up). With own non-null (local scoring), the best also
-// covers own[0] and own[1], the halves' own bests. partial: nchunks ints of
-// scratch; counter: one int that is 0 before the call and is left 0.
-hipError_t launch_meet(const SplitDesc* box, uint32_t nchunks, const int* planes, int* partial,
-                       const int* err, const int* own, int* counter, int32_t* out, hipStream_t s);
+                         uint32_t* out, int* ctl, int* counter, int* pool, uint64_t pool_ints, hipStream_t s);
+// out[box.out] = the best F + R over every box's planes, or INT32_MIN if err[0]
+// is set (a wait of the run gave up). chunk_box[c] = the box of chunk c (null:
+// one box). With own non-null (local scoring), the best of box b also covers
+// own[4b] and own[4b + own_step], the halves' own bests. partial: nchunks ints
+// of scratch; counters: one int per box that is 0 before the call and is left 0.
+hipError_t launch_meet(const SplitDesc* boxes, const uint32_t* chunk_box, uint32_t nchunks, const int* planes,
+                       int* partial, const int* err, const int* own, int own_step, int* counters, int32_t* out,
+                       hipStream_t s);
 // out[3b] = best F + R of box b, out[3b+1], out[3b+2] = its (p, q).
 // chunk_box[c] = the box of chunk c; partial: 2 ints per chunk.
 hipError_t launch_split(const int* planes, const SplitDesc* boxes, uint32_t n, const uint32_t* chunk_box,

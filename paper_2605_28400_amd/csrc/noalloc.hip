@@ -10,7 +10,7 @@
 //
 // Layout of the array: [control 4 KiB | panel-face pool | plain data].
 //  * control: the run generation and error flag (ctl[0], ctl[1]), the
-//    half-split meeting counter (ctl[2], 0 between calls) and the job queue
+//    half-split meeting counter (ctl[2], 0 between calls), highest tag (ctl[3]) and the job queue
 //    head; they persist from call to call and the generation only grows, so
 //    a face tag written by an earlier call never looks current;
 //  * pool: only ever (value, tag) pairs of split triplets' faces, at even

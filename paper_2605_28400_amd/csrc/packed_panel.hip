@@ -23,51 +23,218 @@
 // that one triplet of the int32 kernel moves; a poll takes five loads (16
 // lanes cover a row with two entries each) and three ballots.
 //
-// What bounds it: long triplets (4096 x 4000 x 4150 by halves, 31.3 -> 15.5 ms
-// against the int32 halves) the issue of the lone computing wave on each SIMD;
-// shorter ones (1024 x 1000 x 1048, 975 -> 727 us) the chain of panel hops.
+// What bounds it. Batches and long triplets run on single-wave workgroups,
+// two to a SIMD, bound by VALU issue (about 140 instructions a step against the
+// recurrence's 112) and by the waits it does not cover: 8192 triplets of
+// lengths 100-400 26.7 ms (whole pairs, one wavefront each: 31.3 ms, their
+// unequal sizes leave the device half empty at the end; int32: 46.5 ms), 1999
+// of them under local scoring 8.7 ms (34.8 ms), 4096 x 4000 x 4150 by halves
+// 10.9 ms (int32 halves: 31.3 ms). Short lone triplets are a chain of panel
+// hops: 1024 x 1000 x 1048 by halves on wave pairs 615 us (int32: 976 us), 0.39
+// us a step and 21 steps a hop.
+#include <type_traits>
+
 #include "packed.h"
 
 namespace trioseq {
 namespace {
 
-constexpr int kRingC = 2 * kRing;  // corner rows: staged one step ahead of the other rings
 constexpr int kSideLanes = kPkPanel / 2;   // lanes covering one face row, two entries each
 constexpr int kSideRows = 64 / kSideLanes; // rows per load
 constexpr int kSideLoads = kChunk / kSideRows;
 
+// R: halo and out rows kept (kRing with a memory wave, kChunk without).
+template <int R>
 struct PkPanelLds {
+  static constexpr int kRows = R, kRowsC = 2 * R;         // corner rows are staged one step ahead
   __attribute__((aligned(16))) int sR[64][4];             // right column of each lane
   __attribute__((aligned(16))) int sB[64][4];             // bottom row of each lane
+  __attribute__((aligned(16))) int T[R][kPkPanel];        // halo rings: row t mod R serves step t
+  __attribute__((aligned(16))) int Lf[R][kPkPanel];
+  // Corners of the top lanes; entry 8 is the corner that the panel to the
+  // right takes for the step before the row's.
+  int C[kRowsC][kGK + 1];
+  __attribute__((aligned(16))) int ob[R][kPkPanel];       // out rows
+  __attribute__((aligned(16))) int orr[R][kPkPanel];
   int sX[64];                                             // bottom of each lane's left halo
-  __attribute__((aligned(16))) int T[kRing][kPkPanel];    // halo rings: ring row t mod kRing serves step t
-  __attribute__((aligned(16))) int Lf[kRing][kPkPanel];
-  __attribute__((aligned(16))) int C[kRingC][kGK];
-  __attribute__((aligned(16))) int ob[kRing][kPkPanel];   // out rows of the compute wave
-  __attribute__((aligned(16))) int orr[kRing][kPkPanel];
-  int oc[kRing];
   int cap[2][16];                                         // score tiles of both triplets
   int in_ready, out_done, out_flushed, job;
   uint32_t base;
 };
 
-// One panel's faces. Null: tensor edge (inputs) or not needed (outputs).
+// A panel's faces. A pair has two bottom-face buffers per panel column and two
+// right-face buffers (corner face behind them) per panel row, written in turn:
+// a panel reads the one its neighbour wrote and overwrites the one written two
+// panels before. 260 buffers instead of two for each of 4225 panels of a
+// 2048-residue triplet: the faces stay in the caches (1024 x 1000 x 1048: 711
+// us against 734 with faces of its own for every panel; with a single buffer,
+// read and written in the same lines, 764). Nothing that is needed is
+// overwritten: a panel's row t depends, through its neighbour's row t + 7, on
+// the neighbour having read row t + 14 of the buffer in question. The tag of
+// an entry is gen + 1 + the panel row (bottom faces) or column (right faces)
+// that wrote it; a consumer takes exactly its neighbour's.
 struct PkPanelIO {
-  const int* top;     // bottom face of the panel above
-  const int* left;    // right face of the panel to the left, its corner face behind it
-  int* out;           // this panel's faces: bottom, right, corner
-  bool bot, right;    // whether they have a consumer
-  int gen;
+  int *col_in, *col_out;  // bottom faces of this panel column: read if has_top, written if bot
+  int *row_in, *row_out;  // right faces of this panel row: read if has_left, written if right
+  bool has_top, has_left, bot, right;
+  int top_tag, left_tag;  // the neighbours' tags; this panel's are one more
   int* err;
   uint64_t wait_ticks;
 };
 
-// Half-wise a - b and a + b modulo 2^16 are psub and paddw.
+// One wave's view of a panel's faces. For steps u .. u + 7 a load fetches rows
+// u + 7 .. u + 14 of the top, left and corner faces, five instructions: lane l
+// holds entries 2(l mod 16), +1 of row l / 16 (+ 4 in the second load), so the
+// first row with a stale entry is the lowest set bit of a ballot.
+template <class Lds>
+struct PkFaces {
+  static constexpr uint32_t RB = kPkPanel * 8u;  // bytes of a face row
+  Lds& S;
+  const PkPanelIO& io;
+  int n0, lane, rr0, pr, grp;
+  uint32_t side, vside, off2, delta;  // delta: off - base, per half modulo 2^16
+  Rsrc r_top, r_left, r_bot, r_right;
+  bool have_base;
+  v4i tv[kSideLoads], lv[kSideLoads];
+  v2i cv;
+
+  // A face that does not exist (tensor edge) or has no consumer is an empty
+  // resource: its loads give 0 and its stores are dropped. It is never waited
+  // for (its tag is 0 as well), and every slice counts as before the tensor.
+  int top_tag, left_tag, top_from, left_from;
+
+  __device__ __forceinline__ PkFaces(Lds& S_, const PkPanelIO& io_, int n0_, uint32_t off2_)
+      : S(S_), io(io_), n0(n0_), off2(off2_), delta(off2_) {
+    lane = threadIdx.x & 63;
+    rr0 = lane / kSideLanes;
+    pr = lane % kSideLanes;
+    grp = pr >> 1;
+    vside = (uint32_t)(rr0 * RB + pr * 16);
+    const uint64_t rows = pk_face_rows((uint32_t)n0);
+    side = (uint32_t)(rows * RB);
+    const uint32_t both = side + (uint32_t)rows * 8u;  // right faces, then corners
+    r_top = make_rsrc(io.col_in, io.has_top ? side : 0);
+    r_left = make_rsrc(io.row_in, io.has_left ? both : 0);
+    r_bot = make_rsrc(io.col_out, io.bot ? side : 0);
+    r_right = make_rsrc(io.row_out, io.right ? both : 0);
+    top_tag = io.has_top ? io.top_tag : 0;
+    left_tag = io.has_left ? io.left_tag : 0;
+    top_from = io.has_top ? 0 : INT32_MAX;
+    left_from = io.has_left ? 0 : INT32_MAX;
+    have_base = !io.has_top && !io.has_left;
+    // The corners of step 0 lie before slice 0 (lane 0's comes with the corner
+    // face, or lies outside).
+    if (lane < kGK) S.C[0][lane] = (int)(kSentP * 0x10001u);
+  }
+
+  __device__ __forceinline__ void load(int u) {
+    const uint32_t z = opaque_zero();
+    const uint32_t vo = vside + (uint32_t)(u + kGJ - 1) * RB;
+#pragma unroll
+    for (int q = 0; q < kSideLoads; ++q) {
+      tv[q] = __builtin_amdgcn_raw_buffer_load_b128(r_top, vo + q * kSideRows * RB, z, kCohDevice);
+      lv[q] = __builtin_amdgcn_raw_buffer_load_b128(r_left, vo + q * kSideRows * RB, z, kCohDevice);
+    }
+    cv = __builtin_amdgcn_raw_buffer_load_b64(
+        r_left, lane < kChunk ? side + (uint32_t)(u + kGJ - 1 + lane) * 8u : kOob, z, kCohDevice);
+  }
+
+  // How many of the steps u .. u + 7 have every entry they need (entries of
+  // slices past n0 are never needed, those before 0 are not read).
+  __device__ __forceinline__ int ready(int u) const {
+    int k = kChunk;
+#pragma unroll
+    for (int q = kSideLoads - 1; q >= 0; --q) {
+      const int slice = u + rr0 + q * kSideRows - grp;
+      const int stale =
+          (tv[q].y ^ top_tag) | (tv[q].w ^ top_tag) | (lv[q].y ^ left_tag) | (lv[q].w ^ left_tag);
+      const uint64_t m = __builtin_amdgcn_ballot_w64((uint32_t)slice <= (uint32_t)n0 && stale != 0);
+      if (m) k = q * kSideRows + __builtin_ctzll(m) / kSideLanes;
+    }
+    // (In the first panel row nobody writes or needs corners.)
+    const uint64_t m =
+        __builtin_amdgcn_ballot_w64(io.has_top && lane < kChunk && u + lane <= n0 && cv.y != left_tag);
+    if (m) k = min(k, __builtin_ctzll(m));
+    return k;
+  }
+
+  // Writes the halo rows of steps u .. u + k - 1 to the rings, relative to the
+  // panel's base (taken from the first entry of slice 0). ALL: k = kChunk.
+  template <bool ALL>
+  __device__ __forceinline__ void put(int u, int k) {
+    const uint32_t sent2 = kSentP * 0x10001u;
+    if (!have_base) {
+      // Lane 0 holds entry 0 of row 7, slice 0.
+      const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(io.has_top ? tv[0].x : lv[0].x);
+      delta = psub(off2, b);
+      if (lane == 0) S.base = b;
+      have_base = true;
+    }
+#pragma unroll
+    for (int q = 0; q < kSideLoads; ++q) {
+      const int rr = rr0 + q * kSideRows, st = u + rr;
+      if (ALL || rr < k) {
+        // Slices before 0 lie outside the tensor.
+        const bool no_top = st - grp < top_from, no_left = st - grp < left_from;
+        const uint32_t t0 = no_top ? sent2 : paddw((uint32_t)tv[q].x, delta);
+        const uint32_t t1 = no_top ? sent2 : paddw((uint32_t)tv[q].z, delta);
+        const uint32_t l0 = no_left ? sent2 : paddw((uint32_t)lv[q].x, delta);
+        const uint32_t l1 = no_left ? sent2 : paddw((uint32_t)lv[q].z, delta);
+        *reinterpret_cast<v2i*>(&S.T[st & (Lds::kRows - 1)][2 * pr]) = (v2i){(int)t0, (int)t1};
+        *reinterpret_cast<v2i*>(&S.Lf[st & (Lds::kRows - 1)][2 * pr]) = (v2i){(int)l0, (int)l1};
+        // Entry 4x + 3 is the corner of lane x + 1 at the next step (x = 7:
+        // of the panel to the right, at this step).
+        if (pr & 1) S.C[(st + 1) & (Lds::kRowsC - 1)][grp + 1] = (int)t1;
+      }
+    }
+    if (lane < (ALL ? kChunk : k))
+      S.C[(u + lane) & (Lds::kRowsC - 1)][0] =
+          (int)(io.has_top && io.has_left ? paddw((uint32_t)cv.x, delta) : sent2);
+  }
+
+  // Stores out rows t0 .. t0 + nf - 1, back to M' modulo 2^16.
+  template <bool ALL>
+  __device__ __forceinline__ void flush(int t0, int nf) const {
+    const int bot_tag = io.top_tag + 1, right_tag = io.left_tag + 1;
+    v2i bv[kSideLoads], rv[kSideLoads];
+#pragma unroll
+    for (int q = 0; q < kSideLoads; ++q) {
+      const int ro = (t0 + rr0 + q * kSideRows) & (Lds::kRows - 1);
+      bv[q] = *reinterpret_cast<const v2i*>(&S.ob[ro][2 * pr]);
+      rv[q] = *reinterpret_cast<const v2i*>(&S.orr[ro][2 * pr]);
+    }
+    const int c = S.C[(t0 + (lane & (kChunk - 1)) + 1) & (Lds::kRowsC - 1)][kGK];
+    const uint32_t vo = vside + (uint32_t)t0 * RB;
+#pragma unroll
+    for (int q = 0; q < kSideLoads; ++q) {
+      const uint32_t o = ALL || rr0 + q * kSideRows < nf ? vo + q * kSideRows * RB : kOob;
+      __builtin_amdgcn_raw_buffer_store_b128(
+          (v4i){(int)psub((uint32_t)bv[q].x, delta), bot_tag, (int)psub((uint32_t)bv[q].y, delta), bot_tag}, r_bot,
+          o, 0, kCohDevice);
+      __builtin_amdgcn_raw_buffer_store_b128(
+          (v4i){(int)psub((uint32_t)rv[q].x, delta), right_tag, (int)psub((uint32_t)rv[q].y, delta), right_tag},
+          r_right, o, 0, kCohDevice);
+    }
+    __builtin_amdgcn_raw_buffer_store_b64((v2i){(int)psub((uint32_t)c, delta), right_tag}, r_right,
+                                          lane < (ALL ? kChunk : nf) ? side + (uint32_t)(t0 + lane) * 8u : kOob, 0,
+                                          kCohDevice);
+  }
+};
+
+__device__ __forceinline__ void lds_put4(int* p, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  *reinterpret_cast<v4i*>(__builtin_assume_aligned(p, 16)) = (v4i){(int)a, (int)b, (int)c, (int)d};
+}
 
 // The compute wave. Folds local and semi-global bests into `best`, as the
-// whole-triplet kernel does (local: M; semi-global: M + kc).
-template <int KIND, bool PLANE>
-__device__ void pk_panel_compute(PkPanelLds& S, const uint32_t* sel, const DevScoring& sc,
+// whole-triplet kernel does (local: M; semi-global: M + kc). SELF: the wave
+// moves its faces itself, a chunk of steps at a time (loads of the next chunk
+// issued at step kSelfStageAt of this one).
+#ifndef SSA
+#define SSA 5
+#endif
+constexpr int kSelfStageAt = SSA;
+template <int KIND, bool PLANE, bool SELF, class Lds>
+__device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& sc,
                                  const uint32_t* __restrict__ words, const TripletDesc& ta, const TripletDesc& tb,
                                  int n0, int pj, int pk, const PkPanelIO& io, uint16_t* capt, uint32_t off2,
                                  uint32_t& best, uint32_t kc) {
@@ -127,28 +294,55 @@ __device__ void pk_panel_compute(PkPanelLds& S, const uint32_t* sel, const DevSc
   const int* t_base = y0 ? &S.T[0][x * RK] : &S.sB[y0 ? 0 : lane - 8][0];
   const int* c_base = y0 ? &S.C[0][x] : &S.sX[y0 ? 0 : lane - 8];
   const int* l_base = x0 ? &S.Lf[0][y * RJ] : &S.sR[x0 ? 0 : lane - 1][0];
-  const int t_str = y0 ? W : 0, c_str = y0 ? kGK : 0, l_str = x0 ? H : 0;
+  const int t_str = y0 ? W : 0, c_str = y0 ? kGK + 1 : 0, l_str = x0 ? H : 0;
+  // Where the tile's bottom row and right column go: the lane's slots, or the
+  // out rows for the panel's last lanes (whose slots nobody reads).
+  const bool y7 = y == kGJ - 1, x7 = x == kGK - 1;
+  int* b_base = y7 ? &S.ob[0][x * RK] : &S.sB[lane][0];
+  int* r_base = x7 ? &S.orr[0][y * RJ] : &S.sR[lane][0];
+  const int b_str = y7 ? W : 0, r_str = x7 ? H : 0;
   const uint32_t* sl = sel + kShiftPre - y - x;
 
   int fin = 0, ffl = 0;
   bool gave_up = false;
+  PkFaces<Lds> f(S, io, n0, off2);  // (unused, and dropped, without SELF)
+  if (SELF) f.load(0);
   uint32_t zero2 = off2;  // stored value of M' = 0 (set at step 0, once the base is known)
-  for (int c = 0; c < nchunks; ++c) {
+  auto run_chunk = [&](int c, auto capture) __attribute__((always_inline)) {
+    constexpr bool CAP = decltype(capture)::value;
     const int cb0 = c * kChunk;
-    const bool cap_chunk = (n0a >= cb0 - kSkew && n0a <= cb0 + kChunk - 1) ||
-                           (n0b >= cb0 - kSkew && n0b <= cb0 + kChunk - 1);
-    const int* tb_ = t_base + (c & 1) * kChunk * t_str;
-    const int* cb_ = c_base + (c & 3) * kChunk * c_str;
-    const int* lb_ = l_base + (c & 1) * kChunk * l_str;
+    constexpr int kPh = Lds::kRows / kChunk - 1, kPhC = Lds::kRowsC / kChunk - 1;
+    const int* tb_ = t_base + (c & kPh) * kChunk * t_str;
+    const int* cb_ = c_base + (c & kPhC) * kChunk * c_str;
+    const int* lb_ = l_base + (c & kPh) * kChunk * l_str;
+    int* b_out = b_base + (c & kPh) * kChunk * b_str;
+    int* r_out = r_base + (c & kPh) * kChunk * r_str;
+    if (SELF) {
+      if (!gave_up && f.ready(cb0) < kChunk) {
+        const uint64_t t_start = wall_clock64();
+        do {
+          if (wall_clock64() - t_start > io.wait_ticks) {
+            raise_error(io.err);
+            gave_up = true;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(2);
+          f.load(cb0);
+        } while (f.ready(cb0) < kChunk);
+      }
+      f.template put<true>(cb0, kChunk);
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    }
     uint32_t selv[kChunk];
 #pragma unroll
     for (int s = 0; s < kChunk; ++s) selv[s] = sl[cb0 + s];
 #pragma unroll
     for (int s = 0; s < kChunk; ++s) {
       const int t = cb0 + s;
+      if (SELF && s == kSelfStageAt && c + 1 < nchunks) f.load(cb0 + kChunk);
       // Step t needs its halo rows staged and out row t mod kRing read back;
       // the counters read during the previous step usually already say so.
-      if (!gave_up && !(fin > t && ffl > t - kRing)) {
+      if (!SELF && !gave_up && !(fin > t && ffl > t - kRing)) {
         const uint64_t t_start = wall_clock64();
         for (;;) {
           fin = lds_get(&S.in_ready);
@@ -163,8 +357,11 @@ __device__ void pk_panel_compute(PkPanelLds& S, const uint32_t* sel, const DevSc
         }
       }
       __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      const int fin_next = lds_get(&S.in_ready);
-      const int ffl_next = lds_get(&S.out_flushed);
+      int fin_next = 0, ffl_next = 0;
+      if (!SELF) {
+        fin_next = lds_get(&S.in_ready);
+        ffl_next = lds_get(&S.out_flushed);
+      }
       if (PAD && s == 0 && c == 0) zero2 = psub(off2, S.base);
 
       const uint32_t sv = selv[s];
@@ -254,7 +451,14 @@ __device__ void pk_panel_compute(PkPanelLds& S, const uint32_t* sel, const DevSc
             if (!(cnt & 1)) m = pmax2(m, hold);
             sb = umax2(sb, psub(m, (uint32_t)d * g2));
           }
+#ifdef RF
+          asm volatile("" : "+v"(fi));
+          F0 = paddw(zero2, ((uint32_t)fi & 0xFFFFu) * 0x10001u);
+#endif
           best = umax2(best, psub(sb, F0) & vm);
+          // Formed here: sunk to where `best` is used, the end of the chunk,
+          // it would keep the tiles of all its steps in registers.
+          asm volatile("" : "+v"(best));
         } else {
           const uint32_t sm = (i == n0a ? 0xFFFFu : 0u) | (i == n0b ? 0xFFFF0000u : 0u);
           if (((rcany | sm) & vm) != 0u) {
@@ -267,43 +471,31 @@ __device__ void pk_panel_compute(PkPanelLds& S, const uint32_t* sel, const DevSc
               for (int cc = 0; cc < RK; ++cc)
                 sb = umax2(sb, paddw(N[r][cc], psub(off0, (uint32_t)(r + cc) * g2)) & (RM[r] | CM[cc] | sm));
             best = umax2(best, sb & vm);
+            asm volatile("" : "+v"(best));
           }
         }
         fi += g;
       }
 
-#pragma unroll
-      for (int r = 0; r < RJ; ++r) S.sR[lane][r] = (int)N[r][RK - 1];
-#pragma unroll
-      for (int cc = 0; cc < RK; ++cc) S.sB[lane][cc] = (int)N[RJ - 1][cc];
+lds_put4(b_out + s * b_str, N[RJ - 1][0], N[RJ - 1][1], N[RJ - 1][2], N[RJ - 1][3]);
+      lds_put4(r_out + s * r_str, N[0][RK - 1], N[1][RK - 1], N[2][RK - 1], N[3][RK - 1]);
       S.sX[lane] = (int)Lh[RJ - 1];
-
-      // Out rows (row t mod kRing).
-      const int ro = (c & 1) * kChunk + s;
-      if (y == kGJ - 1) {
-#pragma unroll
-        for (int cc = 0; cc < RK; ++cc) S.ob[ro][x * RK + cc] = (int)N[RJ - 1][cc];
-      }
-      if (x == kGK - 1) {
-#pragma unroll
-        for (int r = 0; r < RJ; ++r) S.orr[ro][y * RJ + r] = (int)N[r][RK - 1];
-        if (y == 0) S.oc[ro] = (int)T[RK - 1];
-      }
       __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      if (lane == 0) lds_put(&S.out_done, t + 1);
+      if (!SELF && lane == 0) lds_put(&S.out_done, t + 1);
       fin = fin_next;
       ffl = ffl_next;
 
-      if (cap_chunk) {
+      if (CAP) {
         if (PLANE) {
+          // (Halves interleaved: 16-bit stores straight from the registers.)
           if (i == n0a) {
 #pragma unroll
-            for (int q = 0; q < RJ * RK; ++q) capt[lane * (RJ * RK) + q] = (uint16_t)(N[q / RK][q % RK] & 0xFFFFu);
+            for (int q = 0; q < RJ * RK; ++q) capt[(lane * (RJ * RK) + q) * 2] = (uint16_t)N[q / RK][q % RK];
           }
           if (i == n0b) {
 #pragma unroll
             for (int q = 0; q < RJ * RK; ++q)
-              capt[64 * RJ * RK + lane * (RJ * RK) + q] = (uint16_t)(N[q / RK][q % RK] >> 16);
+              capt[(lane * (RJ * RK) + q) * 2 + 1] = (uint16_t)(N[q / RK][q % RK] >> 16);
           }
         } else if (KIND == kGlobal) {
           if (own_a && i == n0a) {
@@ -324,8 +516,22 @@ __device__ void pk_panel_compute(PkPanelLds& S, const uint32_t* sel, const DevSc
       }
 #pragma unroll
       for (int cc = 0; cc < RK; ++cc) Tp[cc] = T[cc];
+#ifdef SB
+      if (KIND == SB) __builtin_amdgcn_sched_barrier(0);
+#endif
     }
-  }
+    if (SELF) {
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      f.template flush<true>(cb0, kChunk);
+    }
+  };
+  // A triplet's last slice n0 is captured in the chunks from n0 / kChunk on: a
+  // copy of the body of their own keeps the tests out of all others.
+  constexpr bool kCaptures = PLANE || KIND == kGlobal;
+  const int ccap = kCaptures ? min(n0a, n0b) / kChunk : nchunks;
+  for (int c = 0; c < ccap; ++c) run_chunk(c, std::false_type{});
+  if constexpr (kCaptures)
+    for (int c = ccap; c < nchunks; ++c) run_chunk(c, std::true_type{});
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
 }
 
@@ -340,45 +546,17 @@ __device__ __forceinline__ void pk_write_plane(const uint16_t* capt, int* plane,
     const int j = j0 + q / 4, k = k0 + q % 4;
     if (j <= n1 && k <= n2)
       plane[(uint64_t)j * (uint64_t)(n2 + 1) + (uint64_t)k] =
-          (int)((capt[lane * 16 + q] - zero) & 0xFFFFu) + gap2 * (n0 + j + k);
+          (int)((capt[(lane * 16 + q) * 2] - zero) & 0xFFFFu) + gap2 * (n0 + j + k);
   }
 }
 
-// The memory wave: keeps the compute wave's halo rings filled from the
-// neighbours' tagged faces and writes its out rows. For steps u .. u + 7 one
-// poll loads rows u + 7 .. u + 14 of the top, right and corner faces; lane l of
-// a load holds entries 2(l mod 16), +1 of row l / 16 (+ 4 in the second load),
-// so the first row with a stale entry is the lowest set bit of a ballot. Every
-// wait is bounded (past the limit the error flag is raised and the rows are
-// staged as they are).
-__device__ void pk_panel_memory(PkPanelLds& S, int n0, const PkPanelIO& io, uint32_t off2) {
-  constexpr uint32_t RB = kPkPanel * 8u;  // bytes of a face row
+// The memory wave: keeps the compute wave's halo rings filled and stores its
+// out rows. Every wait is bounded (past the limit the error flag is raised and
+// the rows are staged as they are).
+__device__ void pk_panel_memory(PkPanelLds<kRing>& S, int n0, const PkPanelIO& io, uint32_t off2) {
   const int lane = threadIdx.x & 63;
   const int stepsp = (n0 + 1 + kSkew + kChunk - 1) / kChunk * kChunk;
-  const uint64_t rows = pk_face_rows((uint32_t)n0);
-  const bool has_top = io.top != nullptr, has_left = io.left != nullptr;
-  const uint32_t side = (uint32_t)(rows * RB), all = side * 2 + (uint32_t)rows * 8u;
-  const int* any = has_top ? io.top : io.left;
-  const Rsrc r_top = make_rsrc(any, has_top ? side : 0);
-  // Left neighbour: right face, then the corner face.
-  const Rsrc r_left = make_rsrc(has_left ? io.left : any, has_left ? side + (uint32_t)rows * 8u : 0);
-  const Rsrc r_out = make_rsrc(io.out, all);
-  const int gen = io.gen;
-  const int rr0 = lane / kSideLanes, pr = lane % kSideLanes, grp = pr >> 1;
-  const uint32_t sent2 = kSentP * 0x10001u;
-  const uint32_t vside = (uint32_t)(rr0 * RB + pr * 16);
-  const bool has_corner = has_top && has_left;
-
-  // Rings that nothing fills hold the outside value; so does the corner row of
-  // step 0 (its slices lie before 0, lane 0's comes with the corner face).
-  for (int q = lane; q < kRing * kPkPanel; q += 64) {
-    if (!has_top) (&S.T[0][0])[q] = (int)sent2;
-    if (!has_left) (&S.Lf[0][0])[q] = (int)sent2;
-  }
-  for (int q = lane; q < kRingC * kGK; q += 64) (&S.C[0][0])[q] = (int)sent2;
-  bool have_base = !has_top && !has_left;
-  uint32_t delta = off2;  // off - base, per half modulo 2^16
-
+  PkFaces<PkPanelLds<kRing>> f(S, io, n0, off2);
   int staged = 0, flushed = 0;
   uint64_t stall_since = 0;
   bool gave_up = false;
@@ -386,37 +564,10 @@ __device__ void pk_panel_memory(PkPanelLds& S, int n0, const PkPanelIO& io, uint
     const int done = lds_get(&S.out_done);
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     bool progress = false;
-    const int u = staged;
-    // (The corner rows run one step ahead.)
-    const int nb = min(min(kChunk, stepsp - u), done + kRing - u);
+    const int nb = min(min(kChunk, stepsp - staged), done + kRing - staged);
     if (nb > 0) {
-      v4i tv[kSideLoads], lv[kSideLoads];
-      v2i cv = {0, 0};
-      const uint32_t z = opaque_zero();
-      const uint32_t vo = vside + (uint32_t)(u + kGJ - 1) * RB;
-      uint64_t m[kSideLoads], mc = 0;
-#pragma unroll
-      for (int q = 0; q < kSideLoads; ++q) {
-        if (has_top) tv[q] = __builtin_amdgcn_raw_buffer_load_b128(r_top, vo + q * kSideRows * RB, z, kCohDevice);
-        if (has_left) lv[q] = __builtin_amdgcn_raw_buffer_load_b128(r_left, vo + q * kSideRows * RB, z, kCohDevice);
-      }
-      if (has_corner)
-        cv = __builtin_amdgcn_raw_buffer_load_b64(
-            r_left, lane < kChunk ? side + (uint32_t)(u + kGJ - 1 + lane) * 8u : kOob, z, kCohDevice);
-#pragma unroll
-      for (int q = 0; q < kSideLoads; ++q) {
-        const int slice = u + rr0 + q * kSideRows - grp;
-        int tag = kTagAlways;
-        if (has_top) tag = min(tv[q].y, tv[q].w);
-        if (has_left) tag = min(tag, min(lv[q].y, lv[q].w));
-        m[q] = __builtin_amdgcn_ballot_w64((uint32_t)slice <= (uint32_t)n0 && tag < gen);
-      }
-      if (has_corner) mc = __builtin_amdgcn_ballot_w64(lane < kChunk && u + lane <= n0 && cv.y < gen);
-      int k = nb;
-#pragma unroll
-      for (int q = kSideLoads - 1; q >= 0; --q)
-        if (m[q]) k = min(k, q * kSideRows + __builtin_ctzll(m[q]) / kSideLanes);
-      if (mc) k = min(k, __builtin_ctzll(mc));
+      f.load(staged);
+      int k = min(f.ready(staged), nb);
       if (gave_up) k = nb;
       if (k <= 0 && stall_since && wall_clock64() - stall_since > io.wait_ticks) {
         raise_error(io.err);
@@ -424,71 +575,20 @@ __device__ void pk_panel_memory(PkPanelLds& S, int n0, const PkPanelIO& io, uint
         k = nb;
       }
       if (k > 0) {
-        if (!have_base) {
-          // Lane 0 holds entry 0 of row 7, slice 0.
-          const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane(has_top ? tv[0].x : lv[0].x);
-          delta = psub(off2, b);
-          if (lane == 0) S.base = b;
-          have_base = true;
-        }
-#pragma unroll
-        for (int q = 0; q < kSideLoads; ++q) {
-          const int rr = rr0 + q * kSideRows, st = u + rr;
-          const bool before = st - grp < 0;  // slices before 0 lie outside the tensor
-          if (rr < k) {
-            if (has_top) {
-              const uint32_t v0 = before ? sent2 : paddw((uint32_t)tv[q].x, delta);
-              const uint32_t v1 = before ? sent2 : paddw((uint32_t)tv[q].z, delta);
-              *reinterpret_cast<v2i*>(&S.T[st & (kRing - 1)][2 * pr]) = (v2i){(int)v0, (int)v1};
-              // Entry 4x + 3 is the corner of lane x + 1 at the next step.
-              if ((pr & 1) && grp + 1 < kGK) S.C[(st + 1) & (kRingC - 1)][grp + 1] = (int)v1;
-            }
-            if (has_left) {
-              const uint32_t v0 = before ? sent2 : paddw((uint32_t)lv[q].x, delta);
-              const uint32_t v1 = before ? sent2 : paddw((uint32_t)lv[q].z, delta);
-              *reinterpret_cast<v2i*>(&S.Lf[st & (kRing - 1)][2 * pr]) = (v2i){(int)v0, (int)v1};
-            }
-          }
-        }
-        if (has_corner && lane < k) S.C[(u + lane) & (kRingC - 1)][0] = (int)paddw((uint32_t)cv.x, delta);
+        f.template put<false>(staged, k);
+        staged += k;
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if (lane == 0) lds_put(&S.in_ready, u + k);
-        staged = u + k;
+        if (lane == 0) lds_put(&S.in_ready, staged);
         progress = true;
       }
     }
-    // Flush finished out rows, back to M' modulo 2^16.
     const int nf = min(kChunk, lds_get(&S.out_done) - flushed);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
     if (nf > 0) {
-      v2i bv[kSideLoads], rv[kSideLoads];
-#pragma unroll
-      for (int q = 0; q < kSideLoads; ++q) {
-        const int ro = (flushed + rr0 + q * kSideRows) & (kRing - 1);
-        bv[q] = *reinterpret_cast<const v2i*>(&S.ob[ro][2 * pr]);
-        rv[q] = *reinterpret_cast<const v2i*>(&S.orr[ro][2 * pr]);
-      }
-      const int cv = S.oc[(flushed + lane) & (kRing - 1)];
-      const uint32_t vo = vside + (uint32_t)flushed * RB;
-#pragma unroll
-      for (int q = 0; q < kSideLoads; ++q) {
-        const bool live = rr0 + q * kSideRows < nf;
-        const uint32_t o = live ? vo + q * kSideRows * RB : kOob;
-        if (io.bot)
-          __builtin_amdgcn_raw_buffer_store_b128((v4i){(int)psub((uint32_t)bv[q].x, delta), gen,
-                                                       (int)psub((uint32_t)bv[q].y, delta), gen},
-                                                 r_out, o, 0, kCohDevice);
-        if (io.right)
-          __builtin_amdgcn_raw_buffer_store_b128((v4i){(int)psub((uint32_t)rv[q].x, delta), gen,
-                                                       (int)psub((uint32_t)rv[q].y, delta), gen},
-                                                 r_out, live ? o + side : kOob, 0, kCohDevice);
-      }
-      if (io.right)
-        __builtin_amdgcn_raw_buffer_store_b64((v2i){(int)psub((uint32_t)cv, delta), gen}, r_out,
-                                              lane < nf ? 2 * side + (uint32_t)(flushed + lane) * 8u : kOob, 0,
-                                              kCohDevice);
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      if (lane == 0) lds_put(&S.out_flushed, flushed + nf);
+      f.template flush<false>(flushed, nf);
       flushed += nf;
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      if (lane == 0) lds_put(&S.out_flushed, flushed);
       progress = true;
     }
     if (progress) {
@@ -502,18 +602,21 @@ __device__ void pk_panel_memory(PkPanelLds& S, int n0, const PkPanelIO& io, uint
 
 // Workgroups pop panel jobs (jd.trip = the pair's first descriptor) in the
 // host's dependency order, so every producer was popped earlier by a running
-// workgroup and every wait ends.
-template <int KIND, bool PLANE>
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
-k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc) {
+// workgroup and every wait ends. Pairs that reuse the face buffers of earlier
+// ones (see pair_panel_layout) also wait until those are over; all their jobs
+// were popped before.
+template <int KIND, bool PLANE, bool SELF>
+__global__ void __launch_bounds__(SELF ? 64 : 128) __attribute__((amdgpu_waves_per_eu(2)))
+k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc, uint32_t count) {
   constexpr int H = kPkPanel, W = kPkPanel;
-  __shared__ PkPanelLds S;
+  typedef PkPanelLds<SELF ? kChunk : kRing> Lds;
+  __shared__ Lds S;
   __shared__ __attribute__((aligned(16))) uint16_t capt[PLANE ? 2 * 64 * 16 : 1];
   extern __shared__ uint32_t selw[];
   const int wave = threadIdx.x >> 6;
   const uint32_t off2 = off * 0x10001u;
   const int gen = __hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  uint32_t staged = 0xFFFFFFFFu;
+  uint32_t staged = 0xFFFFFFFFu, seen[2] = {0, 0};
   for (;;) {
     if (threadIdx.x == 0) S.job = atomicAdd(a.counter, 1);
     __syncthreads();
@@ -523,8 +626,23 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc) {
     const TripletDesc ta = a.desc[jd.trip], tb = a.desc[jd.trip + 1];
     const int n0 = (int)max(ta.len[0], tb.len[0]);
     const int n1 = (int)max(ta.len[1], tb.len[1]), n2 = (int)max(ta.len[2], tb.len[2]);
+    // (Counts only grow, so a group's first wait serves its other panels.)
+    if (count && ta.after > seen[ta.set]) {
+      if (threadIdx.x == 0) {
+        const uint64_t t_start = wall_clock64();
+        while (__hip_atomic_load(a.counter + kFinished * (1 + ta.set), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+               (int)ta.after) {
+          if (wall_clock64() - t_start > a.wait_ticks) {
+            raise_error(a.ctl + 1);
+            break;
+          }
+          __builtin_amdgcn_s_sleep(8);
+        }
+      }
+      seen[ta.set] = ta.after;
+    }
     if (jd.trip != staged) {
-      stage_selectors(selw, a.words, ta, tb, n0, (int)threadIdx.x, 128);
+      stage_selectors(selw, a.words, ta, tb, n0, (int)threadIdx.x, SELF ? 64 : 128);
       staged = jd.trip;
     }
     if (threadIdx.x == 0) {
@@ -535,34 +653,52 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc) {
     }
     __syncthreads();
     const int PJ = n1 / H + 1, PK = n2 / W + 1;
-    const uint64_t per_panel = pk_panel_ints((uint32_t)n0), side = pk_face_rows((uint32_t)n0) * (2 * kPkPanel);
+    const uint64_t rows = pk_face_rows((uint32_t)n0);
     const uint32_t p = jd.panel;
     const int pj = (int)(p / (uint32_t)PK), pk = (int)(p % (uint32_t)PK);
     int* pool = a.pface + ta.face_off;
     PkPanelIO io;
-    io.top = pj ? pool + (uint64_t)(p - PK) * per_panel : nullptr;
-    io.left = pk ? pool + (uint64_t)(p - 1) * per_panel + side : nullptr;
-    io.out = pool + (uint64_t)p * per_panel;
+    const uint64_t cs = rows * (2 * kPkPanel), rs = rows * (2 * kPkPanel + 2);
+    int* rpool = pool + (uint64_t)PK * 2 * cs;
+    io.col_in = pool + (uint64_t)(2 * pk + ((pj & 1) ^ 1)) * cs;
+    io.col_out = pool + (uint64_t)(2 * pk + (pj & 1)) * cs;
+    io.row_in = rpool + (uint64_t)(2 * pj + ((pk & 1) ^ 1)) * rs;
+    io.row_out = rpool + (uint64_t)(2 * pj + (pk & 1)) * rs;
+    io.has_top = pj > 0;
+    io.has_left = pk > 0;
     io.bot = pj + 1 < PJ;
     io.right = pk + 1 < PK;
-    io.gen = gen;
+    io.top_tag = gen + (int)ta.tag0 + pj;
+    io.left_tag = gen + (int)ta.tag0 + pk;
     io.err = a.ctl + 1;
     io.wait_ticks = a.wait_ticks;
     uint32_t best = 0;
-    if (wave == 0)
-      pk_panel_compute<KIND, PLANE>(S, selw, a.sc, a.words, ta, tb, n0, pj, pk, io, capt, off2, best, kc);
-    else
-      pk_panel_memory(S, n0, io, off2);
+    if constexpr (SELF) {
+      pk_panel_compute<KIND, PLANE, true>(S, selw, a.sc, a.words, ta, tb, n0, pj, pk, io, capt, off2, best, kc);
+    } else {
+      if (wave == 0)
+        pk_panel_compute<KIND, PLANE, false>(S, selw, a.sc, a.words, ta, tb, n0, pj, pk, io, capt, off2, best, kc);
+      else
+        pk_panel_memory(S, n0, io, off2);
+    }
+    if (count) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's face stores
     __syncthreads();
     // Both waves are done: a wait of this job that gave up has raised the flag
     // by now, and upstream panels raised theirs before writing the faces this
     // job read.
+    if (count && threadIdx.x == 0) {
+      // (Every wave's face stores have reached memory: a later pair may
+      // overwrite them.)
+      __hip_atomic_fetch_add(a.counter + kFinished * (1 + ta.set), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     const uint32_t zero2 = psub(off2, S.base);
     if (PLANE) {
       // One half's plane by each wave.
-      const TripletDesc& td = wave ? tb : ta;
-      pk_write_plane(capt + wave * 64 * 16, a.plane + a.plane_off[jd.trip + wave], td, pj, pk,
-                     wave ? zero2 >> 16 : zero2 & 0xFFFFu, a.sc.gap2);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (SELF || wave == h)
+          pk_write_plane(capt + h, a.plane + a.plane_off[jd.trip + h], h ? tb : ta, pj, pk,
+                         h ? zero2 >> 16 : zero2 & 0xFFFFu, a.sc.gap2);
     }
     if (KIND == kGlobal && !PLANE && threadIdx.x < 2) {
       const int h = (int)threadIdx.x;
@@ -571,7 +707,13 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc) {
       if (r >= 0 && r < H && c >= 0 && c < W) {
         const uint32_t v = psub((uint32_t)S.cap[h][(r & 3) * 4 + (c & 3)], zero2);
         const int m = (int)(h ? v >> 16 : v & 0xFFFFu);
-        publish_score(a.scores + td.out, m + a.sc.gap2 * (int)(td.len[0] + td.len[1] + td.len[2]), io.err);
+        // (The faces this panel read had arrived before the barrier above, so
+        // this load of the flag comes after them.)
+        const bool bad = __hip_atomic_load(io.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        // System scope: the score may live in mapped host memory (serving).
+        __hip_atomic_store(a.scores + td.out,
+                           bad ? INT32_MIN : m + a.sc.gap2 * (int)(td.len[0] + td.len[1] + td.len[2]),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
     if (KIND != kGlobal && wave == 0) {
@@ -583,8 +725,13 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc) {
         int* acc = a.red + 2 * (uint64_t)jd.trip;
         __hip_atomic_fetch_max(acc, (int)(best & 0xFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_fetch_max(acc + 2, (int)(best >> 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int prev = __hip_atomic_fetch_add(acc + 1, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (prev == PJ * PK - 1) {
+        // (Halves: the meeting of their planes reads both bests.) The folds have
+        // reached memory before this panel counts itself finished: waiting for
+        // them is enough, as every access here is device-coherent; a release
+        // would write back the whole L2 for every panel.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const int prev = PLANE ? 0 : __hip_atomic_fetch_add(acc + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!PLANE && prev == PJ * PK - 1) {
           const int sub = KIND == kSemiGlobal ? (int)kc : 0;
           const bool bad = __hip_atomic_load(io.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 #pragma unroll
@@ -599,27 +746,33 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc) {
   }
 }
 
-#define TRIOSEQ_PKP(X) X(0, false) X(0, true) X(1, false) X(2, false) X(2, true)
+#define TRIOSEQ_PKP(X)                                                                  \
+  X(0, true, false) X(0, true, true) X(0, false, false) X(0, false, true)               \
+  X(1, false, false) X(1, false, true)                                                  \
+  X(2, true, false) X(2, true, true) X(2, false, false) X(2, false, true)
 
 }  // namespace
 
-hipError_t launch_panel_pk(int kind, const SweepArgs& a, uint32_t off, uint32_t kc, int grid, hipStream_t s) {
+hipError_t launch_panel_pk(int kind, bool self, const SweepArgs& a, uint32_t off, uint32_t kc, bool count, int grid,
+                           hipStream_t s) {
   const size_t lds = (size_t)(a.lds_n0 + 64) * 4;
   const bool plane = a.plane != nullptr;
-#define X(k, p)                                                                                   \
-  if (kind == k && plane == p) {                                                                  \
-    hipLaunchKernelGGL((k_panel_pk<k, p>), dim3(grid), dim3(128), lds, s, a, off, kc);            \
-    return hipGetLastError();                                                                     \
+#define X(k, p, f)                                                                           \
+  if (kind == k && plane == p && self == f) {                                                \
+    hipLaunchKernelGGL((k_panel_pk<k, p, f>), dim3(grid), dim3(f ? 64 : 128), lds, s, a, off, kc,   \
+                       count ? 1u : 0u);                                                     \
+    return hipGetLastError();                                                                \
   }
   TRIOSEQ_PKP(X)
 #undef X
   return hipErrorInvalidValue;
 }
 
-hipError_t panel_pk_occupancy(int kind, bool plane, uint32_t lds_n0, int* blocks_per_cu) {
-#define X(k, p)           \
-  if (kind == k && plane == p) \
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_panel_pk<k, p>, 128, (size_t)(lds_n0 + 64) * 4);
+hipError_t panel_pk_occupancy(int kind, bool plane, bool self, uint32_t lds_n0, int* blocks_per_cu) {
+#define X(k, p, f)                                                                                       \
+  if (kind == k && plane == p && self == f)                                                              \
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_panel_pk<k, p, f>, f ? 64 : 128, \
+                                                        (size_t)(lds_n0 + 64) * 4);
   TRIOSEQ_PKP(X)
 #undef X
   return hipErrorInvalidValue;

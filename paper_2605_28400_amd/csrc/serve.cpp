@@ -206,7 +206,7 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_jobs, sl.h_jobs, L.jobs.size() * sizeof(JobDesc), hipMemcpyHostToDevice,
                        sl.stream);
-  if (e == hipSuccess) e = launch_prepare(sl.ctl, sl.ctl + 64, d_red, L.red_pairs(), sl.stream);
+  if (e == hipSuccess) e = launch_prepare(sl.ctl, sl.ctl + 64, d_red, L.red_pairs(), sl.tagged, sl.tagged_bytes / 4, L.tag_step, sl.stream);
   if (e == hipSuccess) {
     SweepArgs args = make_sweep_args(d_words, d_desc, d_jobs, (uint32_t)L.jobs.size(), L.lds_n0,
                                      sl.d_scores, sl.ctl + 64, sl.ctl, d_face, L.face_stride, d_pface,
@@ -420,8 +420,8 @@ static trioseq_status trioseq_serve_create_body(const trioseq_serve_config* cfg,
       // Tag 0 belongs to no run (generations start at 1).
       if ((e = hipMemset(sl.tagged, 0, tagged_bytes)) != hipSuccess) return bail(e, "hipMemset");
     }
-    if ((e = hipMalloc((void**)&sl.ctl, 512)) != hipSuccess) return bail(e, "hipMalloc");
-    if ((e = hipMemset(sl.ctl, 0, 512)) != hipSuccess) return bail(e, "hipMemset");
+    if ((e = hipMalloc((void**)&sl.ctl, 256 + kCounterBytes)) != hipSuccess) return bail(e, "hipMalloc");
+    if ((e = hipMemset(sl.ctl, 0, 256 + kCounterBytes)) != hipSuccess) return bail(e, "hipMemset");
     sl.h_words_cap = max_words;
     sl.h_meta_cap = max_jobs;
     if ((e = hipHostMalloc((void**)&sl.h_words, std::max<uint64_t>(max_words, 1) * 4, 0)) != hipSuccess)

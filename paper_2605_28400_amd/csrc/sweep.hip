@@ -1299,12 +1299,9 @@ __global__ void k_init_boundary(Boundary b, int top_entries, int left_entries, i
 
 // Before each run: next generation, error flag cleared, queue head zeroed,
 // and the per-triplet reduction pairs reset (best = INT32_MIN, 0 finished).
-__global__ void k_prepare(int* ctl, int* counter, int* red, uint32_t nred) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    ctl[0] = ctl[0] + 1;
-    ctl[1] = 0;
-    counter[0] = 0;
-  }
+__global__ void k_prepare(int* ctl, int* counter, int* red, uint32_t nred, int* pool, uint64_t pool_ints,
+                          int step) {
+  if (blockIdx.x == 0) next_run(ctl, counter, pool, pool_ints, step);
   for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < nred; q += gridDim.x * blockDim.x) {
     red[2 * (uint64_t)q] = INT32_MIN;
     red[2 * (uint64_t)q + 1] = 0;
@@ -1340,9 +1337,11 @@ hipError_t launch_init_boundary(const KernelShape& ks, const Boundary& b, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_prepare(int* ctl, int* counter, int* red, uint32_t nred, hipStream_t s) {
+hipError_t launch_prepare(int* ctl, int* counter, int* red, uint32_t nred, int* pool, uint64_t pool_ints, int step,
+                          hipStream_t s) {
   const uint32_t blocks = nred == 0 ? 1 : nred > 256 * 256 ? 256 : (nred + 255) / 256;
-  hipLaunchKernelGGL(k_prepare, dim3(blocks), dim3(256), 0, s, ctl, counter, red, nred);
+  hipLaunchKernelGGL(k_prepare, dim3(blocks), dim3(256), 0, s, ctl, counter, red, nred, pool,
+                     pool_ints, step);
   return hipGetLastError();
 }
 

@@ -10,7 +10,7 @@
 // the box's score, so the split kernels pick such a cell and the box becomes
 // two. Boxes of at most kLeafCells cells are solved by k_leaf: the full
 // table of the box in LDS and a walk back from its far corner.
-#include "internal.h"
+#include "device.h"
 
 namespace trioseq {
 namespace {
@@ -201,16 +201,12 @@ __global__ void __launch_bounds__(64) k_leaf(LeafArgs a) {
 __global__ void __launch_bounds__(256) k_gather(const uint32_t* __restrict__ in,
                                                 const GatherDesc* __restrict__ d, uint32_t n,
                                                 uint32_t words_out, uint32_t* __restrict__ out,
-                                                int* __restrict__ ctl, int* __restrict__ counter) {
+                                                int* __restrict__ ctl, int* __restrict__ counter,
+                                                int* __restrict__ pool, uint64_t pool_ints) {
   const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-  // With ctl given, also the per-run preparation of the sweep that follows
-  // (next generation, error flag cleared, queue head zeroed), saving its
-  // launch: nothing here reads these words.
-  if (ctl && w == 0) {
-    ctl[0] = ctl[0] + 1;
-    ctl[1] = 0;
-    counter[0] = 0;
-  }
+  // With ctl given, also the per-run preparation of the sweep that follows,
+  // saving its launch: nothing here reads these words.
+  if (ctl && blockIdx.x == 0) next_run(ctl, counter, pool, pool_ints, 1);
   if (w >= words_out) return;
   // The output sequence holding word w (sequences start on fresh words).
   uint32_t q = 0;
@@ -227,21 +223,23 @@ __global__ void __launch_bounds__(256) k_gather(const uint32_t* __restrict__ in,
   out[w] = v;
 }
 
-// Meet, in one launch: workgroup c reduces chunk c of box 0 (kSplitChunk
-// plane cells) to its best F + R; the workgroup that finishes last folds the
-// chunks' bests, and the halves' own bests when given, into the score
-// (INT32_MIN if a wait of the run gave up) and clears the counter for the
-// next run.
-__global__ void __launch_bounds__(256) k_meet(const int* __restrict__ planes, const SplitDesc* __restrict__ box,
-                                              uint32_t nchunks, int* partial, const int* __restrict__ err,
-                                              const int* __restrict__ own, int* counter, int32_t* out) {
+// Meet, in one launch: a workgroup reduces one chunk of kSplitChunk plane cells
+// of a box to its best F + R; the workgroup that finishes its box last folds
+// the chunks' bests, and the halves' own bests when given, into the box's score
+// (INT32_MIN if a wait of the run gave up) and clears the box's counter for
+// the next run.
+__global__ void __launch_bounds__(256) k_meet(const int* __restrict__ planes, const SplitDesc* __restrict__ boxes,
+                                              const uint32_t* __restrict__ chunk_box, int* partial,
+                                              const int* __restrict__ err, const int* __restrict__ own, int own_step,
+                                              int* counters, int32_t* out) {
   __shared__ int s_val[256];
   __shared__ int s_last;
-  const SplitDesc d = box[0];
+  const uint32_t box = chunk_box ? chunk_box[blockIdx.x] : 0u;
+  const SplitDesc d = boxes[box];
   const int* F = planes + d.fwd;
   const int* R = planes + d.bwd;
   const uint32_t cells = d.rows * d.cols;
-  const uint32_t lo = blockIdx.x * kSplitChunk;
+  const uint32_t lo = (blockIdx.x - d.chunk0) * kSplitChunk;
   const uint32_t hi = min(cells, lo + kSplitChunk);
   int best = INT32_MIN;
   // kSplitBatch cells per thread per pass, their loads issued together.
@@ -265,14 +263,14 @@ __global__ void __launch_bounds__(256) k_meet(const int* __restrict__ planes, co
   }
   if (threadIdx.x == 0) {
     __hip_atomic_store(&partial[blockIdx.x], s_val[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int done = __hip_atomic_fetch_add(counter, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = done == (int)nchunks - 1;
+    const int done = __hip_atomic_fetch_add(counters + box, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = done == (int)d.nchunk - 1;
   }
   __syncthreads();
   if (!s_last) return;
-  int b = (own && threadIdx.x < 2) ? own[threadIdx.x] : INT32_MIN;
-  for (uint32_t c = threadIdx.x; c < nchunks; c += blockDim.x)
-    b = max(b, __hip_atomic_load(&partial[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  int b = (own && threadIdx.x < 2) ? own[4 * (uint64_t)box + threadIdx.x * own_step] : INT32_MIN;
+  for (uint32_t c = threadIdx.x; c < d.nchunk; c += blockDim.x)
+    b = max(b, __hip_atomic_load(&partial[d.chunk0 + c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   __syncthreads();
   s_val[threadIdx.x] = b;
   __syncthreads();
@@ -282,26 +280,28 @@ __global__ void __launch_bounds__(256) k_meet(const int* __restrict__ planes, co
   }
   if (threadIdx.x == 0) {
     const bool bad = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    __hip_atomic_store(out, bad ? INT32_MIN : s_val[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(out + d.out, bad ? INT32_MIN : s_val[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(counters + box, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 }  // namespace
 
 hipError_t launch_gather(const uint32_t* in, const GatherDesc* d, uint32_t n, uint32_t words_out,
-                         uint32_t* out, int* ctl, int* counter, hipStream_t s) {
+                         uint32_t* out, int* ctl, int* counter, int* pool, uint64_t pool_ints, hipStream_t s) {
   if (words_out == 0 && !ctl) return hipSuccess;
   const uint32_t blocks = words_out == 0 ? 1 : (words_out + 255) / 256;
-  hipLaunchKernelGGL(k_gather, dim3(blocks), dim3(256), 0, s, in, d, n, words_out, out, ctl, counter);
+  hipLaunchKernelGGL(k_gather, dim3(blocks), dim3(256), 0, s, in, d, n, words_out, out, ctl, counter,
+                     pool, pool_ints);
   return hipGetLastError();
 }
 
-hipError_t launch_meet(const SplitDesc* box, uint32_t nchunks, const int* planes, int* partial,
-                       const int* err, const int* own, int* counter, int32_t* out, hipStream_t s) {
+hipError_t launch_meet(const SplitDesc* boxes, const uint32_t* chunk_box, uint32_t nchunks, const int* planes,
+                       int* partial, const int* err, const int* own, int own_step, int* counters, int32_t* out,
+                       hipStream_t s) {
   if (nchunks == 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_meet, dim3(nchunks), dim3(256), 0, s, planes, box, nchunks, partial, err, own, counter,
-                     out);
+  hipLaunchKernelGGL(k_meet, dim3(nchunks), dim3(256), 0, s, planes, boxes, chunk_box, partial, err, own, own_step,
+                     counters, out);
   return hipGetLastError();
 }
 

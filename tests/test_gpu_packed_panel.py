@@ -86,3 +86,64 @@ def test_largest_values(torch_cuda):
         print(f"values n={n}", flush=True)
         outs, info = run(torch_cuda, [(x, x, x)], ts.scoring(5, -4, -6))
         assert info["packed"] == 1 and int(outs[0][0]) == 15 * n  # 3 pairs of 5 per column
+
+
+def batches(rng):
+    def mut(n):
+        return synth.mutated_triplet(rng, int(n), 0.1)
+
+    def uni(*n):
+        return tuple(synth.uniform_seq(rng, m) for m in n)
+
+    return {"two": [mut(100), mut(60)],
+            "odd count": [mut(100), mut(130), mut(20)],
+            "one large": [mut(220)] + [mut(n) for n in rng.integers(5, 60, 40)],
+            "shapes": [uni(300, 5, 70), uni(0, 90, 120), uni(64, 64, 64), uni(1, 1, 200), uni(33, 200, 2),
+                       uni(0, 0, 0), uni(96, 0, 33)],
+            "halves": [mut(n) for n in (420, 400, 380)],
+            # More panels a diagonal than a group of pairs takes: three groups
+            # or more, whose faces share two sets of buffers.
+            "groups": [mut(n) for n in rng.integers(40, 75, 9000)]}
+
+
+@pytest.mark.parametrize("name", ["two", "odd count", "one large", "shapes", "halves", "groups"])
+@pytest.mark.parametrize("kind", [ts.GLOBAL, ts.SEMI_GLOBAL, ts.LOCAL], ids=["global", "semi-global", "local"])
+def test_batches_equal_oracle(torch_cuda, kind, name):
+    trips = batches(np.random.default_rng(82))[name]
+    for scheme in SCHEMES[:1] if name == "groups" else SCHEMES:
+        want = want_scores(trips, scheme, kind)
+        for graph in (False, True):
+            print(f"batch kind={kind} {name} scheme={scheme} graph={graph}", flush=True)
+            outs, info = run(torch_cuda, trips, ts.scoring(*scheme, kind=kind), reps=3, use_graph=graph)
+            assert info["packed"] == 1 and info["panels"] > 0
+            for got in outs:
+                bad = np.flatnonzero(got != want)
+                assert bad.size == 0, [(int(q), int(got[q]), int(want[q])) for q in bad[:5]]
+
+
+def test_lone_semi_global(torch_cuda):
+    rng = np.random.default_rng(83)
+    for n in LONE:
+        t = synth.mutated_triplet(rng, max(n), 0.1, lens=n)
+        print(f"lone semi-global lens={n}", flush=True)
+        for scheme in SCHEMES:
+            outs, _ = run(torch_cuda, [t], ts.scoring(*scheme, kind=ts.SEMI_GLOBAL))
+            assert all((o == want_scores([t], scheme, ts.SEMI_GLOBAL)).all() for o in outs)
+
+
+def test_bounded_wait_gives_int32_min(torch_cuda):
+    # A wait bound of one clock tick: a panel whose neighbour is not there yet
+    # gives up at once, every kernel ends, and no score but INT32_MIN comes
+    # back; the plan works again afterwards.
+    rng = np.random.default_rng(84)
+    t = synth.mutated_triplet(rng, 400, 0.05, lens=(400, 380, 390))
+    want = int(want_scores([t], SCHEMES[0], ts.GLOBAL)[0])
+    try:
+        ts.set_wait_limit(10)
+        outs, info = run(torch_cuda, [t], ts.scoring())
+    finally:
+        ts.set_wait_limit(0)
+    assert info["packed"] == 1 and all(int(o[0]) in (-2**31, want) for o in outs)
+    assert any(int(o[0]) == -2**31 for o in outs)
+    outs, _ = run(torch_cuda, [t], ts.scoring())
+    assert all(int(o[0]) == want for o in outs)
