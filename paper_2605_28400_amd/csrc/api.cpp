@@ -533,8 +533,16 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
     const uint64_t most = sc.kind == kGlobal ? A * pairs : std::max(A, g) * (a + b + c);
     const uint64_t score = (uint64_t)maxs * pairs;  // no score is larger
     if (most > 0xFFFF || (sc.kind == kLocal && score > 30000)) return false;
-    if (sc.kind == kSemiGlobal) kc = std::max(kc, g * (a + b + c) + 1);
   }
+  // Semi-global candidates M + kc must be positive on every cell of a pair's
+  // common panel grid: a triplet's last slice is taken with its padding.
+  if (sc.kind == kSemiGlobal)
+    for (size_t p = 0; p + 1 < desc.size(); p += 2) {
+      const TripletDesc &a = desc[p], &b = desc[p + 1];
+      uint64_t sum = std::max(a.len[0], b.len[0]);
+      for (int k = 1; k < 3; ++k) sum += (uint64_t)(std::max(a.len[k], b.len[k]) / kPkPanel + 1) * kPkPanel;
+      kc = std::max(kc, g * sum + 1);
+    }
   for (const TripletDesc& d : desc)
     if (sc.kind == kSemiGlobal &&
         kc + (uint64_t)maxs * (std::min(d.len[0], d.len[1]) + std::min(d.len[0], d.len[2]) + std::min(d.len[1], d.len[2])) >
@@ -659,6 +667,38 @@ static void half_descs(const uint32_t* l, const uint64_t* off, TripletDesc d[2],
     d[h].rev = (uint32_t)h;
   }
   *box = SplitDesc{0, 0, l[order[1]] + 1, l[order[2]] + 1, 0, 0, 0};
+}
+
+bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L) {
+  TripletDesc h[2];
+  SplitDesc box;
+  half_descs(lens, off, h, &box);
+  const uint64_t cells = (uint64_t)box.rows * box.cols;
+  Layout P;
+  if (!pair_panel_layout({h[0], h[1]}, sc, true, &P)) return false;
+  box.bwd = cells;
+  box.nchunk = (uint32_t)((cells + kSplitChunk - 1) / kSplitChunk);
+  P.halves = true;
+  P.boxes = {box};
+  P.chunk_box.assign(box.nchunk, 0u);
+  P.plane_off = {0, cells};
+  P.plane_ints = 2 * cells;
+  *L = std::move(P);
+  return true;
+}
+
+bool packed_self_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L) {
+  const AxisChoice w = choose_axes_wide(lens);
+  TripletDesc d{};
+  for (int k = 0; k < 3; ++k) {
+    d.off[k] = off[w.perm[k]];
+    d.len[k] = lens[w.perm[k]];
+  }
+  Layout P;
+  if (!pair_panel_layout({d, d}, sc, false, &P)) return false;
+  P.panels /= 2;
+  *L = std::move(P);
+  return true;
 }
 
 bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L) {
@@ -1039,8 +1079,6 @@ bool half_split_layout(const uint32_t* lens, const uint64_t* word_off, int32_t m
       h->gather[i] = GatherDesc{src[q], w, start, len, (uint32_t)half};
       w += (len + 15) / 16;
     }
-  SplitDesc box;
-  half_descs(lens, src, h->pair, &box);
   h->words = (uint32_t)w;
   h->rows = lens[r] + 1;
   h->cols = lens[c] + 1;
@@ -1115,32 +1153,33 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
                           half_split_layout(lens, word_off, 0, &hs);
   if ((half && may_pack) || long_local) {
     const uint64_t int32_pool = L.pool_ints * sizeof(int);
+    const double cells = L.cells;
+    std::vector<uint64_t> def(3);
+    uint64_t tw = 0;
+    if (!word_off) trioseq_packed_layout(lens, 1, def.data(), &tw);
     Layout P;
-    if (pair_panel_layout({hs.pair[0], hs.pair[1]}, *scp, true, &P)) {
+    if (packed_halves_layout(lens, word_off ? word_off : def.data(), *scp, &P)) {
       if (mem && int32_pool > mem->pool_bytes)
         return fail(TRIOSEQ_ERR_TOO_LARGE,
                     "allocation-free scoring: panel faces of split triplets exceed the scratch array's face pool");
-      P.cells = L.cells;
-      const uint64_t cells = (uint64_t)hs.rows * hs.cols;
-      P.halves = true;
-      P.boxes = {SplitDesc{0, cells, hs.rows, hs.cols, 0, (uint32_t)((cells + kSplitChunk - 1) / kSplitChunk), 0}};
-      P.plane_off = {0, cells};
-      P.plane_ints = 2 * cells;
       L = std::move(P);
+      L.cells = cells;
       half = true;
     }
   }
-  // A lone semi-global triplet runs as a pair with itself: per cell as many
-  // instructions as int32 lanes take, but the packed kernel's shorter hops and
-  // polls (723 x 651 x 698: 824 -> 721 us, 1024 x 1000 x 1048: 1.33 -> 1.15 ms).
-  if (n == 1 && scp->kind == kSemiGlobal && defaults && may_pack && !mem && o.lane_exchange != 2 && L.modes == 2) {
-    const TripletDesc& d = L.desc[0];
-    Layout P;
-    if (pair_panel_layout({d, d}, *scp, false, &P)) {
-      P.panels /= 2;
-      P.cells = L.cells;
-      L = std::move(P);
-    }
+  // A lone triplet that has no halves path (semi-global scoring, or shorter than
+  // it takes) runs as a pair with itself: per cell as many instructions as
+  // int32 lanes take, but the packed kernel's shorter hops and polls
+  // (semi-global 723 x 651 x 698: 824 -> 721 us, 1024 x 1000 x 1048: 1.33 -> 1.15
+  // ms; global 48 x 45 x 51: 68 -> 58 us, 100 x 97 x 104: 119 -> 95 us).
+  if (n == 1 && defaults && may_pack && !mem && !half && o.lane_exchange != 2 && L.modes == 2 &&
+      (scp->kind == kSemiGlobal ||
+       (o.half_split_min == 0 && std::max({lens[0], lens[1], lens[2]}) < kHalfSplitMin))) {
+    std::vector<uint64_t> def(3);
+    uint64_t tw = 0;
+    if (!word_off) trioseq_packed_layout(lens, 1, def.data(), &tw);
+    const double cells = L.cells;
+    if (packed_self_layout(lens, word_off ? word_off : def.data(), *scp, &L)) L.cells = cells;
   }
   const size_t nd = L.desc.size();  // triplets the kernels see
 

@@ -120,6 +120,10 @@ trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
 // in dependency order; false if a pair's values could leave the 16-bit range
 // under this scoring.
 bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, Layout* L);
+// One triplet's halves (longest sequence cut in two) as one packed pair, and
+// one triplet as a pair with itself.
+bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
+bool packed_self_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 // Lays out a batch as packed panel jobs of pairs: neighbours by size, or the
 // halves of every triplet. False if a value could leave the 16-bit range.
 bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L);
@@ -186,7 +190,6 @@ struct HalfSplit {
   uint32_t lens[6];
   uint64_t offs[6];      // word offsets in the gathered buffer
   GatherDesc gather[6];
-  TripletDesc pair[2];   // the same halves read from the caller's words in place
   uint32_t words = 0;    // gathered words
   uint32_t rows = 0, cols = 0;
 };

@@ -63,7 +63,8 @@ struct Slot {
   uint64_t h_words_cap = 0;
   TripletDesc* h_desc = nullptr;
   JobDesc* h_jobs = nullptr;
-  uint64_t h_meta_cap = 0;      // entries of h_desc / h_jobs
+  char* h_meet = nullptr;
+  uint64_t h_desc_cap = 0, h_jobs_cap = 0, h_meet_cap = 0;
   int32_t* h_scores = nullptr;  // pinned, mapped: written by the GPU
   int32_t* d_scores = nullptr;  // device address of h_scores
   uint32_t max_batch = 0;
@@ -112,12 +113,18 @@ namespace {
 
 uint64_t align256(uint64_t v) { return (v + 255) / 256 * 256; }
 
+// Bytes of a round's meeting tables (boxes, plane offsets, chunks, counters).
+uint64_t meet_bytes(const Layout& L) {
+  return L.halves ? L.boxes.size() * (sizeof(SplitDesc) + 20) + L.chunk_box.size() * 4 : 0;
+}
+
 // Device bytes a round needs in a slot arena (the panel-face pool lives in
 // the slot's tagged region instead: L.pool_ints * 4 bytes).
 uint64_t arena_need(const Layout& L, uint64_t words, int grid) {
   return align256(words * 4) + align256(L.desc.size() * sizeof(TripletDesc)) +
          align256(L.jobs.size() * sizeof(JobDesc)) + align256((uint64_t)L.red_pairs() * 8) +
-         align256((uint64_t)grid * L.face_stride * 4);
+         align256((uint64_t)grid * L.face_stride * 4) +
+         (L.halves ? align256(meet_bytes(L)) + align256(L.chunk_box.size() * 4) + align256(L.plane_ints * 4) : 0);
 }
 
 void record_result(trioseq_server* s, const Request& r, int32_t score, int32_t status, uint64_t t) {
@@ -153,27 +160,47 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
     }
     words += batch[q].words.size();
   }
-  trioseq_plan_options o{-1, s->ks.rj, s->ks.rk, 0, 0, 0};
+  // Packed panel jobs where the round's values fit 16 bits: a lone request's
+  // halves, several in pairs or by halves, on single waves while other rounds
+  // share the device. Else int32 jobs. (500 requests of 64-2048 residues at
+  // once: 59 ms, 212 ms with int32 jobs.)
   Layout& L = *L_out;
-  trioseq_status st =
-      build_layout(lens.data(), offs.data(), n, s->sc, o, s->dp.cus * kWavesPerCuHint, &L);
-  if (st != TRIOSEQ_OK) {
-    *err = trioseq_last_error();
-    return st;
-  }
-  // Rounds of several split requests, or of one that shares the device with
-  // other rounds: their panel jobs are swept by single-wave workgroups (two
-  // computing waves per SIMD) rather than by computing and staging wave
-  // pairs.
-  if (L.modes == 2 && (L.desc.size() >= 2 || !alone)) L.modes = 3;
+  L = Layout{};
+  const bool halves = n == 1 && s->sc.kind != kSemiGlobal && std::max({lens[0], lens[1], lens[2]}) >= kHalfSplitMin;
+  bool packed = halves ? packed_halves_layout(lens.data(), offs.data(), s->sc, &L)
+                : n == 1 ? packed_self_layout(lens.data(), offs.data(), s->sc, &L)
+                         : packed_batch_layout(lens.data(), offs.data(), n, s->sc, &L);
+  if (packed && !alone) L.pk_self = true;
   int grid = 0, wpc = 0;
-  st = layout_grid(L, s->dp, 0, &grid, &wpc);
-  if (st != TRIOSEQ_OK) {
-    *err = trioseq_last_error();
-    return st;
-  }
-  if (arena_need(L, words, grid) > sl.arena_bytes || L.pool_ints * 4 > sl.tagged_bytes ||
-      words > sl.h_words_cap || L.jobs.size() > sl.h_meta_cap || n > sl.max_batch) {
+  for (;;) {
+    if (!packed) {
+      L = Layout{};
+      const trioseq_plan_options o{-1, s->ks.rj, s->ks.rk, 0, 0, 0};
+      const trioseq_status st = build_layout(lens.data(), offs.data(), n, s->sc, o, s->dp.cus * kWavesPerCuHint, &L);
+      if (st != TRIOSEQ_OK) {
+        *err = trioseq_last_error();
+        return st;
+      }
+      // Rounds of several split requests, or of one that shares the device with
+      // other rounds: their panel jobs are swept by single-wave workgroups (two
+      // computing waves per SIMD) rather than by computing and staging wave
+      // pairs.
+      if (L.modes == 2 && (L.desc.size() >= 2 || !alone)) L.modes = 3;
+    }
+    const trioseq_status st = layout_grid(L, s->dp, 0, &grid, &wpc);
+    if (st != TRIOSEQ_OK) {
+      *err = trioseq_last_error();
+      return st;
+    }
+    if (arena_need(L, words, grid) <= sl.arena_bytes && L.pool_ints * 4 <= sl.tagged_bytes && words <= sl.h_words_cap &&
+        L.jobs.size() <= sl.h_jobs_cap && L.desc.size() <= sl.h_desc_cap && meet_bytes(L) <= sl.h_meet_cap &&
+        n <= sl.max_batch)
+      break;
+    // A slot holds at least the int32 layout of any one request.
+    if (packed && n == 1) {
+      packed = false;
+      continue;
+    }
     *err = "round does not fit its slot";
     return TRIOSEQ_ERR_TOO_LARGE;
   }
@@ -183,7 +210,8 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
     std::memcpy(sl.h_words + w, batch[q].words.data(), batch[q].words.size() * 4);
     w += batch[q].words.size();
   }
-  std::memcpy(sl.h_desc, L.desc.data(), n * sizeof(TripletDesc));
+  const size_t nd = L.desc.size();
+  std::memcpy(sl.h_desc, L.desc.data(), nd * sizeof(TripletDesc));
   std::memcpy(sl.h_jobs, L.jobs.data(), L.jobs.size() * sizeof(JobDesc));
   for (size_t q = 0; q < n; ++q) sl.h_scores[q] = kPending;
 
@@ -191,27 +219,53 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
   uint32_t* d_words = (uint32_t*)a;
   a += align256(words * 4);
   TripletDesc* d_desc = (TripletDesc*)a;
-  a += align256(n * sizeof(TripletDesc));
+  a += align256(nd * sizeof(TripletDesc));
   JobDesc* d_jobs = (JobDesc*)a;
   a += align256(L.jobs.size() * sizeof(JobDesc));
   int* d_red = (int*)a;
   a += align256((uint64_t)L.red_pairs() * 8);
+  // Halves: boxes, plane offsets, the box of every chunk and a zeroed counter
+  // per box (staged as one block), then the chunks' bests and the planes.
+  const size_t nb = L.boxes.size(), nc = L.chunk_box.size();
+  char* d_meet = a;
+  if (L.halves) {
+    char* h = sl.h_meet;
+    std::memcpy(h, L.boxes.data(), nb * sizeof(SplitDesc));
+    std::memcpy(h + nb * sizeof(SplitDesc), L.plane_off.data(), nb * 16);
+    std::memcpy(h + nb * (sizeof(SplitDesc) + 16), L.chunk_box.data(), nc * 4);
+    std::memset(h + nb * (sizeof(SplitDesc) + 16) + nc * 4, 0, nb * 4);
+    a += align256(meet_bytes(L)) + align256(nc * 4) + align256(L.plane_ints * 4);
+  }
+  int* d_partial = (int*)(d_meet + align256(meet_bytes(L)));
+  int* d_plane = (int*)((char*)d_partial + align256(nc * 4));
   int* d_face = (int*)a;
   int* d_pface = sl.tagged;
 
   hipError_t e = hipSuccess;
   if (words) e = hipMemcpyAsync(d_words, sl.h_words, words * 4, hipMemcpyHostToDevice, sl.stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(d_desc, sl.h_desc, n * sizeof(TripletDesc), hipMemcpyHostToDevice, sl.stream);
+    e = hipMemcpyAsync(d_desc, sl.h_desc, nd * sizeof(TripletDesc), hipMemcpyHostToDevice, sl.stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_jobs, sl.h_jobs, L.jobs.size() * sizeof(JobDesc), hipMemcpyHostToDevice,
                        sl.stream);
+  if (e == hipSuccess && L.halves)
+    e = hipMemcpyAsync(d_meet, sl.h_meet, meet_bytes(L), hipMemcpyHostToDevice, sl.stream);
   if (e == hipSuccess) e = launch_prepare(sl.ctl, sl.ctl + 64, d_red, L.red_pairs(), sl.tagged, sl.tagged_bytes / 4, L.tag_step, sl.stream);
   if (e == hipSuccess) {
     SweepArgs args = make_sweep_args(d_words, d_desc, d_jobs, (uint32_t)L.jobs.size(), L.lds_n0,
                                      sl.d_scores, sl.ctl + 64, sl.ctl, d_face, L.face_stride, d_pface,
                                      s->bnd, d_red, s->dsc);
-    e = launch_sweep(L.ks, L.modes, args, grid, sl.stream);
+    if (L.halves) {
+      args.plane = d_plane;
+      args.plane_off = (const uint64_t*)(d_meet + nb * sizeof(SplitDesc));
+    }
+    e = packed ? launch_panel_pk(s->sc.kind, L.pk_self, args, L.pk_base, L.pk_kc, L.pk_reuse, grid, sl.stream)
+               : launch_sweep(L.ks, L.modes, args, grid, sl.stream);
+    if (e == hipSuccess && L.halves) {
+      const uint32_t* d_chunk_box = (const uint32_t*)(d_meet + nb * (sizeof(SplitDesc) + 16));
+      e = launch_meet((const SplitDesc*)d_meet, d_chunk_box, (uint32_t)nc, d_plane, d_partial, sl.ctl + 1,
+                      s->sc.kind == kLocal ? d_red : nullptr, 2, (int*)(d_chunk_box + nc), sl.d_scores, sl.stream);
+    }
   }
   if (e == hipSuccess) e = hipEventRecord(sl.done, sl.stream);
   if (e != hipSuccess) {
@@ -322,6 +376,7 @@ void free_server(trioseq_server* s) {
     (void)hipHostFree(sl.h_words);
     (void)hipHostFree(sl.h_desc);
     (void)hipHostFree(sl.h_jobs);
+    (void)hipHostFree(sl.h_meet);
     (void)hipHostFree(sl.h_scores);
   }
   (void)hipFree(s->d_bnd);
@@ -404,7 +459,11 @@ static trioseq_status trioseq_serve_create_body(const trioseq_serve_config* cfg,
   s->bnd = carve_boundary(s->ks, cfg->max_len, s->d_bnd);
   if ((e = launch_init_boundary(s->ks, s->bnd, nullptr)) != hipSuccess) return bail(e, "boundary init");
   const uint64_t max_words = (uint64_t)s->cfg.max_batch * 3 * ((cfg->max_len + 15) / 16);
-  const uint64_t max_jobs = (uint64_t)s->cfg.max_batch + 65536;
+  // Panel jobs of a full round, at least those of its largest request. (A
+  // round with more is made smaller.)
+  const uint64_t side = cfg->max_len / kPkPanel + 1;
+  const uint64_t max_jobs = std::max<uint64_t>((uint64_t)s->cfg.max_batch + (1u << 19), side * side);
+  const uint64_t max_desc = 2 * ((uint64_t)s->cfg.max_batch + 1);
   for (Slot& sl : s->slots) {
     sl.max_batch = s->cfg.max_batch;
     sl.arena_bytes = per_slot - tagged_bytes;
@@ -423,10 +482,13 @@ static trioseq_status trioseq_serve_create_body(const trioseq_serve_config* cfg,
     if ((e = hipMalloc((void**)&sl.ctl, 256 + kCounterBytes)) != hipSuccess) return bail(e, "hipMalloc");
     if ((e = hipMemset(sl.ctl, 0, 256 + kCounterBytes)) != hipSuccess) return bail(e, "hipMemset");
     sl.h_words_cap = max_words;
-    sl.h_meta_cap = max_jobs;
+    sl.h_jobs_cap = max_jobs;
+    sl.h_desc_cap = max_desc;
+    sl.h_meet_cap = 1u << 22;
     if ((e = hipHostMalloc((void**)&sl.h_words, std::max<uint64_t>(max_words, 1) * 4, 0)) != hipSuccess)
       return bail(e, "hipHostMalloc");
-    if ((e = hipHostMalloc((void**)&sl.h_desc, max_jobs * sizeof(TripletDesc), 0)) != hipSuccess)
+    if ((e = hipHostMalloc((void**)&sl.h_desc, max_desc * sizeof(TripletDesc), 0)) != hipSuccess ||
+        (e = hipHostMalloc((void**)&sl.h_meet, sl.h_meet_cap, 0)) != hipSuccess)
       return bail(e, "hipHostMalloc");
     if ((e = hipHostMalloc((void**)&sl.h_jobs, max_jobs * sizeof(JobDesc), 0)) != hipSuccess)
       return bail(e, "hipHostMalloc");

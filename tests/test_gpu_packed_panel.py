@@ -101,12 +101,14 @@ def batches(rng):
             "shapes": [uni(300, 5, 70), uni(0, 90, 120), uni(64, 64, 64), uni(1, 1, 200), uni(33, 200, 2),
                        uni(0, 0, 0), uni(96, 0, 33)],
             "halves": [mut(n) for n in (420, 400, 380)],
+            # Partners whose common grid is larger than either.
+            "crossed": [uni(140, 100, 20), uni(140, 40, 90), uni(70, 66, 65), uni(70, 95, 5)],
             # More panels a diagonal than a group of pairs takes: three groups
             # or more, whose faces share two sets of buffers.
             "groups": [mut(n) for n in rng.integers(40, 75, 9000)]}
 
 
-@pytest.mark.parametrize("name", ["two", "odd count", "one large", "shapes", "halves", "groups"])
+@pytest.mark.parametrize("name", ["two", "odd count", "one large", "shapes", "halves", "crossed", "groups"])
 @pytest.mark.parametrize("kind", [ts.GLOBAL, ts.SEMI_GLOBAL, ts.LOCAL], ids=["global", "semi-global", "local"])
 def test_batches_equal_oracle(torch_cuda, kind, name):
     trips = batches(np.random.default_rng(82))[name]
