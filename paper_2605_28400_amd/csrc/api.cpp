@@ -1374,8 +1374,10 @@ namespace trioseq {
 
 PlaneWorkspace::~PlaneWorkspace() {
   for (Buf* b : {&ctl, &desc, &jobs, &face, &pool, &bnd, &red, &plane, &plane_off, &words, &scores, &sd,
-                 &split_out, &chunk_box, &partial, &lwords, &leaves, &cols, &ncols, &lscore})
+                 &split_out, &chunk_box, &partial, &lwords, &leaves, &cols, &ncols, &lscore, &tables})
     (void)hipFree(b->p);
+  (void)hipHostFree(h_stage);
+  (void)hipHostFree(h_out);
 }
 
 uint64_t ws_bytes(const PlaneWorkspace& ws) {
@@ -1383,7 +1385,7 @@ uint64_t ws_bytes(const PlaneWorkspace& ws) {
   for (const PlaneWorkspace::Buf* b :
        {&ws.ctl, &ws.desc, &ws.jobs, &ws.face, &ws.pool, &ws.bnd, &ws.red, &ws.plane, &ws.plane_off,
         &ws.words, &ws.scores, &ws.sd, &ws.split_out, &ws.chunk_box, &ws.partial, &ws.lwords, &ws.leaves,
-        &ws.cols, &ws.ncols, &ws.lscore})
+        &ws.cols, &ws.ncols, &ws.lscore, &ws.tables})
     t += b->bytes;
   return t;
 }

@@ -212,6 +212,14 @@ struct PlaneWorkspace {
   Buf ctl, desc, jobs, face, pool, bnd, red, plane, plane_off, words, scores;
   // Traceback levels: split descriptors and results, leaf tables and columns.
   Buf sd, split_out, chunk_box, partial, lwords, leaves, cols, ncols, lscore;
+  // Packed levels: a level's tables in one buffer, staged in pinned host memory
+  // (which the copies of the level before have left), and its split points,
+  // written to mapped host memory.
+  Buf tables;
+  char* h_stage = nullptr;
+  uint64_t h_stage_bytes = 0;
+  int *h_out = nullptr, *d_out = nullptr;
+  uint64_t h_out_ints = 0;
   Boundary boundary{};
   uint32_t bnd_n0 = 0;
   bool have_props = false;

@@ -116,84 +116,101 @@ __global__ void __launch_bounds__(64) k_split_final(const SplitDesc* __restrict_
   }
 }
 
-// One wave per leaf box: the table of Eq. 1 over the box (global
+// One workgroup per leaf box: the table of Eq. 1 over the box (global
 // initialisation: the box's corner is 0, moves leaving the box do not exist)
 // in LDS, filled one anti-diagonal plane i + j + k = const at a time (every
-// predecessor lies on one of the three previous planes), then lane 0 walks
-// back from the far corner, taking at every cell the first move, in a fixed
-// order, whose predecessor plus column score gives the cell's value. Columns
-// are written last first, one byte per sequence (0..3 a residue, 4 a gap).
-__global__ void __launch_bounds__(64) k_leaf(LeafArgs a) {
+// predecessor lies on one of the three previous planes), then the first wave
+// walks back from the far corner, taking at every cell the first move, in a
+// fixed order, whose predecessor plus column score gives the cell's value.
+// Columns are written last first, one byte per sequence (0..3 a residue, 4 a
+// gap). Both parts are chains of LDS latencies, not work: four waves share a
+// plane, the substitution scores are in LDS (read from the kernel arguments,
+// they were a memory access per lane), and the walk tests a cell's seven moves
+// on seven lanes. With one wave
+// a box the boxes of a 1024 x 1000 x 1048 alignment took 107 us, now 29; 1000
+// alignments of 8-64 residues 240, now 71.
+constexpr int kLeafThreads = 256;
+__global__ void __launch_bounds__(kLeafThreads) k_leaf(LeafArgs a) {
   __shared__ int T[kLeafCells];
-  __shared__ uint8_t res[3][kLeafCells];
+  __shared__ uint8_t res[kLeafCells + 4];  // the three sequences, one behind the other
+  __shared__ int sub[16];
   const uint32_t leaf = blockIdx.x;
   if (leaf >= a.n) return;
   const LeafDesc d = a.leaves[leaf];
   const int A = (int)d.len[0], B = (int)d.len[1], C = (int)d.len[2];
-  const int lane = threadIdx.x;
-  for (int s = 0; s < 3; ++s)
-    for (int q = lane; q < (int)d.len[s]; q += 64) res[s][q] = (uint8_t)leaf_residue(a.words, d.off[s], d.lo[s] + q);
+  const int tid = threadIdx.x;
+  // (Residue p of a sequence sits at index p of its part; index -1 is read for
+  // cells on a face and not used.)
+  uint8_t *rx = res + 1, *ry = rx + A, *rz = ry + B;
+  for (int q = tid; q < A; q += kLeafThreads) rx[q] = (uint8_t)leaf_residue(a.words, d.off[0], d.lo[0] + q);
+  for (int q = tid; q < B; q += kLeafThreads) ry[q] = (uint8_t)leaf_residue(a.words, d.off[1], d.lo[1] + q);
+  for (int q = tid; q < C; q += kLeafThreads) rz[q] = (uint8_t)leaf_residue(a.words, d.off[2], d.lo[2] + q);
+  if (tid == 0) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) sub[q] = a.sub[q];
+    res[0] = 0;
+    T[0] = 0;
+  }
   __syncthreads();
   const int sB = (B + 1) * (C + 1), sC = C + 1;
   const int g2 = 2 * a.gap;
   constexpr int kNone = INT32_MIN / 2;
   const int pairs = (A + 1) * (B + 1);
-  for (int dd = 0; dd <= A + B + C; ++dd) {
-    for (int q = lane; q < pairs; q += 64) {
-      const int i = q / (B + 1), j = q - i * (B + 1), k = dd - i - j;
+  // q / (B + 1) for q < 4096 (exact: the quotient's distance to an integer is
+  // far above the rounding).
+  const float inv = 1.0f / (float)(B + 1);
+  for (int dd = 1; dd <= A + B + C; ++dd) {
+    for (int q = tid; q < pairs; q += kLeafThreads) {
+      const int i = (int)(((float)q + 0.5f) * inv), j = q - i * (B + 1), k = dd - i - j;
       if (k < 0 || k > C) continue;
       const int at = i * sB + j * sC + k;
-      if (dd == 0) {
-        T[0] = 0;
-        continue;
-      }
-      const int x = i ? res[0][i - 1] : 0, y = j ? res[1][j - 1] : 0, z = k ? res[2][k - 1] : 0;
+      const int x = 4 * rx[i - 1], y = ry[j - 1], z = rz[k - 1];
+      const int sxy = sub[x + y], sxz = sub[x + z], syz = sub[4 * y + z];
+      // Predecessors outside the box are read from the corner and dropped.
+      const bool ij = i && j, ik = i && k, jk = j && k, ijk = ij && k;
+      const int t7 = T[ijk ? at - sB - sC - 1 : 0], t6 = T[ij ? at - sB - sC : 0], t5 = T[ik ? at - sB - 1 : 0],
+                t4 = T[jk ? at - sC - 1 : 0], t3 = T[i ? at - sB : 0], t2 = T[j ? at - sC : 0], t1 = T[k ? at - 1 : 0];
       int m = kNone;
-      if (i && j && k) m = max(m, T[at - sB - sC - 1] + a.sub[4 * x + y] + a.sub[4 * x + z] + a.sub[4 * y + z]);
-      if (i && j) m = max(m, T[at - sB - sC] + a.sub[4 * x + y] + g2);
-      if (i && k) m = max(m, T[at - sB - 1] + a.sub[4 * x + z] + g2);
-      if (j && k) m = max(m, T[at - sC - 1] + a.sub[4 * y + z] + g2);
-      if (i) m = max(m, T[at - sB] + g2);
-      if (j) m = max(m, T[at - sC] + g2);
-      if (k) m = max(m, T[at - 1] + g2);
+      m = max(m, ijk ? t7 + sxy + sxz + syz : kNone);
+      m = max(m, ij ? t6 + sxy + g2 : kNone);
+      m = max(m, ik ? t5 + sxz + g2 : kNone);
+      m = max(m, jk ? t4 + syz + g2 : kNone);
+      m = max(m, i ? t3 + g2 : kNone);
+      m = max(m, j ? t2 + g2 : kNone);
+      m = max(m, k ? t1 + g2 : kNone);
       T[at] = m;
     }
     __syncthreads();
   }
-  if (lane != 0) return;
-  a.score[leaf] = T[A * sB + B * sC + C];
+  if (tid >= 64) return;
+  if (tid == 0) a.score[leaf] = T[A * sB + B * sC + C];
+  // Lane m < 7 tests move m: which sequences it consumes (bits 0, 1, 2).
+  const int move = tid < 7 ? (0x4216537 >> (4 * tid)) & 7 : 0;  // ijk, ij, ik, jk, i, j, k
+  const int ui = move & 1, uj = (move >> 1) & 1, uk = (move >> 2) & 1;
+  const int back = ui * sB + uj * sC + uk;
   uint8_t* out = a.cols + d.out;
   int i = A, j = B, k = C, n = 0;
   while (i || j || k) {
     const int at = i * sB + j * sC + k;
-    const int v = T[at];
-    const int x = i ? res[0][i - 1] : 0, y = j ? res[1][j - 1] : 0, z = k ? res[2][k - 1] : 0;
-    int di = 0, dj = 0, dk = 0;
-    if (i && j && k && T[at - sB - sC - 1] + a.sub[4 * x + y] + a.sub[4 * x + z] + a.sub[4 * y + z] == v) {
-      di = dj = dk = 1;
-    } else if (i && j && T[at - sB - sC] + a.sub[4 * x + y] + g2 == v) {
-      di = dj = 1;
-    } else if (i && k && T[at - sB - 1] + a.sub[4 * x + z] + g2 == v) {
-      di = dk = 1;
-    } else if (j && k && T[at - sC - 1] + a.sub[4 * y + z] + g2 == v) {
-      dj = dk = 1;
-    } else if (i && T[at - sB] + g2 == v) {
-      di = 1;
-    } else if (j && T[at - sC] + g2 == v) {
-      dj = 1;
-    } else {
-      dk = 1;  // the only move left (k > 0 here, or the table is inconsistent)
-      if (!k) break;
-    }
-    out[3 * n] = (uint8_t)(di ? x : 4);
-    out[3 * n + 1] = (uint8_t)(dj ? y : 4);
-    out[3 * n + 2] = (uint8_t)(dk ? z : 4);
+    const int x = rx[i - 1], y = ry[j - 1], z = rz[k - 1];
+    const bool legal = move && (!ui || i) && (!uj || j) && (!uk || k);
+    const int v = T[at], p = T[legal ? at - back : 0];
+    // A pair of residues scores its substitution, a residue and a gap the gap.
+    const int s = (ui && uj ? sub[4 * x + y] : 0) + (ui && uk ? sub[4 * x + z] : 0) + (uj && uk ? sub[4 * y + z] : 0) +
+                  (ui + uj + uk == 3 ? 0 : g2);
+    const uint64_t hits = __builtin_amdgcn_ballot_w64(legal && p + s == v);
+    // (The last move is taken when no earlier one fits, as the only one left.)
+    const int which = hits ? __builtin_ctzll(hits) : 6;
+    const int w = (0x4216537 >> (4 * which)) & 7;
+    if (which == 6 && !k) break;  // an inconsistent table
+    const int di = w & 1, dj = (w >> 1) & 1, dk = (w >> 2) & 1;
+    if (tid < 3) out[3 * n + tid] = (uint8_t)(tid == 0 ? (di ? x : 4) : tid == 1 ? (dj ? y : 4) : (dk ? z : 4));
     ++n;
     i -= di;
     j -= dj;
     k -= dk;
   }
-  a.ncols[leaf] = (uint32_t)n;
+  if (tid == 0) a.ncols[leaf] = (uint32_t)n;
 }
 
 // Gather: one thread per output word packs 16 residues of one output
@@ -316,7 +333,7 @@ hipError_t launch_split(const int* planes, const SplitDesc* boxes, uint32_t n, c
 
 hipError_t launch_leaf(const LeafArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_leaf, dim3(a.n), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(k_leaf, dim3(a.n), dim3(kLeafThreads), 0, s, a);
   return hipGetLastError();
 }
 
