@@ -284,13 +284,10 @@ def align(triplet, sc: Scoring | None = None, stream=None):
 def align_batch(triplets, sc: Scoring | None = None, stream=None) -> list:
     """Optimal global alignments of many triplets, computed together:
     a list of ((row0, row1, row2), score)."""
-    keep: list = []
     n = len(triplets)
-    arr = (Triplet * max(n, 1))()
-    caps = []
-    for q, t in enumerate(triplets):
-        arr[q] = _triplet(t, keep)
-        caps.append(int(arr[q].len[0]) + int(arr[q].len[1]) + int(arr[q].len[2]))
+    arr, keep = triplet_array([(t[0], t[1], t[2]) for t in triplets])
+    view = np.frombuffer(arr, dtype=_TRIPLET_FIELDS, count=n)
+    caps = view["len"].astype(np.int64).sum(axis=1).tolist()
     buf = ctypes.create_string_buffer(max(1, 3 * sum(caps)))
     ncols = np.zeros(max(n, 1), dtype=np.uint32)
     scores = np.zeros(max(n, 1), dtype=np.int32)
@@ -298,17 +295,19 @@ def align_batch(triplets, sc: Scoring | None = None, stream=None) -> list:
                                     ncols.ctypes.data_as(ctypes.POINTER(ctypes.c_uint32)),
                                     scores.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
                                     _stream_ptr(stream)))
-    raw = buf.raw
-    out, base = [], 0
-    for q in range(n):
-        c, k = caps[q], int(ncols[q])
-        out.append((tuple(raw[base + a * c: base + a * c + k].decode() for a in range(3)),
-                    int(scores[q])))
-        base += 3 * c
+    text = buf.raw.decode("latin-1")  # (one character per byte, also in the unused tails)
+    out, r0 = [], 0
+    for c, k, sco in zip(caps, ncols.tolist(), scores.tolist()):
+        r1, r2 = r0 + c, r0 + 2 * c
+        out.append(((text[r0:r0 + k], text[r1:r1 + k], text[r2:r2 + k]), sco))
+        r0 += 3 * c
     return out
 
 
 _ASCII = np.frombuffer(b"ACGT", dtype=np.uint8)
+_TRIPLET_FIELDS = np.dtype({"names": ["seq", "len"], "formats": [("<u8", 3), ("<u4", 3)],
+                            "offsets": [Triplet.seq.offset, Triplet.len.offset],
+                            "itemsize": ctypes.sizeof(Triplet)})
 
 
 def triplet_array(triplets):
@@ -321,21 +320,20 @@ def triplet_array(triplets):
     if n == 0:
         return arr, None
     seqs = [s for t in triplets for s in t]
-    if all(isinstance(s, np.ndarray) for s in seqs):
+    kinds = set(map(type, seqs))
+    if kinds == {np.ndarray}:
         lens = np.fromiter((s.size for s in seqs), dtype=np.int64, count=3 * n)
         codes = np.concatenate(seqs).astype(np.uint8, copy=False) if lens.sum() else np.zeros(0, np.uint8)
         data = _ASCII[codes] if codes.size else codes
     else:
-        parts = [_as_bytes(s) for s in seqs]
-        lens = np.fromiter((len(b) for b in parts), dtype=np.int64, count=3 * n)
+        parts = seqs if kinds == {bytes} else [_as_bytes(s) for s in seqs]
+        lens = np.fromiter(map(len, parts), dtype=np.int64, count=3 * n)
         data = np.frombuffer(b"".join(parts), dtype=np.uint8)
     buf = np.empty(max(int(lens.sum()), 1), dtype=np.uint8)
     buf[:data.size] = data
     starts = np.zeros(3 * n, dtype=np.int64)
     np.cumsum(lens[:-1], out=starts[1:])
-    view = np.frombuffer(arr, dtype=np.dtype({"names": ["seq", "len"], "formats": [("<u8", 3), ("<u4", 3)],
-                                               "offsets": [Triplet.seq.offset, Triplet.len.offset],
-                                               "itemsize": ctypes.sizeof(Triplet)}), count=n)
+    view = np.frombuffer(arr, dtype=_TRIPLET_FIELDS, count=n)
     view["seq"] = (buf.ctypes.data + starts).reshape(n, 3)
     view["len"] = lens.reshape(n, 3)
     return arr, buf
