@@ -122,8 +122,11 @@ struct PkFaces {
     top_from = io.has_top ? 0 : INT32_MAX;
     left_from = io.has_left ? 0 : INT32_MAX;
     have_base = !io.has_top && !io.has_left;
-    // The corners of step 0 lie before slice 0 (lane 0's comes with the corner
-    // face, or lies outside).
+  }
+
+  // Before the first put, by the wave that stages: the corners of step 0 lie
+  // before slice 0 (lane 0's comes with the corner face, or lies outside).
+  __device__ __forceinline__ void begin() {
     if (lane < kGK) S.C[0][lane] = (int)(kSentP * 0x10001u);
   }
 
@@ -306,7 +309,10 @@ __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& 
   int fin = 0, ffl = 0;
   bool gave_up = false;
   PkFaces<Lds> f(S, io, n0, off2);  // (unused, and dropped, without SELF)
-  if (SELF) f.load(0);
+  if (SELF) {
+    f.begin();
+    f.load(0);
+  }
   uint32_t zero2 = off2;  // stored value of M' = 0 (set at step 0, once the base is known)
   auto run_chunk = [&](int c, auto capture) __attribute__((always_inline)) {
     constexpr bool CAP = decltype(capture)::value;
@@ -557,6 +563,7 @@ __device__ void pk_panel_memory(PkPanelLds<kRing>& S, int n0, const PkPanelIO& i
   const int lane = threadIdx.x & 63;
   const int stepsp = (n0 + 1 + kSkew + kChunk - 1) / kChunk * kChunk;
   PkFaces<PkPanelLds<kRing>> f(S, io, n0, off2);
+  f.begin();
   int staged = 0, flushed = 0;
   uint64_t stall_since = 0;
   bool gave_up = false;
