@@ -701,11 +701,29 @@ bool packed_self_layout(const uint32_t* lens, const uint64_t* off, const trioseq
   return true;
 }
 
+// The axes of a triplet among others: the fewest panel steps (whole chunks of
+// them, and about 12 for a panel's start). 8192 triplets of 100-400 residues:
+// 0.862 of the executed cells are theirs, 0.846 with the longest axis swept.
+static AxisChoice choose_axes_panels(const uint32_t len[3]) {
+  AxisChoice best{{0, 1, 2}};
+  uint64_t best_cost = UINT64_MAX;
+  for (const auto& p : kPerms) {
+    if (len[p[0]] > (uint32_t)kMaxSweepLen) continue;
+    const uint64_t cost = (uint64_t)(len[p[1]] / kPkPanel + 1) * (len[p[2]] / kPkPanel + 1) *
+                          ((len[p[0]] + 1 + kSkew + kChunk - 1) / kChunk * kChunk + 12);
+    if (cost < best_cost) {
+      best_cost = cost;
+      std::memcpy(best.perm, p, 3);
+    }
+  }
+  return best;
+}
+
 bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L) {
   std::vector<size_t> split(n);
   std::iota(split.begin(), split.end(), 0);
   std::vector<AxisChoice> ax(n);
-  for (size_t t = 0; t < n; ++t) ax[t] = choose_axes_wide(lens + 3 * t);
+  for (size_t t = 0; t < n; ++t) ax[t] = choose_axes_panels(lens + 3 * t);
 
   // Panel pairs: neighbours by size, or each triplet's own two halves (global
   // and local scoring), whichever the times above make shorter.
