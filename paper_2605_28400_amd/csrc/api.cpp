@@ -1025,7 +1025,8 @@ static hipError_t cached_occupancy(const Layout& L, int device, int* w) {
                           std::to_string(L.ks.group) + "/" + std::to_string(L.ks.xch) + "/" +
                           std::to_string((int)L.packed + 2 * (int)L.pk_self) + "/" +
                           std::to_string(L.modes) + "/" + std::to_string(L.kind) + "/" +
-                          std::to_string((int)L.planes) + "/" + std::to_string(shift_lds_bytes(L.lds_n0));
+                          std::to_string((int)L.planes) + "/" + std::to_string(shift_lds_bytes(L.lds_n0)) + "/" +
+                          std::to_string(pk_waves_per_simd(L.kind, L.planes, L.pk_self, L.lds_n0, L.jobs.size()));
   {
     std::lock_guard<std::mutex> lk(g_occ_mu);
     for (const auto& kv : g_occ)
@@ -1034,7 +1035,7 @@ static hipError_t cached_occupancy(const Layout& L, int device, int* w) {
         return hipSuccess;
       }
   }
-  hipError_t e = L.modes == kModePkPanel ? panel_pk_occupancy(L.kind, L.planes, L.pk_self, L.lds_n0, w)
+  hipError_t e = L.modes == kModePkPanel ? panel_pk_occupancy(L.kind, L.planes, L.pk_self, L.lds_n0, L.jobs.size(), w)
                  : L.packed ? sweep_pk_occupancy(L.ks, L.kind, L.lds_n0, w)
                          : sweep_occupancy(L.ks, L.modes, L.kind, L.planes, L.lds_n0, w);
   if (e == hipSuccess && L.modes == 2 && L.ks.group > 1) {

@@ -192,7 +192,19 @@ inline uint64_t pk_pair_ints(uint32_t n0, uint64_t PJ, uint64_t PK) {
 // jobs are counted for pairs that wait for them.
 hipError_t launch_panel_pk(int kind, bool self, const SweepArgs& a, uint32_t off, uint32_t kc, bool count, int grid,
                            hipStream_t s);
-hipError_t panel_pk_occupancy(int kind, bool plane, bool self, uint32_t lds_n0, int* blocks_per_cu);
+hipError_t panel_pk_occupancy(int kind, bool plane, bool self, uint32_t lds_n0, uint64_t njobs, int* blocks_per_cu);
+
+// Waves on a SIMD of single-wave panel workgroups. A third (168 registers; the
+// few spilled values lie outside the step loop) covers the starts of panels,
+// which weigh most where panels are short, but only where a launch has panels
+// enough to keep 3072 waves in step. Two / three waves, global: 8192 triplets
+// of 100-400 residues 26.00 / 25.15 ms, 20000 of 40-150 4.74 / 4.58 ms, 2000 of
+// 100-400 (70k panels) 6.45 / 6.33 ms; 500 (17k panels) 1.80 / 1.82 ms; 400 of
+// 500-800 16.25 / 16.38 ms, 60 of 1200-1600 24.1 / 25.3 ms. The other kinds and
+// the plane form spill within the loop (local batch 33.6 / 36.2 ms).
+inline int pk_waves_per_simd(int kind, bool plane, bool self, uint32_t lds_n0, uint64_t njobs) {
+  return kind == kGlobal && !plane && self && lds_n0 <= 512 && njobs >= 32768 ? 3 : 2;
+}
 
 // Traceback (traceback.hip). A split box: the forward and reversed planes
 // (ints from the plane buffer base), rows x cols entries each, reduced in

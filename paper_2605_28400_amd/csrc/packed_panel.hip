@@ -233,7 +233,7 @@ __device__ __forceinline__ void lds_put4(int* p, uint32_t a, uint32_t b, uint32_
 // moves its faces itself, a chunk of steps at a time (loads of the next chunk
 // issued at step kSelfStageAt of this one).
 constexpr int kSelfStageAt = 5;
-template <int KIND, bool PLANE, bool SELF, class Lds>
+template <int KIND, bool PLANE, bool SELF, int WPS, class Lds>
 __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& sc,
                                  const uint32_t* __restrict__ words, const TripletDesc& ta, const TripletDesc& tb,
                                  int n0, int pj, int pk, const PkPanelIO& io, uint16_t* capt, uint32_t off2,
@@ -519,6 +519,8 @@ __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& 
 #pragma unroll
       for (int cc = 0; cc < RK; ++cc) Tp[cc] = T[cc];
       to += t_str, co += c_str, lo += l_str, bo += b_str, ro += r_str;
+      // (Formed step by step: all steps' addresses at once do not fit.)
+      if (WPS == 3) asm volatile("" : "+v"(to), "+v"(co), "+v"(lo), "+v"(bo), "+v"(ro));
     }
     if (SELF) {
       __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -606,8 +608,8 @@ __device__ void pk_panel_memory(PkPanelLds<kRing>& S, int n0, const PkPanelIO& i
 // workgroup and every wait ends. Pairs that reuse the face buffers of earlier
 // ones (see pair_panel_layout) also wait until those are over; all their jobs
 // were popped before.
-template <int KIND, bool PLANE, bool SELF>
-__global__ void __launch_bounds__(SELF ? 64 : 128) __attribute__((amdgpu_waves_per_eu(2)))
+template <int KIND, bool PLANE, bool SELF, int WPS>
+__global__ void __launch_bounds__(SELF ? 64 : 128) __attribute__((amdgpu_waves_per_eu(WPS)))
 k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc, uint32_t count) {
   constexpr int H = kPkPanel, W = kPkPanel;
   typedef PkPanelLds<SELF ? kChunk : kRing> Lds;
@@ -675,10 +677,10 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc, uint32_t count) {
     io.wait_ticks = a.wait_ticks;
     uint32_t best = 0;
     if constexpr (SELF) {
-      pk_panel_compute<KIND, PLANE, true>(S, selw, a.sc, a.words, ta, tb, n0, pj, pk, io, capt, off2, best, kc);
+      pk_panel_compute<KIND, PLANE, true, WPS>(S, selw, a.sc, a.words, ta, tb, n0, pj, pk, io, capt, off2, best, kc);
     } else {
       if (wave == 0)
-        pk_panel_compute<KIND, PLANE, false>(S, selw, a.sc, a.words, ta, tb, n0, pj, pk, io, capt, off2, best, kc);
+        pk_panel_compute<KIND, PLANE, false, WPS>(S, selw, a.sc, a.words, ta, tb, n0, pj, pk, io, capt, off2, best, kc);
       else
         pk_panel_memory(S, n0, io, off2);
     }
@@ -747,10 +749,12 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc, uint32_t count) {
   }
 }
 
-#define TRIOSEQ_PKP(X)                                                                  \
-  X(0, true, false) X(0, true, true) X(0, false, false) X(0, false, true)               \
-  X(1, false, false) X(1, false, true)                                                  \
-  X(2, true, false) X(2, true, true) X(2, false, false) X(2, false, true)
+// Kind, planes, single waves, waves per SIMD (see pk_waves_per_simd).
+#define TRIOSEQ_PKP(X)                                                                           \
+  X(0, true, false, 2) X(0, true, true, 2) X(0, false, false, 2) X(0, false, true, 2)            \
+  X(0, false, true, 3)                                                                           \
+  X(1, false, false, 2) X(1, false, true, 2)                                                     \
+  X(2, true, false, 2) X(2, true, true, 2) X(2, false, false, 2) X(2, false, true, 2)
 
 }  // namespace
 
@@ -758,21 +762,23 @@ hipError_t launch_panel_pk(int kind, bool self, const SweepArgs& a, uint32_t off
                            hipStream_t s) {
   const size_t lds = (size_t)(a.lds_n0 + 64) * 4;
   const bool plane = a.plane != nullptr;
-#define X(k, p, f)                                                                           \
-  if (kind == k && plane == p && self == f) {                                                \
-    hipLaunchKernelGGL((k_panel_pk<k, p, f>), dim3(grid), dim3(f ? 64 : 128), lds, s, a, off, kc,   \
-                       count ? 1u : 0u);                                                     \
-    return hipGetLastError();                                                                \
+  const int wps = pk_waves_per_simd(kind, plane, self, a.lds_n0, a.njobs);
+#define X(k, p, f, w)                                                                                \
+  if (kind == k && plane == p && self == f && wps == w) {                                            \
+    hipLaunchKernelGGL((k_panel_pk<k, p, f, w>), dim3(grid), dim3(f ? 64 : 128), lds, s, a, off, kc, \
+                       count ? 1u : 0u);                                                             \
+    return hipGetLastError();                                                                        \
   }
   TRIOSEQ_PKP(X)
 #undef X
   return hipErrorInvalidValue;
 }
 
-hipError_t panel_pk_occupancy(int kind, bool plane, bool self, uint32_t lds_n0, int* blocks_per_cu) {
-#define X(k, p, f)                                                                                       \
-  if (kind == k && plane == p && self == f)                                                              \
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_panel_pk<k, p, f>, f ? 64 : 128, \
+hipError_t panel_pk_occupancy(int kind, bool plane, bool self, uint32_t lds_n0, uint64_t njobs, int* blocks_per_cu) {
+  const int wps = pk_waves_per_simd(kind, plane, self, lds_n0, njobs);
+#define X(k, p, f, w)                                                                                        \
+  if (kind == k && plane == p && self == f && wps == w)                                                      \
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_panel_pk<k, p, f, w>, f ? 64 : 128, \
                                                         (size_t)(lds_n0 + 64) * 4);
   TRIOSEQ_PKP(X)
 #undef X

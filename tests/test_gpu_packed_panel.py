@@ -123,6 +123,22 @@ def test_batches_equal_oracle(torch_cuda, kind, name):
                 assert bad.size == 0, [(int(q), int(got[q]), int(want[q])) for q in bad[:5]]
 
 
+# (With inner axes 40 x 33 the axis of 33 is swept, with 63 x 63 the longest.)
+@pytest.mark.parametrize("longest,inner,grid", [(512, (40, 33), 3072), (513, (40, 33), 3072),
+                                                (512, (63, 63), 3072), (513, (63, 63), 2048)])
+def test_many_short_panels(torch_cuda, longest, inner, grid):
+    """Three waves a SIMD from 32768 panel jobs on, for sweeps up to 512."""
+    rng = np.random.default_rng(85)
+    some = [tuple(synth.uniform_seq(rng, int(m)) for m in rng.integers(32, 64, 3)) for _ in range(62)]
+    some += [tuple(synth.uniform_seq(rng, m) for m in n) for n in ((longest, *inner), (63, 32, 63))]
+    want = want_scores(some, (1, -1, -2), ts.GLOBAL)
+    outs, info = run(torch_cuda, [some[q % 64] for q in range(16640)], ts.scoring(), use_graph=True)
+    cus = torch_cuda.cuda.get_device_properties(0).multi_processor_count
+    assert info["packed"] == 1 and info["grid"] == grid * cus // 256
+    for got in outs:
+        assert np.array_equal(got, np.tile(want, 260))
+
+
 def test_lone_semi_global(torch_cuda):
     rng = np.random.default_rng(83)
     for n in LONE:
