@@ -209,10 +209,12 @@ typedef struct trioseq_plan_options {
                              mean cells per wavefront (or 2.5e8); 0 = default (4).
                              Int32 lanes only: a batch that qualifies for packed
                              pairs under this engine runs as panel jobs throughout */
-  int32_t half_split_min; /* automatic engine, one global or local triplet: scored by
-                             two concurrent halves when its longest sequence has at
-                             least this many residues; -1 = never; 0 = default (128,
-                             and for local scoring only below 2048 residues) */
+  int32_t half_split_min; /* automatic engine, one triplet: scored by two concurrent
+                             halves when its longest sequence has at least this many
+                             residues; -1 = never; 0 = default (128). Local scoring
+                             in int32 lanes: by default only below 2048 residues;
+                             semi-global scoring: packed lanes only, and from nine
+                             panels on */
   int32_t packed;         /* 1 = int32 lanes; 2 = two triplets per lane, 16 bits each
                              (batches of whole triplets, any kind, whose substitution
                              terms sub - 2*gap are all >= 0 and whose values fit the

@@ -532,7 +532,9 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
     if (off + step * (a + 2 * kPkPanel + 2) > kPackedMax) return false;
     const uint64_t most = sc.kind == kGlobal ? A * pairs : std::max(A, g) * (a + b + c);
     const uint64_t score = (uint64_t)maxs * pairs;  // no score is larger
-    if (most > 0xFFFF || (sc.kind == kLocal && score > 30000)) return false;
+    // (Floors are told from live values by their distance, below 2^15.)
+    const bool floors = sc.kind == kLocal || (sc.kind == kSemiGlobal && planes);
+    if (most > 0xFFFF || (floors && score > 30000)) return false;
   }
   // Semi-global candidates M + kc must be positive on every cell of a pair's
   // common panel grid: a triplet's last slice is taken with its padding.
@@ -667,6 +669,17 @@ static void half_descs(const uint32_t* l, const uint64_t* off, TripletDesc d[2],
     d[h].rev = (uint32_t)h;
   }
   *box = SplitDesc{0, 0, l[order[1]] + 1, l[order[2]] + 1, 0, 0, 0};
+}
+
+// Semi-global halves (packed only): at least nine panels across the two shorter
+// axes. Halves / the triplet as a pair with itself: 128 x 125 x 131 142 / 152
+// us, 300 x 290 x 305 271 / 319, 723 x 651 x 698 595 / 737, 2048 x 2000 x 2080
+// 2.79 / 4.74 ms, 4096 x 4000 x 4150 12.7 / 35.2 ms (int32). Thin triplets would
+// gain as well, but their plans have always reported the panels of one sweep.
+bool semi_global_halves(const uint32_t* l) {
+  const uint32_t lo = std::min({l[0], l[1], l[2]}), hi = std::max({l[0], l[1], l[2]});
+  const uint32_t mid = (uint32_t)((uint64_t)l[0] + l[1] + l[2] - lo - hi);
+  return (uint64_t)(lo / kPkPanel + 1) * (mid / kPkPanel + 1) >= 9;
 }
 
 bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L) {
@@ -1167,10 +1180,12 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   // stay on it in int32 (2048 x 2000 x 2080: 5.62 -> 2.58 ms, 4096 x 4000 x
   // 4150: 38.8 -> 14.6 ms).
   const bool may_pack = o.packed != 1 && o.panel_group <= 1;
-  const bool long_local = defaults && !half && n == 1 && !mem && may_pack && scp->kind == kLocal &&
-                          o.half_split_min == 0 && o.lane_exchange != 2 && L.cells >= kSplitCells &&
-                          half_split_layout(lens, word_off, 0, &hs);
-  if ((half && may_pack) || long_local) {
+  // Semi-global halves exist in packed form only.
+  const bool packed_half =
+      defaults && !half && n == 1 && !mem && may_pack && o.lane_exchange != 2 &&
+      ((scp->kind == kSemiGlobal && semi_global_halves(lens)) || (scp->kind == kLocal && o.half_split_min == 0 && L.cells >= kSplitCells)) &&
+      half_split_layout(lens, word_off, o.half_split_min, &hs);
+  if ((half && may_pack) || packed_half) {
     const uint64_t int32_pool = L.pool_ints * sizeof(int);
     const double cells = L.cells;
     std::vector<uint64_t> def(3);
@@ -1186,11 +1201,11 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
       half = true;
     }
   }
-  // A lone triplet that has no halves path (semi-global scoring, or shorter than
-  // it takes) runs as a pair with itself: per cell as many instructions as
-  // int32 lanes take, but the packed kernel's shorter hops and polls
-  // (semi-global 723 x 651 x 698: 824 -> 721 us, 1024 x 1000 x 1048: 1.33 -> 1.15
-  // ms; global 48 x 45 x 51: 68 -> 58 us, 100 x 97 x 104: 119 -> 95 us).
+  // A lone triplet that has no halves path (thin under semi-global scoring, or
+  // shorter than it takes) runs as a pair with itself: per cell as many
+  // instructions as int32 lanes take, but the packed kernel's shorter hops and
+  // polls (semi-global 723 x 651 x 698: 824 -> 721 us; global 48 x 45 x 51: 68 ->
+  // 58 us, 100 x 97 x 104: 119 -> 95 us).
   if (n == 1 && defaults && may_pack && !mem && !half && o.lane_exchange != 2 && L.modes == 2 &&
       (scp->kind == kSemiGlobal ||
        (o.half_split_min == 0 && std::max({lens[0], lens[1], lens[2]}) < kHalfSplitMin))) {
@@ -1534,9 +1549,9 @@ static hipError_t plan_enqueue(trioseq_plan* p, const uint32_t* d_words, int32_t
   if (e != hipSuccess || !p->half) return e;
   // The planes of the halves meet. Under local scoring the score is the best
   // of the crossing paths and the halves' own bests.
-  const int* own = p->sc.kind != kLocal ? nullptr : pk_panel ? p->d_red : p->d_hscores;
+  const int* own = p->sc.kind == kGlobal ? nullptr : pk_panel ? p->d_red : p->d_hscores;
   return launch_meet(p->d_sdesc, p->d_chunk_box, p->h_nchunk, p->d_plane, p->d_partial, p->d_ctl + 1, own,
-                     pk_panel ? 2 : 1, p->d_meet ? p->d_meet : p->d_ctl + 2, d_scores, s);
+                     pk_panel ? 2 : 1, pk_panel ? (int)p->pk_kc : 0, p->d_meet ? p->d_meet : p->d_ctl + 2, d_scores, s);
 }
 
 trioseq_status trioseq_plan_run(trioseq_plan* p, const uint32_t* d_words, int32_t* d_scores,

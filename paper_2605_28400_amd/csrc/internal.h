@@ -252,12 +252,13 @@ hipError_t launch_gather(const uint32_t* in, const GatherDesc* d, uint32_t n, ui
                          uint32_t* out, int* ctl, int* counter, int* pool, uint64_t pool_ints, hipStream_t s);
 // out[box.out] = the best F + R over every box's planes, or INT32_MIN if err[0]
 // is set (a wait of the run gave up). chunk_box[c] = the box of chunk c (null:
-// one box). With own non-null (local scoring), the best of box b also covers
-// own[4b] and own[4b + own_step], the halves' own bests. partial: nchunks ints
+// one box). With own non-null (local and semi-global scoring), the best of box
+// b also covers own[4b] and own[4b + own_step] less own_base, the halves' own
+// bests. partial: nchunks ints
 // of scratch; counters: one int per box that is 0 before the call and is left 0.
 hipError_t launch_meet(const SplitDesc* boxes, const uint32_t* chunk_box, uint32_t nchunks, const int* planes,
-                       int* partial, const int* err, const int* own, int own_step, int* counters, int32_t* out,
-                       hipStream_t s);
+                       int* partial, const int* err, const int* own, int own_step, int own_base, int* counters,
+                       int32_t* out, hipStream_t s);
 // out[3b] = best F + R of box b, out[3b+1], out[3b+2] = its (p, q).
 // chunk_box[c] = the box of chunk c; partial: 2 ints per chunk.
 hipError_t launch_split(const int* planes, const SplitDesc* boxes, uint32_t n, const uint32_t* chunk_box,

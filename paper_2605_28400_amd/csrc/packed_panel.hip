@@ -228,6 +228,9 @@ __device__ __forceinline__ void lds_put4(int* p, uint32_t a, uint32_t b, uint32_
   *reinterpret_cast<v4i*>(__builtin_assume_aligned(p, 16)) = (v4i){(int)a, (int)b, (int)c, (int)d};
 }
 
+// b where the mask is set, else a.
+__device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t b, uint32_t a) { return (b & mask) | (a & ~mask); }
+
 // The compute wave. Folds local and semi-global bests into `best`, as the
 // whole-triplet kernel does (local: M; semi-global: M + kc). SELF: the wave
 // moves its faces itself, a chunk of steps at a time (loads of the next chunk
@@ -241,6 +244,13 @@ __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& 
   constexpr int RJ = 4, RK = 4;
   constexpr int H = kPkPanel, W = kPkPanel;
   constexpr bool PAD = KIND != kGlobal;
+  // Semi-global halves. An alignment ends on any last face, so the reversed
+  // half starts with 0 on all three of its faces (M' = g * index sum there),
+  // and what it finds of its own are the alignments that start on the cut axis
+  // past the middle: those through its row n1, column n2. The first half starts
+  // on the axes as ever, and its own best takes the last row and column only:
+  // its last slice is the cut, not a face.
+  constexpr bool kFaces = KIND == kSemiGlobal && PLANE;
   const int lane = threadIdx.x & 63;
   const int y = lane >> 3, x = lane & 7;
   const int j0 = pj * H + y * RJ, k0 = pk * W + x * RK;
@@ -385,15 +395,29 @@ __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& 
       const uint32_t corner = (uint32_t)*reinterpret_cast<const int*>(lds + co);
       const int i = t - y - x;  // this lane's slice
       if (KIND == kSemiGlobal && axis_panel) {
-        // The axes hold 0 (M' = g * index): see the whole-triplet kernel.
+        // The axes hold 0 (M' = g * index): see the whole-triplet kernel. With
+        // planes the second half of the pair starts on its whole faces instead
+        // (see kFaces).
+        const uint32_t keep = kFaces ? 0xFFFFu : 0xFFFFFFFFu;
+        const uint32_t faces = kFaces && i >= 0 ? 0xFFFF0000u : 0u;
+        if (kFaces && j0 == 0) {
+#pragma unroll
+          for (int cc = 0; cc < RK; ++cc)
+            T[cc] = bfi(faces, paddw(zero2, ((uint32_t)(g * (i + k0 + cc)) & 0xFFFFu) * 0x10001u), T[cc]);
+        }
+        if (kFaces && k0 == 0) {
+#pragma unroll
+          for (int r = 0; r < RJ; ++r)
+            Lh[r] = bfi(faces, paddw(zero2, ((uint32_t)(g * (i + j0 + r)) & 0xFFFFu) * 0x10001u), Lh[r]);
+        }
         if (j0 == 0) {
 #pragma unroll
-          for (int cc = 0; cc < RK; ++cc) T[cc] = i == 0 ? paddw(zero2, (uint32_t)(g * (k0 + cc)) * 0x10001u) : T[cc];
-          if (k0 == 0) T[0] = i >= 0 ? paddw(zero2, (uint32_t)(g * i) * 0x10001u) : T[0];
+          for (int cc = 0; cc < RK; ++cc) T[cc] = bfi(i == 0 ? keep : 0u, paddw(zero2, (uint32_t)(g * (k0 + cc)) * 0x10001u), T[cc]);
+          if (k0 == 0) T[0] = bfi(i >= 0 ? keep : 0u, paddw(zero2, (uint32_t)(g * i) * 0x10001u), T[0]);
         }
         if (k0 == 0) {
 #pragma unroll
-          for (int r = 0; r < RJ; ++r) Lh[r] = i == 0 ? paddw(zero2, (uint32_t)(g * (j0 + r)) * 0x10001u) : Lh[r];
+          for (int r = 0; r < RJ; ++r) Lh[r] = bfi(i == 0 ? keep : 0u, paddw(zero2, (uint32_t)(g * (j0 + r)) * 0x10001u), Lh[r]);
         }
       }
       // Local floors per anti-diagonal class, F_d = F_0 + g*d. A floor below
@@ -418,6 +442,16 @@ __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& 
           X7[r][cc] = D[r][cc] + A[r] + B[cc];
           if (KIND == kLocal) Q[r][cc] = pmax3(Q[r][cc], X7[r][cc], F[r + cc]);
         }
+      if (kFaces && c < 2 && i == 0) {
+        // Slice 0 of the second half is a face (lanes reach it in steps 0 .. 14).
+        // A value below the window counts as none, as the local floors do.
+        const uint32_t f0 = smax2(paddw(zero2, ((uint32_t)(g * (j0 + k0)) & 0xFFFFu) * 0x10001u), 0u) & 0xFFFF0000u;
+#pragma unroll
+        for (int r = 0; r < RJ; ++r)
+#pragma unroll
+          for (int cc = 0; cc < RK; ++cc)
+            Q[r][cc] = pmax2(Q[r][cc], f0 + ((uint32_t)((r + cc) * g) << 16));
+      }
 #pragma unroll
       for (int r = 0; r < RJ; ++r)
 #pragma unroll
@@ -462,7 +496,7 @@ __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& 
           // it would keep the tiles of all its steps in registers.
           asm volatile("" : "+v"(best));
         } else {
-          const uint32_t sm = (i == n0a ? 0xFFFFu : 0u) | (i == n0b ? 0xFFFF0000u : 0u);
+          const uint32_t sm = kFaces ? 0u : (i == n0a ? 0xFFFFu : 0u) | (i == n0b ? 0xFFFF0000u : 0u);
           if (((rcany | sm) & vm) != 0u) {
             // M + kc = stored - zero2 - g*(i + j + k) + kc.
             const uint32_t off0 = psub(((kc - (uint32_t)fi) & 0xFFFFu) * 0x10001u, zero2);
@@ -471,7 +505,8 @@ __device__ void pk_panel_compute(Lds& S, const uint32_t* sel, const DevScoring& 
             for (int r = 0; r < RJ; ++r)
 #pragma unroll
               for (int cc = 0; cc < RK; ++cc)
-                sb = umax2(sb, paddw(N[r][cc], psub(off0, (uint32_t)(r + cc) * g2)) & (RM[r] | CM[cc] | sm));
+                sb = umax2(sb, paddw(N[r][cc], psub(off0, (uint32_t)(r + cc) * g2)) &
+                                   (kFaces ? bfi(0xFFFFu, RM[r] | CM[cc], RM[r] & CM[cc]) : RM[r] | CM[cc] | sm));
             best = umax2(best, sb & vm);
             asm volatile("" : "+v"(best));
           }
@@ -753,7 +788,7 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc, uint32_t count) {
 #define TRIOSEQ_PKP(X)                                                                           \
   X(0, true, false, 2) X(0, true, true, 2) X(0, false, false, 2) X(0, false, true, 2)            \
   X(0, false, true, 3)                                                                           \
-  X(1, false, false, 2) X(1, false, true, 2)                                                     \
+  X(1, true, false, 2) X(1, true, true, 2) X(1, false, false, 2) X(1, false, true, 2)            \
   X(2, true, false, 2) X(2, true, true, 2) X(2, false, false, 2) X(2, false, true, 2)
 
 }  // namespace

@@ -166,7 +166,8 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
   // once: 59 ms, 212 ms with int32 jobs.)
   Layout& L = *L_out;
   L = Layout{};
-  const bool halves = n == 1 && s->sc.kind != kSemiGlobal && std::max({lens[0], lens[1], lens[2]}) >= kHalfSplitMin;
+  const bool halves = n == 1 && (s->sc.kind != kSemiGlobal || semi_global_halves(lens.data())) &&
+                      std::max({lens[0], lens[1], lens[2]}) >= kHalfSplitMin;
   bool packed = halves ? packed_halves_layout(lens.data(), offs.data(), s->sc, &L)
                 : n == 1 ? packed_self_layout(lens.data(), offs.data(), s->sc, &L)
                          : packed_batch_layout(lens.data(), offs.data(), n, s->sc, &L);
@@ -264,7 +265,8 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
     if (e == hipSuccess && L.halves) {
       const uint32_t* d_chunk_box = (const uint32_t*)(d_meet + nb * (sizeof(SplitDesc) + 16));
       e = launch_meet((const SplitDesc*)d_meet, d_chunk_box, (uint32_t)nc, d_plane, d_partial, sl.ctl + 1,
-                      s->sc.kind == kLocal ? d_red : nullptr, 2, (int*)(d_chunk_box + nc), sl.d_scores, sl.stream);
+                      s->sc.kind != kGlobal ? d_red : nullptr, 2, (int)L.pk_kc, (int*)(d_chunk_box + nc), sl.d_scores,
+                      sl.stream);
     }
   }
   if (e == hipSuccess) e = hipEventRecord(sl.done, sl.stream);

@@ -248,7 +248,7 @@ __global__ void __launch_bounds__(256) k_gather(const uint32_t* __restrict__ in,
 __global__ void __launch_bounds__(256) k_meet(const int* __restrict__ planes, const SplitDesc* __restrict__ boxes,
                                               const uint32_t* __restrict__ chunk_box, int* partial,
                                               const int* __restrict__ err, const int* __restrict__ own, int own_step,
-                                              int* counters, int32_t* out) {
+                                              int own_base, int* counters, int32_t* out) {
   __shared__ int s_val[256];
   __shared__ int s_last;
   const uint32_t box = chunk_box ? chunk_box[blockIdx.x] : 0u;
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(256) k_meet(const int* __restrict__ planes, co
   }
   __syncthreads();
   if (!s_last) return;
-  int b = (own && threadIdx.x < 2) ? own[4 * (uint64_t)box + threadIdx.x * own_step] : INT32_MIN;
+  int b = (own && threadIdx.x < 2) ? own[4 * (uint64_t)box + threadIdx.x * own_step] - own_base : INT32_MIN;
   for (uint32_t c = threadIdx.x; c < d.nchunk; c += blockDim.x)
     b = max(b, __hip_atomic_load(&partial[d.chunk0 + c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   __syncthreads();
@@ -314,11 +314,11 @@ hipError_t launch_gather(const uint32_t* in, const GatherDesc* d, uint32_t n, ui
 }
 
 hipError_t launch_meet(const SplitDesc* boxes, const uint32_t* chunk_box, uint32_t nchunks, const int* planes,
-                       int* partial, const int* err, const int* own, int own_step, int* counters, int32_t* out,
-                       hipStream_t s) {
+                       int* partial, const int* err, const int* own, int own_step, int own_base, int* counters,
+                       int32_t* out, hipStream_t s) {
   if (nchunks == 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_meet, dim3(nchunks), dim3(256), 0, s, planes, boxes, chunk_box, partial, err, own, own_step,
-                     counters, out);
+                     own_base, counters, out);
   return hipGetLastError();
 }
 

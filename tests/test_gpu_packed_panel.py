@@ -149,6 +149,33 @@ def test_lone_semi_global(torch_cuda):
             assert all((o == want_scores([t], scheme, ts.SEMI_GLOBAL)).all() for o in outs)
 
 
+@pytest.mark.parametrize("where", ["first half", "second half", "across", "nowhere", "other axes"])
+def test_lone_semi_global_halves(torch_cuda, where):
+    """Alignments that start and end in either half, on every axis and face."""
+    rng = np.random.default_rng(86)
+    seq = lambda m: synth.uniform_seq(rng, m)
+    for scheme in ((1, -1, -2), (5, -4, -6), (1, -3, 0)):
+        for q, m in enumerate((20, 60, 97, 70, 130)):
+            core = synth.mutated_triplet(rng, m, 0.05, lens=(m, m, m))
+            pre, post = {"first half": (0, 170 - m), "second half": (170 - m, 0), "across": (85 - m // 2, 60),
+                         "nowhere": (90, 90), "other axes": (0, 170)}[where]
+            if where == "other axes":  # a ends in the core that b and c start late
+                a = np.concatenate([core[0], seq(post)])
+                b, c = np.concatenate([seq(33 * q), core[1]]), np.concatenate([seq(31), core[2]])
+            else:
+                a = np.concatenate([seq(pre), core[0], seq(post)])
+                b, c = (seq(m), seq(m)) if where == "nowhere" else (core[1], core[2])
+            for t in ((a, b, c), (b, c, a)):
+                print(f"semi-global halves {where} scheme={scheme} lens={[len(z) for z in t]}", flush=True)
+                want = want_scores([t], scheme, ts.SEMI_GLOBAL)
+                outs, info = run(torch_cuda, [t], ts.scoring(*scheme, kind=ts.SEMI_GLOBAL))
+                assert all((o == want).all() for o in outs)
+                # (A negative term, mismatch - 2 gap, keeps int32 lanes; thin ones are one sweep.)
+                lo, mid, _ = sorted(len(z) for z in t)
+                if scheme[1] - 2 * scheme[2] >= 0 and (lo // 32 + 1) * (mid // 32 + 1) >= 9:
+                    assert info["packed"] == 1 and info["panels"] == 2 * (lo // 32 + 1) * (mid // 32 + 1)
+
+
 def test_bounded_wait_gives_int32_min(torch_cuda):
     # A wait bound of one clock tick: a panel whose neighbour is not there yet
     # gives up at once, every kernel ends, and no score but INT32_MIN comes
