@@ -738,8 +738,8 @@ bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, co
   std::vector<AxisChoice> ax(n);
   for (size_t t = 0; t < n; ++t) ax[t] = choose_axes_panels(lens + 3 * t);
 
-  // Panel pairs: neighbours by size, or each triplet's own two halves (global
-  // and local scoring), whichever the times above make shorter.
+  // Panel pairs: neighbours by size, or each triplet's own two halves,
+  // whichever the times above make shorter.
   Layout P, H;
   bool have_p = false, have_h = false;
   {
@@ -763,7 +763,7 @@ bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, co
     }
     have_p = pair_panel_layout(d, sc, false, &P);
   }
-  if (sc.kind != kSemiGlobal) {
+  {
     std::vector<TripletDesc> d;
     uint64_t ints = 0;
     uint32_t chunks = 0;
