@@ -33,11 +33,11 @@ PEAK_INT32_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # semi-global adds maxima over the last slices only (O(n^2) cells).
 OPS_PER_CELL_OF = {"global": 7, "semi-global": 7, "local": 9}
 OPS_PER_CELL = OPS_PER_CELL_OF["global"]
-# Packed pairs (two triplets per lane, one 16-bit half each): 5 packed
-# additions and 3 packed three-input maxima serve two cell updates, so the
-# floor is 4 VALU instructions per cell against the same 39.32e12 lane-
-# instruction peak; local scoring adds a packed floor maximum and a packed
-# running maximum per two cells.
+# Packed pairs (two triplets per lane, one 16-bit half each): 5 additions and
+# 3 packed three-input maxima serve two cell updates, 4 operations per cell
+# against the same 39.32e12 lane-instruction peak (the kernels issue two of the
+# additions as one v_add3_u32); local scoring adds a packed floor maximum and a
+# packed running maximum per two cells.
 OPS_PER_CELL_PACKED_OF = {"global": 4, "semi-global": 4, "local": 5}
 OPS_PER_CELL_PACKED = OPS_PER_CELL_PACKED_OF["global"]
 
@@ -66,6 +66,30 @@ TRAFFIC = {
     ("single_1024x1000x1048", "semi-global", "4x4", "split"): (1.6210e9, "5b986628d09c52c4"),
     ("batch_8192_len100-400", "semi-global", "8x4", "batch"): (7.3193e10, "5b986628d09c52c4"),
 }
+
+
+# The same for packed panel jobs, keyed by (workload, kind) and measured on
+# packed_panel.hip.
+PANEL_TRAFFIC = {
+    ("batch_8192_len100-400", "global"): (9.5286e+10, "a1c5c1c927a9c0be"),
+    ("batch_8192_len100-400", "local"): (9.3456e+10, "a1c5c1c927a9c0be"),
+    ("single_1024x1000x1048", "local"): (8.8610e+08, "a1c5c1c927a9c0be"),
+    ("batch_8192_len100-400", "semi-global"): (9.3148e+10, "a1c5c1c927a9c0be"),
+    ("single_1024x1000x1048", "semi-global"): (9.1904e+08, "a1c5c1c927a9c0be"),
+    ("single_1024x1000x1048", "global"): (8.6315e+08, "a1c5c1c927a9c0be"),
+    ("single_128x128x128", "global"): (3.3457e+06, "a1c5c1c927a9c0be"),
+    ("single_4096x4000x4150", "global"): (4.0290e+10, "a1c5c1c927a9c0be"),
+}
+
+
+def panel_traffic(workload_name: str, kind: str):
+    import hashlib
+    entry = PANEL_TRAFFIC.get((workload_name, kind))
+    if entry is None:
+        return None
+    with open(os.path.join(ROOT, "paper_2605_28400_amd", "csrc", "packed_panel.hip"), "rb") as f:
+        sha = hashlib.sha256(f.read()).hexdigest()[:16]
+    return entry[0] if sha == entry[1] else None
 
 
 def scoring_path(trips, kind: str, engine: int, tile: str, packed: bool = False) -> str:
@@ -420,11 +444,12 @@ def main():
     plan = ts.Plan(lens, off, sc=sc, engine=args.engine, tile=(rj, rk), use_graph=bool(args.graph))
     info = plan.info()
     packed = bool(info["packed"])
+    panel_jobs = packed and info["panels"] > 0  # packed panel jobs, not whole pairs
     path = scoring_path(trips, args.kind, args.engine, args.tile, packed)
     if packed:
         ops = OPS_PER_CELL_PACKED_OF[args.kind]
         # The plan takes the autotuner's choice, staging included.
-        if tuned is not None and tuned["best"]["staging"] == 2:
+        if tuned is not None and not panel_jobs and tuned["best"]["staging"] == 2:
             path += "+lds-direct"
     d_scores = torch.zeros(len(trips), dtype=torch.int32, device="cuda")
     stream = torch.cuda.current_stream()
@@ -466,15 +491,19 @@ def main():
         "roofline": {"bound": "alu", "achieved": round(achieved, 3),
                      "peak": round(PEAK_INT32_TOPS, 2), "unit": "TOP/s",
                      "frac": round(achieved / PEAK_INT32_TOPS, 4),
-                     "traffic": measured_traffic(workload.name, args.kind,
-                                                 f"{info['tile_rows']}x{info['tile_cols']}", path),
+                     "traffic": (panel_traffic(workload.name, args.kind) if panel_jobs else
+                                 measured_traffic(workload.name, args.kind,
+                                                  f"{info['tile_rows']}x{info['tile_cols']}", path)),
                      "kernel_ms": round(ms_events, 4), "ops_per_cell": ops,
                      # Eq. 1 counted as 7 sums and a 7-way maximum (13 two-input
                      # operations), each an int32 instruction.
                      "frac_13_ops_per_cell": round(cells * (OPS_PER_CELL_OF[args.kind] + 6)
                                                    / (ms_events * 1e-3) / 1e12
                                                    / PEAK_INT32_TOPS, 4),
-                     "kernel": ("k_panel plane variant (two halves swept concurrently, two-wave "
+                     "kernel": ("k_panel_pk (persistent queue of packed panel jobs, two triplets or "
+                                "halves per lane in 16-bit halves); time of the whole plan run"
+                                if panel_jobs else
+                                "k_panel plane variant (two halves swept concurrently, two-wave "
                                 "panel workgroups) + gather + meet; time of the whole plan run"
                                 if path == "halves" else
                                 "k_sweep_pk (persistent job queue of whole-triplet pairs, two "
