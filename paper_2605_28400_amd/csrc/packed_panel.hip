@@ -23,15 +23,15 @@
 // that one triplet of the int32 kernel moves; a poll takes five loads (16
 // lanes cover a row with two entries each) and three ballots.
 //
-// What bounds it. Batches and long triplets run on single-wave workgroups,
-// two to a SIMD, bound by VALU issue (about 140 instructions a step against the
-// recurrence's 112) and by the waits it does not cover: 8192 triplets of
-// lengths 100-400 26.7 ms (whole pairs, one wavefront each: 31.3 ms, their
-// unequal sizes leave the device half empty at the end; int32: 46.5 ms), 1999
-// of them under local scoring 8.7 ms (34.8 ms), 4096 x 4000 x 4150 by halves
-// 10.9 ms (int32 halves: 31.3 ms). Short lone triplets are a chain of panel
-// hops: 1024 x 1000 x 1048 by halves on wave pairs 615 us (int32: 976 us), 0.39
-// us a step and 21 steps a hop.
+// What bounds it. Batches and long triplets run on single-wave workgroups, two
+// or three to a SIMD, bound by VALU issue (about 139 instructions a step
+// against the recurrence's 112; 93 % of the issue slots of the batch): 8192
+// triplets of lengths 100-400 24.9 ms (whole pairs, one wavefront each: 31.3
+// ms, their unequal sizes leave the device half empty at the end; int32: 46.5
+// ms), 1999 of them under local scoring 8.5 ms (34.8 ms), 4096 x 4000 x 4150 by
+// halves 10.8 ms (int32 halves: 31.3 ms). Short lone triplets are a chain of
+// panel hops: 1024 x 1000 x 1048 by halves on wave pairs 613 us (int32: 976 us),
+// 0.39 us a step and 21 steps a hop.
 #include <type_traits>
 
 #include "packed.h"
