@@ -78,6 +78,16 @@ def test_window_limit(torch_cuda, kind, na, packed):
     assert (outs[0] == want_scores([t], (5, -4, -6), kind)).all()
 
 
+@pytest.mark.parametrize("lens,packed", [((1588, 70, 65), 1), ((1594, 70, 65), 0), ((640, 600, 610), 1)])
+def test_semi_global_window(torch_cuda, lens, packed):
+    # As above; the third puts the faces' values far below the panels' windows.
+    t = tuple(np.full(n, 1, np.uint8) for n in lens)
+    print(f"semi-global window lens={lens}", flush=True)
+    outs, info = run(torch_cuda, [t], ts.scoring(5, -4, -6, kind=ts.SEMI_GLOBAL))
+    assert info["packed"] == packed
+    assert (outs[0] == want_scores([t], (5, -4, -6), ts.SEMI_GLOBAL)).all()
+
+
 def test_largest_values(torch_cuda):
     # 17 per residue pair and all-equal residues: a half's values reach 17 *
     # (645 + 645 + 1290) of the 65535 that 16 bits recover.
