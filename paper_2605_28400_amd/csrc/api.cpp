@@ -529,6 +529,8 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
   for (const TripletDesc& d : desc) {
     const uint64_t a = d.len[0], b = d.len[1], c = d.len[2];
     const uint64_t pairs = std::min(a, b) + std::min(a, c) + std::min(b, c);
+    // (Where every term is 0 nothing but the kernels' own limit bounds the sweep.)
+    if (a > (uint64_t)kMaxSweepLen) return false;
     if (off + step * (a + 2 * kPkPanel + 2) > kPackedMax) return false;
     const uint64_t most = sc.kind == kGlobal ? A * pairs : std::max(A, g) * (a + b + c);
     const uint64_t score = (uint64_t)maxs * pairs;  // no score is larger

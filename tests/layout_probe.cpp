@@ -1,0 +1,37 @@
+// Host-side view of the library's layouts, for tests without a GPU: the job
+// queue, the descriptors and the memory a batch would be given.
+#include <cstring>
+
+#include "../paper_2605_28400_amd/csrc/common.h"
+
+using namespace trioseq;
+
+// The layout of a plan (default options, packed panel jobs allowed). info:
+// [0] status, [1] modes, [2] packed, [3] halves, [4] longest sweep, [5] panels
+// reported, [6] jobs, [7] descriptors, [8] face pool ints, [9] plane ints,
+// [10] single-wave workgroups, [11] engine reported. desc (7 per descriptor,
+// up to cap: lens, out, start of the sweep, direction, longest sweep's
+// sequence) may be null.
+extern "C" void probe_layout(const uint32_t* lens, size_t n, const trioseq_scoring* sc, int64_t* info, int64_t* desc,
+                             size_t cap) {
+  const trioseq_plan_options o{-1, 0, 0, 0, 0, 0};
+  Layout L;
+  info[0] = build_layout(lens, nullptr, n, *sc, o, 256 * kWavesPerCuHint, &L, false, true);
+  info[1] = L.modes;
+  info[2] = L.packed;
+  info[3] = L.halves;
+  info[4] = L.lds_n0;
+  info[5] = L.panels;
+  info[6] = (int64_t)L.jobs.size();
+  info[7] = (int64_t)L.desc.size();
+  info[8] = (int64_t)L.pool_ints;
+  info[9] = (int64_t)L.plane_ints;
+  info[10] = L.pk_self;
+  info[11] = L.engine;
+  if (!desc) return;
+  for (size_t d = 0; d < L.desc.size() && d < cap; ++d) {
+    const TripletDesc& t = L.desc[d];
+    const int64_t row[7] = {t.len[0], t.len[1], t.len[2], t.out, t.start[0], t.rev, 0};
+    std::memcpy(desc + 7 * d, row, sizeof row);
+  }
+}

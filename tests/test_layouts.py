@@ -1,0 +1,46 @@
+"""CPU checks of the layouts plans are given: which form of the kernels a batch
+takes, and the limits of each."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2605_28400_amd as ts
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+FIELDS = ["status", "modes", "packed", "halves", "sweep", "panels", "jobs", "descs", "pool", "planes", "single_wave",
+          "engine"]
+WHOLE, PK_PANEL = 1, 4  # Layout::modes of whole-triplet jobs and of packed panel jobs
+MAX_SWEEP = 16384
+KINDS = [ts.GLOBAL, ts.SEMI_GLOBAL, ts.LOCAL]
+KIND_IDS = ["global", "semi-global", "local"]
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("probe") / "layout_probe.so")
+    lib = os.path.join(os.path.dirname(HERE), "paper_2605_28400_amd", "libtrioseq.so")
+    ts.lib()
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(HERE, "layout_probe.cpp"), lib, "-o", out], check=True)
+    return ctypes.CDLL(out)
+
+
+def layout(probe, lens, sc=None):
+    lens = np.ascontiguousarray(np.asarray(lens, dtype=np.uint32).reshape(-1))
+    info = np.zeros(len(FIELDS), dtype=np.int64)
+    probe.probe_layout(lens.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(lens.size // 3),
+                       ctypes.byref(sc or ts.scoring()), info.ctypes.data_as(ctypes.c_void_p), None, ctypes.c_size_t(0))
+    return dict(zip(FIELDS, info.tolist()))
+
+
+@pytest.mark.parametrize("inner", [40, 300])
+def test_no_sweep_beyond_the_longest_the_kernels_hold(probe, inner):
+    # Every term 0 (sub = 2 * gap): values never grow, so only the sweep's
+    # length bounds the packed forms.
+    sc = ts.scoring(-2, -2, -1)
+    for longest in (2 * MAX_SWEEP, 2 * MAX_SWEEP + 2, 100000):
+        got = layout(probe, [(longest, inner, inner)] * 2, sc)
+        assert got["status"] == 0 and got["sweep"] <= MAX_SWEEP, (longest, got)
