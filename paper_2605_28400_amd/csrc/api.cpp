@@ -646,8 +646,11 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
   // neighbour. Lone 1024 x 1000 x 1048: 0.82 ms single, 0.62 ms in pairs; 2560 x
   // 2500 x 2600: 3.49 and 3.48; 3072 x 3000 x 3120: 5.13 and 5.74; 4096 x 4000 x
   // 4150: 10.9 and 12.9.
+  // Pairs of one panel each have no faces to move: single waves (halves of 1000
+  // x 31 x 31: 191 us, 198 in wave pairs, 192 in int32 lanes; local 241, 253,
+  // 248; 250 x 31 x 31: 75.5, 77.4, 75.0).
   const PkTime t = pk_panel_time(*L);
-  L->pk_self = t.single_us < t.wave_pair_us;
+  L->pk_self = t.single_us < t.wave_pair_us || jobs == np;
   return true;
 }
 
@@ -734,7 +737,83 @@ static AxisChoice choose_axes_panels(const uint32_t len[3]) {
   return best;
 }
 
-bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L) {
+// Whether a batch runs better as whole pairs (W, one wavefront a pair) than as
+// the panel jobs chosen for it (P in pairs, or by halves), or in pairs after all. Panel jobs use the
+// device where whole pairs leave it waiting for their longest; where the pairs
+// are many and alike, or too short to be worth splitting, the jobs' own costs
+// decide: a panel takes one pop of the queue (16 ns, whatever its size), its
+// faces pass through memory, and halves add their planes' meeting. Microseconds,
+// whole pairs / panel jobs in pairs / by halves, at the lines drawn here:
+//   one panel a pair: 20000 of 20 residues 256 / 308 / -, 2048 of 128 x 31 x 31
+//     90 / 98 / 172, 512 of them 73 / 74 / 77, 128 of them 70 / 71 / 61, 1024 of
+//     500 x 31 x 31 207 / 229 / 171, 1300 of them 208 / 235 / 281;
+//   two by two panels: 2000 of 32 114 / 127, 2300 of them 153 / 137, 3800 168 /
+//     185, 30000 908 / 1320; 1700 of 40-60 151 / 145; 8192 of 5-60 on every
+//     axis 179 / 190, 4096 of them 166 / 129; semi-global, 8000 of 63: 685 /
+//     623, 6000 of them 421 / 473, 15000 of 20-60 616 / 702;
+//   more: 20000 of 64 1979 / 2337, 8192 of 100 2252 / 2188, 20000 of 30-100
+//     1721 / 2018, 8192 of 30-150 2121 / 1891.
+enum BatchForm { kChosen, kPairs, kWhole };
+static BatchForm batch_form(const Layout& W, const Layout& P, bool halves, int waves) {
+  const double np = (double)(W.desc.size() / 2);
+  double steps = 0, panels = 0, sweeps = 0, most = 0;  // of the panel pairs
+  for (size_t p = 0; p + 1 < P.desc.size(); p += 2) {
+    const TripletDesc &a = P.desc[p], &b = P.desc[p + 1];
+    const double n0 = std::max(a.len[0], b.len[0]) + 1 + kSkew;
+    const double k = (std::max(a.len[1], b.len[1]) / kPkPanel + 1.0) * (std::max(a.len[2], b.len[2]) / kPkPanel + 1);
+    steps += k * n0;
+    panels += k;
+    sweeps += k * (n0 - 1 - kSkew);
+    most = std::max(most, k);
+  }
+  // Whole pairs: steps, and with about 12 for a panel's start and 27 for a
+  // pair's, what the longest-first queue makes of them.
+  const int H = panel_rows(W.ks), C = panel_cols(W.ks);
+  double wsteps = 0, wpanels = 0, longest = 0;
+  std::vector<double> cost;
+  cost.reserve(W.desc.size() / 2);
+  for (size_t p = 0; p + 1 < W.desc.size(); p += 2) {
+    const TripletDesc &a = W.desc[p], &b = W.desc[p + 1];
+    const double n0 = std::max(a.len[0], b.len[0]) + 1 + kSkew;
+    const double k = (std::max(a.len[1], b.len[1]) / H + 1.0) * (std::max(a.len[2], b.len[2]) / C + 1);
+    wsteps += k * n0;
+    wpanels += k;
+    longest = std::max(longest, k * n0);
+    cost.push_back(k * (n0 + 12) + 27);
+  }
+  const bool global = P.kind == kGlobal, semi = P.kind == kSemiGlobal;
+  if (panels <= 1.1 * np && (most <= 1 || np > waves / 2)) {
+    // One panel a pair. Halves are worth their meeting while there is room for
+    // them and the sweep is long; whole pairs may take other axes, of more panels
+    // (20000 of 64 x 10 x 10 354 / 350 us, of 64 x 5 x 5 294 / 344, of 1000 x 10 x 10
+    // 3078 / 2577).
+    if (halves && np <= waves / 4 && steps / np >= 64 + 0.4 * np) return kChosen;
+    const bool dearer = 1.08 * (steps + 40 * panels) < wsteps + 12 * wpanels + 27 * np;
+    return dearer && !semi && (np > 0.93 * waves || (global && np <= waves / 2)) ? kPairs : kWhole;
+  }
+  const double fill = wsteps / waves / longest;  // rounds of the longest pair's
+  if (halves) return fill > 1. / 3 ? kWhole : kChosen;
+  if (fill <= 1. / 3) return kChosen;
+  // Where the two are close: few rounds of unlike panel counts; about two of
+  // semi-global pairs that are alike.
+  if ((most > 4 && fill < 1.2) || (semi && fill > 1.55 && fill < 3 && wsteps >= 0.8 * longest * np)) return kChosen;
+  if (steps > 400 * np && !(wpanels <= 12.5 * np && sweeps <= 115 * panels && np > 5.4 * waves)) return kChosen;
+  std::sort(cost.begin(), cost.end(), std::greater<double>());
+  std::vector<double> busy(waves, 0.);  // a min-heap of the waves' ends
+  double total = 0, end = 0;
+  for (double c : cost) {
+    std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+    busy.back() += c;
+    total += c;
+    end = std::max(end, busy.back());
+    std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+  }
+  const double use = total / waves / end;
+  return use > (steps > 400 * np ? 0.75 : np <= waves / 2 ? 0.4 : fill < 1.2 ? 0.75 : 0.7) ? kWhole : kChosen;
+}
+
+bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L,
+                         const Layout* whole, int waves) {
   std::vector<size_t> split(n);
   std::iota(split.begin(), split.end(), 0);
   std::vector<AxisChoice> ax(n);
@@ -800,6 +879,14 @@ bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, co
   if (have_h && have_p) {
     const PkTime h = pk_panel_time(H), p = pk_panel_time(P);
     use_h = std::min(h.single_us * 1.03, h.wave_pair_us * 1.25) < std::min(p.single_us, p.wave_pair_us);
+  }
+  if (whole && have_p) {
+    const BatchForm form = batch_form(*whole, P, use_h, waves);
+    if (form == kWhole) {
+      *L = *whole;
+      return true;
+    }
+    if (form == kPairs) use_h = false;
   }
   Layout& Q = use_h ? H : P;
   Q.cells = L->cells;
@@ -955,9 +1042,12 @@ trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
                              (o.waves_per_simd == 0 || o.waves_per_simd == 2) && o.lane_exchange != 2 && o.staging != 2;
   const bool any_shape = o.tile_rows || o.tile_cols || o.waves_per_simd || o.lane_exchange || o.staging;
   if (packed_panels && !planes && n > 1 && o.engine == -1 && !o.grid && ks.group == 1 &&
-      (o.packed == 2 ? default_shape : o.packed == 0 && !any_shape) &&
-      packed_batch_layout(lens, off, n, sc, L))
-    return TRIOSEQ_OK;
+      (o.packed == 2 ? default_shape : o.packed == 0 && !any_shape)) {
+    // (Whole pairs exist where the split rule splits none of the batch.)
+    Layout whole = *L;
+    const bool pairs = pair_up(&whole, sc, KernelShape{4, 4, 2});
+    if (packed_batch_layout(lens, off, n, sc, L, pairs ? &whole : nullptr, std::max(4, waves_hint))) return TRIOSEQ_OK;
+  }
   if (o.packed == 2) {
     KernelShape pks{o.tile_rows ? o.tile_rows : 4, o.tile_cols ? o.tile_cols : 4,
                     o.waves_per_simd ? o.waves_per_simd : 2};

@@ -44,3 +44,28 @@ def test_no_sweep_beyond_the_longest_the_kernels_hold(probe, inner):
     for longest in (2 * MAX_SWEEP, 2 * MAX_SWEEP + 2, 100000):
         got = layout(probe, [(longest, inner, inner)] * 2, sc)
         assert got["status"] == 0 and got["sweep"] <= MAX_SWEEP, (longest, got)
+
+
+# Small and thin triplets: what the default options take (measured times beside
+# the rule). "pairs" and "halves" are panel jobs.
+@pytest.mark.parametrize("n,lens,form", [
+    (2, (20, 20, 20), "whole"), (20000, (20, 20, 20), "whole"), (2048, (128, 20, 20), "whole"),
+    (512, (128, 31, 31), "whole"), (64, (128, 31, 31), "halves"), (1024, (500, 31, 31), "halves"),
+    (1300, (500, 31, 31), "whole"), (2000, (32, 32, 32), "whole"), (2300, (32, 32, 32), "pairs"),
+    (30000, (32, 32, 32), "whole"), (600, (63, 63, 63), "pairs"), (8192, (128, 128, 128), "pairs")])
+@pytest.mark.parametrize("kind", KINDS, ids=KIND_IDS)
+def test_which_form_a_batch_takes(probe, kind, n, lens, form):
+    got = layout(probe, [lens] * n, ts.scoring(kind=kind))
+    assert got["status"] == 0 and got["packed"] == 1
+    assert got["modes"] == (WHOLE if form == "whole" else PK_PANEL), got
+    assert got["halves"] == (form == "halves"), got
+    if lens[1] < 32 and form == "halves":  # no faces to move: one wave a workgroup
+        assert got["single_wave"] == 1
+
+
+def test_unlike_lengths_stay_panel_jobs(probe):
+    rng = np.random.default_rng(3)
+    anc = rng.uniform(100, 400, 8192)
+    assert layout(probe, np.rint(anc[:, None] * rng.uniform(0.97, 1.03, (8192, 3))))["modes"] == PK_PANEL
+    assert layout(probe, rng.integers(5, 61, (4096, 3)))["modes"] == PK_PANEL
+    assert layout(probe, rng.integers(5, 61, (8192, 3)))["modes"] == WHOLE
