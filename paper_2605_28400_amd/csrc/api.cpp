@@ -676,15 +676,34 @@ static void half_descs(const uint32_t* l, const uint64_t* off, TripletDesc d[2],
   *box = SplitDesc{0, 0, l[order[1]] + 1, l[order[2]] + 1, 0, 0, 0};
 }
 
+// At least nine panels across the two shorter axes.
+static bool nine_panels(const uint32_t* l) {
+  const uint32_t lo = std::min({l[0], l[1], l[2]}), hi = std::max({l[0], l[1], l[2]});
+  const uint32_t mid = (uint32_t)((uint64_t)l[0] + l[1] + l[2] - lo - hi);
+  return (uint64_t)(lo / kPkPanel + 1) * (mid / kPkPanel + 1) >= 9;
+}
+
 // Semi-global halves (packed only): at least nine panels across the two shorter
 // axes. Halves / the triplet as a pair with itself: 128 x 125 x 131 142 / 152
 // us, 300 x 290 x 305 271 / 319, 723 x 651 x 698 595 / 737, 2048 x 2000 x 2080
 // 2.79 / 4.74 ms, 4096 x 4000 x 4150 12.7 / 35.2 ms (int32). Thin triplets would
 // gain as well, but their plans have always reported the panels of one sweep.
+// Beyond the longest sweep the pair with itself takes a shorter axis: 17000 x 64
+// x 64 3.65 ms (halves 5.73, int32 4.80), 30000 x 1000 x 1000 14.2 ms (19.9,
+// 16.4); 16000 x 64 x 64 by halves 5.3 ms, 8.9 as a pair with itself.
 bool semi_global_halves(const uint32_t* l) {
-  const uint32_t lo = std::min({l[0], l[1], l[2]}), hi = std::max({l[0], l[1], l[2]});
-  const uint32_t mid = (uint32_t)((uint64_t)l[0] + l[1] + l[2] - lo - hi);
-  return (uint64_t)(lo / kPkPanel + 1) * (mid / kPkPanel + 1) >= 9;
+  return nine_panels(l) && std::max({l[0], l[1], l[2]}) <= (uint32_t)kMaxSweepLen;
+}
+
+// Lone triplets that run as a pair with themselves unless they have halves:
+// short ones of every kind, and semi-global ones of nine panels or of a length
+// no sweep takes. Long thin semi-global ones keep int32 lanes (pair with itself
+// / int32: 64 x 40 x 40 81 / 84 us, 250 x 40 x 40 190 / 188, 2000 x 40 x 40 1191 /
+// 1145; 20000 x 40 x 40 4.2 / 5.5 ms).
+bool self_pair(int kind, const uint32_t* l) {
+  const uint32_t longest = std::max({l[0], l[1], l[2]});
+  if (longest < kHalfSplitMin) return true;
+  return kind == kSemiGlobal && (longest > (uint32_t)kMaxSweepLen || nine_panels(l));
 }
 
 bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L) {
@@ -1293,14 +1312,12 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
       half = true;
     }
   }
-  // A lone triplet that has no halves path (thin under semi-global scoring, or
-  // shorter than it takes) runs as a pair with itself: per cell as many
-  // instructions as int32 lanes take, but the packed kernel's shorter hops and
-  // polls (semi-global 723 x 651 x 698: 824 -> 721 us; global 48 x 45 x 51: 68 ->
-  // 58 us, 100 x 97 x 104: 119 -> 95 us).
+  // A lone triplet that takes no halves may run as a pair with itself: per cell
+  // as many instructions as int32 lanes take, but the packed kernel's shorter
+  // hops and polls (semi-global 723 x 651 x 698: 824 -> 721 us; global 48 x 45 x
+  // 51: 68 -> 58 us, 100 x 97 x 104: 119 -> 95 us).
   if (n == 1 && defaults && may_pack && !mem && !half && o.lane_exchange != 2 && L.modes == 2 &&
-      (scp->kind == kSemiGlobal ||
-       (o.half_split_min == 0 && std::max({lens[0], lens[1], lens[2]}) < kHalfSplitMin))) {
+      (scp->kind == kSemiGlobal || o.half_split_min == 0) && self_pair(scp->kind, lens)) {
     std::vector<uint64_t> def(3);
     uint64_t tw = 0;
     if (!word_off) trioseq_packed_layout(lens, 1, def.data(), &tw);

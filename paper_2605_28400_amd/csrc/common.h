@@ -123,6 +123,7 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
 // One triplet's halves (longest sequence cut in two) as one packed pair, and
 // one triplet as a pair with itself.
 bool semi_global_halves(const uint32_t* lens);
+bool self_pair(int kind, const uint32_t* lens);
 bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 bool packed_self_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 // Lays out a batch as packed panel jobs of pairs: neighbours by size, or the

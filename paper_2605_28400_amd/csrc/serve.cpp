@@ -169,7 +169,7 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
   const bool halves = n == 1 && (s->sc.kind != kSemiGlobal || semi_global_halves(lens.data())) &&
                       std::max({lens[0], lens[1], lens[2]}) >= kHalfSplitMin;
   bool packed = halves ? packed_halves_layout(lens.data(), offs.data(), s->sc, &L)
-                : n == 1 ? packed_self_layout(lens.data(), offs.data(), s->sc, &L)
+                : n == 1 ? self_pair(s->sc.kind, lens.data()) && packed_self_layout(lens.data(), offs.data(), s->sc, &L)
                          : packed_batch_layout(lens.data(), offs.data(), n, s->sc, &L);
   if (packed && !alone) L.pk_self = true;
   int grid = 0, wpc = 0;

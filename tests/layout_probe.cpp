@@ -35,3 +35,9 @@ extern "C" void probe_layout(const uint32_t* lens, size_t n, const trioseq_scori
     std::memcpy(desc + 7 * d, row, sizeof row);
   }
 }
+
+// Which packed forms a lone triplet of these lengths may take: bit 0 semi-global
+// halves, bit 1 a pair with itself (of that kind).
+extern "C" int probe_lone(const uint32_t* lens, int kind) {
+  return (semi_global_halves(lens) ? 1 : 0) | (self_pair(kind, lens) ? 2 : 0);
+}

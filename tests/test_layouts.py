@@ -69,3 +69,18 @@ def test_unlike_lengths_stay_panel_jobs(probe):
     assert layout(probe, np.rint(anc[:, None] * rng.uniform(0.97, 1.03, (8192, 3))))["modes"] == PK_PANEL
     assert layout(probe, rng.integers(5, 61, (4096, 3)))["modes"] == PK_PANEL
     assert layout(probe, rng.integers(5, 61, (8192, 3)))["modes"] == WHOLE
+
+
+@pytest.mark.parametrize("lens,halves,pair", [
+    ((723, 651, 698), 1, 1), ((130, 64, 64), 1, 1), ((127, 40, 40), 0, 1), ((128, 40, 40), 0, 0), ((2047, 40, 40), 0, 0),
+    ((128, 63, 95), 0, 0), ((16384, 64, 64), 1, 1), ((16385, 64, 64), 0, 1), ((64, 30000, 64), 0, 1),
+    ((24000, 20, 20), 0, 1)])
+def test_which_form_a_lone_semi_global_triplet_may_take(probe, lens, halves, pair):
+    got = probe.probe_lone((ctypes.c_uint32 * 3)(*lens), ts.SEMI_GLOBAL)
+    assert (got & 1, got >> 1) == (halves, pair)
+
+
+def test_only_short_lone_triplets_of_the_other_kinds_pair_with_themselves(probe):
+    for kind in (ts.GLOBAL, ts.LOCAL):
+        for lens, pair in (((127, 120, 126), 1), ((128, 120, 126), 0), ((20000, 20, 20), 0), ((1000, 900, 950), 0)):
+            assert probe.probe_lone((ctypes.c_uint32 * 3)(*lens), kind) >> 1 == pair
