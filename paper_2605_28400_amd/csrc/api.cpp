@@ -388,6 +388,40 @@ trioseq_status trioseq_packed_layout(const uint32_t* lens, size_t n, uint64_t* w
 
 namespace trioseq {
 
+// 0 .. n - 1 in ascending order of their keys (equal keys in index order): by
+// comparison for a few, else byte by byte from the last, leaving out the bytes
+// that all keys share (20000 triplets of 8-31 residues: a plan's three sorts 0.6
+// ms, 11 ms when they compared descriptors through the indices).
+struct SortKey {
+  uint64_t w[3];
+};
+template <class F>
+static std::vector<uint32_t> sorted_by(size_t n, F key) {
+  std::vector<SortKey> k(n);
+  std::vector<uint32_t> idx(n), to(n);
+  for (size_t t = 0; t < n; ++t) k[t] = key(t);
+  std::iota(idx.begin(), idx.end(), 0u);
+  if (n < 256) {
+    std::stable_sort(idx.begin(), idx.end(), [&](uint32_t x, uint32_t y) {
+      return std::lexicographical_compare(k[x].w, k[x].w + 3, k[y].w, k[y].w + 3);
+    });
+    return idx;
+  }
+  for (int w = 2; w >= 0; --w) {
+    uint64_t differ = 0;
+    for (const SortKey& x : k) differ |= x.w[w] ^ k[0].w[w];
+    for (int shift = 0; shift < 64; shift += 8) {
+      if (!((differ >> shift) & 255u)) continue;
+      size_t at[257] = {0};
+      for (const SortKey& x : k) ++at[1 + ((x.w[w] >> shift) & 255u)];
+      for (int v = 0; v < 255; ++v) at[v + 1] += at[v];
+      for (uint32_t t : idx) to[at[(k[t].w[w] >> shift) & 255u]++] = t;
+      idx.swap(to);
+    }
+  }
+  return idx;
+}
+
 // Packed pairs (two triplets per lane, one 16-bit half each): the batch's
 // whole triplets, sorted by their axis lengths, are paired neighbour with
 // neighbour (a lone last one with itself) and each pair is one job over the
@@ -419,24 +453,20 @@ static bool pair_up(Layout* L, const trioseq_scoring& sc, const KernelShape& ks)
     const uint64_t PJ = std::max(a.len[1], b.len[1]) / H + 1, PK = std::max(a.len[2], b.len[2]) / W + 1;
     return PJ * PK * (n0 + 1 + kSkew);
   };
-  auto total_cost = [&](const std::vector<size_t>& v) {
+  auto total_cost = [&](const std::vector<uint32_t>& v) {
     uint64_t c = 0;
     for (size_t q = 0; q < np; ++q) c += pair_cost(L->desc[v[2 * q]], L->desc[v[std::min(2 * q + 1, n - 1)]]);
     return c;
   };
-  std::vector<size_t> idx(n), idx2(n);
-  std::iota(idx.begin(), idx.end(), 0);
-  std::iota(idx2.begin(), idx2.end(), 0);
-  std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) {
-    const TripletDesc &da = L->desc[a], &db = L->desc[b];
-    return std::make_tuple(da.len[0], da.len[1], da.len[2]) < std::make_tuple(db.len[0], db.len[1], db.len[2]);
+  const std::vector<TripletDesc>& in = L->desc;
+  const std::vector<uint32_t> by_len = sorted_by(n, [&](size_t t) {
+    return SortKey{{in[t].len[0], in[t].len[1], in[t].len[2]}};
   });
-  std::stable_sort(idx2.begin(), idx2.end(), [&](size_t a, size_t b) {
-    const TripletDesc &da = L->desc[a], &db = L->desc[b];
-    return std::make_tuple(da.len[1] / H, da.len[2] / W, da.len[0], da.len[1], da.len[2]) <
-           std::make_tuple(db.len[1] / H, db.len[2] / W, db.len[0], db.len[1], db.len[2]);
+  const std::vector<uint32_t> by_panels = sorted_by(n, [&](size_t t) {
+    return SortKey{{(uint64_t)(in[t].len[1] / H) << 32 | in[t].len[2] / W, in[t].len[0],
+                    (uint64_t)in[t].len[1] << 32 | in[t].len[2]}};
   });
-  if (total_cost(idx2) < total_cost(idx)) idx.swap(idx2);
+  const std::vector<uint32_t>& idx = total_cost(by_panels) < total_cost(by_len) ? by_panels : by_len;
   uint64_t box_jk = 0, n0max = 0, stride = 0;
   std::vector<uint64_t> cost(np);
   for (size_t q = 0; q < np; ++q) {
@@ -469,9 +499,7 @@ static bool pair_up(Layout* L, const trioseq_scoring& sc, const KernelShape& ks)
     desc[2 * q] = L->desc[idx[2 * q]];
     desc[2 * q + 1] = L->desc[idx[std::min(2 * q + 1, n - 1)]];
   }
-  std::vector<size_t> order(np);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+  const std::vector<uint32_t> order = sorted_by(np, [&](size_t q) { return SortKey{{~cost[q], 0, 0}}; });
   L->jobs.clear();
   for (size_t q : order) L->jobs.push_back(JobDesc{(uint32_t)(2 * q), kWholeTriplet});
   L->desc.swap(desc);
@@ -484,22 +512,31 @@ static bool pair_up(Layout* L, const trioseq_scoring& sc, const KernelShape& ks)
   return true;
 }
 
-// Estimated times of a layout's packed panel jobs (see pair_panel_layout).
+// Estimated times of the panel jobs of packed pairs (see panel_jobs).
 struct PkTime {
-  double single_us, wave_pair_us;
-};
-static PkTime pk_panel_time(const Layout& L) {
   double steps = 0, chain = 0;
-  for (size_t p = 0; p + 1 < L.desc.size(); p += 2) {
-    const TripletDesc &a = L.desc[p], &b = L.desc[p + 1];
-    const double n0 = std::max(a.len[0], b.len[0]) + 1 + kSkew;
-    const double PJ = std::max(a.len[1], b.len[1]) / kPkPanel + 1, PK = std::max(a.len[2], b.len[2]) / kPkPanel + 1;
-    steps += PJ * PK * (n0 + 12);  // (a panel's start costs about 12 steps)
-    chain = std::max(chain, n0 + 21 * (PJ + PK));
+  void add(uint32_t n0, uint32_t n1, uint32_t n2) {
+    const double slices = n0 + 1 + kSkew, PJ = n1 / kPkPanel + 1, PK = n2 / kPkPanel + 1;
+    steps += PJ * PK * (slices + 12);  // (a panel's start costs about 12 steps)
+    chain = std::max(chain, slices + 21 * (PJ + PK));
   }
   // 256 compute units: 2048 single waves, 1024 wave pairs.
-  const double s1 = steps / 2048 * 0.66, c1 = chain * 24 / 21 * 0.4, s2 = steps / 1024 * 0.385, c2 = chain * 0.4;
-  return PkTime{std::max(s1, c1) + 0.4 * std::min(s1, c1), std::max(s2, c2) + 0.25 * std::min(s2, c2)};
+  double single_us() const {
+    const double s = steps / 2048 * 0.66, c = chain * 24 / 21 * 0.4;
+    return std::max(s, c) + 0.4 * std::min(s, c);
+  }
+  double wave_pair_us() const {
+    const double s = steps / 1024 * 0.385, c = chain * 0.4;
+    return std::max(s, c) + 0.25 * std::min(s, c);
+  }
+};
+static PkTime pk_panel_time(const std::vector<TripletDesc>& desc) {
+  PkTime t;
+  for (size_t p = 0; p + 1 < desc.size(); p += 2) {
+    const TripletDesc &a = desc[p], &b = desc[p + 1];
+    t.add(std::max(a.len[0], b.len[0]), std::max(a.len[1], b.len[1]), std::max(a.len[2], b.len[2]));
+  }
+  return t;
 }
 
 // What a pair must keep to for its panels to run packed (the reasons are in
@@ -509,9 +546,10 @@ static PkTime pk_panel_time(const Layout& L) {
 // itself is recovered from 16 bits where it leaves the panel (score, plane), so
 // it must stay below 2^16: at most maxA per residue pair that two sequences can
 // form, or per residue with the semi-global axes and local floors.
-// Panels that a diagonal of a group of pairs has at least, on average.
-constexpr double kPkWidth = 2048;
-bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, Layout* L) {
+struct PanelValues {
+  uint64_t off, kc;  // stored value of a panel's base, offset of semi-global candidates
+};
+static bool panel_values(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, PanelValues* v) {
   int mina = INT32_MAX, maxa = 0, maxs = 0;
   for (int x = 0; x < 4; ++x)
     for (int y = 0; y < 4; ++y) {
@@ -552,9 +590,18 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
         kc + (uint64_t)maxs * (std::min(d.len[0], d.len[1]) + std::min(d.len[0], d.len[2]) + std::min(d.len[1], d.len[2])) >
             0xFFFF)
       return false;
+  *v = PanelValues{off, kc};
+  return true;
+}
 
+// Panels that a diagonal of a group of pairs has at least, on average.
+constexpr double kPkWidth = 2048;
+
+// The job queue and buffers of pairs whose values fit (panel_values).
+static bool panel_jobs(std::vector<TripletDesc> desc, const trioseq_scoring& sc, bool planes, const PanelValues& v,
+                       Layout* L) {
   const size_t np = desc.size() / 2;
-  L->desc = desc;
+  L->desc = std::move(desc);
   L->jobs.clear();
   std::vector<uint32_t> PJ(np), PK(np);
   std::vector<uint64_t> cost(np);
@@ -580,9 +627,7 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
   // pairs in one group.) Two sets of face buffers serve the groups in turn: a
   // group's panels start when all jobs of the group two before are finished,
   // which is long before they are popped.
-  std::vector<size_t> idx(np);
-  std::iota(idx.begin(), idx.end(), 0);
-  std::stable_sort(idx.begin(), idx.end(), [&](size_t x, size_t y) { return cost[x] > cost[y]; });
+  const std::vector<uint32_t> idx = sorted_by(np, [&](size_t p) { return SortKey{{~cost[p], 0, 0}}; });
   L->jobs.reserve(jobs);
   uint64_t region[2] = {0, 0}, done[2] = {0, 0};  // per set: ints of buffers, jobs of its groups so far
   uint64_t tags = 0;
@@ -623,7 +668,7 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
     for (size_t q = groups[g].first; q < groups[g].second; ++q) L->desc[2 * idx[q]].face_off += region[0];
   if (tags + 2 > (1u << 24)) return false;
   const uint64_t pool = region[0] + region[1];
-  L->pk_reuse = groups.size() > 2;
+  L->pk_reuse = groups.size() > 2 && pool != 0;
   L->tag_step = (int)tags + 2;
   L->ks = KernelShape{4, 4, 2};
   L->kind = sc.kind;
@@ -636,8 +681,8 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
   L->face_stride = 0;
   L->pool_ints = pool;
   L->packed = true;
-  L->pk_base = (uint32_t)off;
-  L->pk_kc = (uint32_t)kc;
+  L->pk_base = (uint32_t)v.off;
+  L->pk_kc = (uint32_t)v.kc;
   // Single-wave workgroups (two computing waves on a SIMD) or a computing and a
   // memory wave each (shorter hops from panel to panel): whichever the batch's
   // total work and its longest chain of panels make faster, at the steps both
@@ -649,18 +694,32 @@ bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scori
   // Pairs of one panel each have no faces to move: single waves (halves of 1000
   // x 31 x 31: 191 us, 198 in wave pairs, 192 in int32 lanes; local 241, 253,
   // 248; 250 x 31 x 31: 75.5, 77.4, 75.0).
-  const PkTime t = pk_panel_time(*L);
-  L->pk_self = t.single_us < t.wave_pair_us || jobs == np;
+  const PkTime t = pk_panel_time(L->desc);
+  L->pk_self = t.single_us() < t.wave_pair_us() || jobs == np;
   return true;
+}
+
+bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, Layout* L) {
+  PanelValues v;
+  return panel_values(desc, sc, planes, &v) && panel_jobs(desc, sc, planes, v, L);
+}
+
+// The halved axis of a triplet (its longest) and the other two.
+static void half_order(const uint32_t* l, int order[3]) {
+  int ax = 0;
+  for (int q = 1; q < 3; ++q)
+    if (l[q] > l[ax]) ax = q;
+  order[0] = ax;
+  order[1] = ax == 0 ? 1 : 0;
+  order[2] = ax == 2 ? 1 : 2;
 }
 
 // The halves of a triplet as two descriptors (the longest sequence cut in two,
 // the second half read backwards), and the size of their last slices.
 static void half_descs(const uint32_t* l, const uint64_t* off, TripletDesc d[2], SplitDesc* box) {
-  int ax = 0;
-  for (int q = 1; q < 3; ++q)
-    if (l[q] > l[ax]) ax = q;
-  const int order[3] = {ax, ax == 0 ? 1 : 0, ax == 2 ? 1 : 2};
+  int order[3];
+  half_order(l, order);
+  const int ax = order[0];
   const uint32_t mid = l[ax] / 2;
   for (int h = 0; h < 2; ++h) {
     d[h] = TripletDesc{};
@@ -756,13 +815,14 @@ static AxisChoice choose_axes_panels(const uint32_t len[3]) {
   return best;
 }
 
-// Whether a batch runs better as whole pairs (W, one wavefront a pair) than as
-// the panel jobs chosen for it (P in pairs, or by halves), or in pairs after all. Panel jobs use the
-// device where whole pairs leave it waiting for their longest; where the pairs
-// are many and alike, or too short to be worth splitting, the jobs' own costs
-// decide: a panel takes one pop of the queue (16 ns, whatever its size), its
-// faces pass through memory, and halves add their planes' meeting. Microseconds,
-// whole pairs / panel jobs in pairs / by halves, at the lines drawn here:
+// Whether a batch runs better as whole pairs (one wavefront a pair) than as the
+// panel jobs chosen for it (P in pairs, or by halves), or in pairs after all.
+// Panel jobs use the device where whole pairs leave it waiting for their
+// longest; where the pairs are many and alike, or too short to be worth
+// splitting, the jobs' own costs decide: a panel takes one pop of the queue (16
+// ns, whatever its size), its faces pass through memory, and halves add their
+// planes' meeting. Microseconds, whole pairs / panel jobs in pairs / by halves,
+// at the lines drawn here:
 //   one panel a pair: 20000 of 20 residues 256 / 308 / -, 2048 of 128 x 31 x 31
 //     90 / 98 / 172, 512 of them 73 / 74 / 77, 128 of them 70 / 71 / 61, 1024 of
 //     500 x 31 x 31 207 / 229 / 171, 1300 of them 208 / 235 / 281;
@@ -772,27 +832,37 @@ static AxisChoice choose_axes_panels(const uint32_t len[3]) {
 //     623, 6000 of them 421 / 473, 15000 of 20-60 616 / 702;
 //   more: 20000 of 64 1979 / 2337, 8192 of 100 2252 / 2188, 20000 of 30-100
 //     1721 / 2018, 8192 of 30-150 2121 / 1891.
+// *W: the batch as whole pairs, made from the triplets of `unsplit` when kWhole is
+// in question.
 enum BatchForm { kChosen, kPairs, kWhole };
-static BatchForm batch_form(const Layout& W, const Layout& P, bool halves, int waves) {
-  const double np = (double)(W.desc.size() / 2);
+static BatchForm batch_form(const std::vector<TripletDesc>& P, bool halves, const Layout& unsplit,
+                            const trioseq_scoring& sc, int waves, Layout* W) {
+  const double np = (double)(P.size() / 2);
   double steps = 0, panels = 0, sweeps = 0, most = 0;  // of the panel pairs
-  for (size_t p = 0; p + 1 < P.desc.size(); p += 2) {
-    const TripletDesc &a = P.desc[p], &b = P.desc[p + 1];
-    const double n0 = std::max(a.len[0], b.len[0]) + 1 + kSkew;
+  for (size_t p = 0; p + 1 < P.size(); p += 2) {
+    const TripletDesc &a = P[p], &b = P[p + 1];
+    const double n0 = std::max(a.len[0], b.len[0]);
     const double k = (std::max(a.len[1], b.len[1]) / kPkPanel + 1.0) * (std::max(a.len[2], b.len[2]) / kPkPanel + 1);
-    steps += k * n0;
+    steps += k * (n0 + 1 + kSkew);
     panels += k;
-    sweeps += k * (n0 - 1 - kSkew);
+    sweeps += k * n0;
     most = std::max(most, k);
   }
+  const bool one_panel = panels <= 1.1 * np && (most <= 1 || np > waves / 2), long_pairs = steps > 400 * np;
+  // One panel a pair: halves are worth their meeting while there is room for
+  // them and the sweep is long.
+  if (one_panel && halves && np <= waves / 4 && steps / np >= 64 + 0.4 * np) return kChosen;
+  if (!one_panel && !halves && long_pairs && !(sweeps <= 115 * panels && np > 5.4 * waves)) return kChosen;
+  *W = unsplit;
+  if (!pair_up(W, sc, KernelShape{4, 4, 2})) return kChosen;
   // Whole pairs: steps, and with about 12 for a panel's start and 27 for a
   // pair's, what the longest-first queue makes of them.
-  const int H = panel_rows(W.ks), C = panel_cols(W.ks);
+  const int H = panel_rows(W->ks), C = panel_cols(W->ks);
   double wsteps = 0, wpanels = 0, longest = 0;
   std::vector<double> cost;
-  cost.reserve(W.desc.size() / 2);
-  for (size_t p = 0; p + 1 < W.desc.size(); p += 2) {
-    const TripletDesc &a = W.desc[p], &b = W.desc[p + 1];
+  cost.reserve(P.size() / 2);
+  for (size_t p = 0; p + 1 < W->desc.size(); p += 2) {
+    const TripletDesc &a = W->desc[p], &b = W->desc[p + 1];
     const double n0 = std::max(a.len[0], b.len[0]) + 1 + kSkew;
     const double k = (std::max(a.len[1], b.len[1]) / H + 1.0) * (std::max(a.len[2], b.len[2]) / C + 1);
     wsteps += k * n0;
@@ -800,13 +870,10 @@ static BatchForm batch_form(const Layout& W, const Layout& P, bool halves, int w
     longest = std::max(longest, k * n0);
     cost.push_back(k * (n0 + 12) + 27);
   }
-  const bool global = P.kind == kGlobal, semi = P.kind == kSemiGlobal;
-  if (panels <= 1.1 * np && (most <= 1 || np > waves / 2)) {
-    // One panel a pair. Halves are worth their meeting while there is room for
-    // them and the sweep is long; whole pairs may take other axes, of more panels
-    // (20000 of 64 x 10 x 10 354 / 350 us, of 64 x 5 x 5 294 / 344, of 1000 x 10 x 10
-    // 3078 / 2577).
-    if (halves && np <= waves / 4 && steps / np >= 64 + 0.4 * np) return kChosen;
+  const bool global = sc.kind == kGlobal, semi = sc.kind == kSemiGlobal;
+  if (one_panel) {
+    // (Whole pairs may take other axes, of more panels: 20000 of 64 x 10 x 10 354
+    // / 350 us, of 64 x 5 x 5 294 / 344, of 1000 x 10 x 10 3078 / 2577.)
     const bool dearer = 1.08 * (steps + 40 * panels) < wsteps + 12 * wpanels + 27 * np;
     return dearer && !semi && (np > 0.93 * waves || (global && np <= waves / 2)) ? kPairs : kWhole;
   }
@@ -816,7 +883,7 @@ static BatchForm batch_form(const Layout& W, const Layout& P, bool halves, int w
   // Where the two are close: few rounds of unlike panel counts; about two of
   // semi-global pairs that are alike.
   if ((most > 4 && fill < 1.2) || (semi && fill > 1.55 && fill < 3 && wsteps >= 0.8 * longest * np)) return kChosen;
-  if (steps > 400 * np && !(wpanels <= 12.5 * np && sweeps <= 115 * panels && np > 5.4 * waves)) return kChosen;
+  if (long_pairs && wpanels > 12.5 * np) return kChosen;
   std::sort(cost.begin(), cost.end(), std::greater<double>());
   std::vector<double> busy(waves, 0.);  // a min-heap of the waves' ends
   double total = 0, end = 0;
@@ -828,86 +895,94 @@ static BatchForm batch_form(const Layout& W, const Layout& P, bool halves, int w
     std::push_heap(busy.begin(), busy.end(), std::greater<double>());
   }
   const double use = total / waves / end;
-  return use > (steps > 400 * np ? 0.75 : np <= waves / 2 ? 0.4 : fill < 1.2 ? 0.75 : 0.7) ? kWhole : kChosen;
+  return use > (long_pairs ? 0.75 : np <= waves / 2 ? 0.4 : fill < 1.2 ? 0.75 : 0.7) ? kWhole : kChosen;
 }
 
 bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L,
-                         const Layout* whole, int waves) {
-  std::vector<size_t> split(n);
-  std::iota(split.begin(), split.end(), 0);
+                         const Layout* unsplit, int waves) {
+  // Panel pairs: neighbours by size (the panels of the common grid, then the
+  // slices; the largest first), or each triplet's own two halves, whichever the
+  // times above make shorter.
   std::vector<AxisChoice> ax(n);
   for (size_t t = 0; t < n; ++t) ax[t] = choose_axes_panels(lens + 3 * t);
-
-  // Panel pairs: neighbours by size, or each triplet's own two halves,
-  // whichever the times above make shorter.
-  Layout P, H;
-  bool have_p = false, have_h = false;
-  {
-    std::vector<TripletDesc> d;
-    // By the panels of the common grid, then by the slices.
-    const auto key = [&](size_t t) {
-      const uint32_t* l = lens + 3 * t;
-      const uint32_t pj = l[ax[t].perm[1]] / kPkPanel + 1, pk = l[ax[t].perm[2]] / kPkPanel + 1;
-      return std::make_tuple(pj * pk, pj, l[ax[t].perm[0]]);
-    };
-    std::stable_sort(split.begin(), split.end(), [&](size_t a, size_t b) { return key(a) > key(b); });
-    for (size_t q = 0; q < n + n % 2; ++q) {
-      const size_t t = split[std::min(q, n - 1)];
-      TripletDesc e{};
-      for (int k = 0; k < 3; ++k) {
-        e.off[k] = off[3 * t + ax[t].perm[k]];
-        e.len[k] = lens[3 * t + ax[t].perm[k]];
-      }
-      e.out = (uint32_t)t;
-      d.push_back(e);
+  const std::vector<uint32_t> order = sorted_by(n, [&](size_t t) {
+    const uint32_t* l = lens + 3 * t;
+    const uint32_t pj = l[ax[t].perm[1]] / kPkPanel + 1, pk = l[ax[t].perm[2]] / kPkPanel + 1;
+    return SortKey{{~((uint64_t)pj * pk), ~((uint64_t)pj << 32 | l[ax[t].perm[0]]), 0}};
+  });
+  std::vector<TripletDesc> P;
+  P.reserve(n + 1);
+  for (size_t q = 0; q < n + n % 2; ++q) {
+    const size_t t = order[std::min(q, n - 1)];
+    TripletDesc e{};
+    for (int k = 0; k < 3; ++k) {
+      e.off[k] = off[3 * t + ax[t].perm[k]];
+      e.len[k] = lens[3 * t + ax[t].perm[k]];
     }
-    have_p = pair_panel_layout(d, sc, false, &P);
+    e.out = (uint32_t)t;
+    P.push_back(e);
   }
-  {
-    std::vector<TripletDesc> d;
-    uint64_t ints = 0;
-    uint32_t chunks = 0;
-    for (size_t t : split) {
+  PkTime ht;
+  for (size_t t = 0; t < n; ++t) {
+    const uint32_t* l = lens + 3 * t;
+    int o[3];
+    half_order(l, o);
+    ht.add(l[o[0]] - l[o[0]] / 2, l[o[1]], l[o[2]]);
+  }
+  // (The halves' estimate leaves out their second start per panel and their
+  // meeting: measured, they had to be ahead by 3 % on single waves, 25 % on wave
+  // pairs. 16 triplets of 800-1200 residues: 2.84 ms by halves, 3.10 in pairs;
+  // four of 1000: 1.27 and 1.11; 2000 of 100-400: 8.5 and 6.6.)
+  const PkTime pt = pk_panel_time(P);
+  PanelValues vp, vh;
+  const bool have_p = panel_values(P, sc, false, &vp);
+  bool use_h = !have_p || std::min(ht.single_us() * 1.03, ht.wave_pair_us() * 1.25) <
+                              std::min(pt.single_us(), pt.wave_pair_us());
+  Layout Q;
+  std::vector<TripletDesc> H;
+  if (use_h) {
+    uint64_t chunks = 0;
+    H.reserve(2 * n);
+    Q.boxes.reserve(n);
+    for (size_t t : order) {
       TripletDesc h[2];
       SplitDesc box;
       half_descs(lens + 3 * t, off + 3 * t, h, &box);
       h[0].out = h[1].out = box.out = (uint32_t)t;
       const uint64_t cells = (uint64_t)box.rows * box.cols;
-      box.fwd = ints;
-      box.bwd = ints + cells;
-      box.chunk0 = chunks;
+      box.fwd = Q.plane_ints;
+      box.bwd = Q.plane_ints + cells;
+      box.chunk0 = (uint32_t)chunks;
       box.nchunk = (uint32_t)((cells + kSplitChunk - 1) / kSplitChunk);
-      H.plane_off.push_back(box.fwd);
-      H.plane_off.push_back(box.bwd);
-      H.chunk_box.insert(H.chunk_box.end(), box.nchunk, (uint32_t)H.boxes.size());
-      H.boxes.push_back(box);
-      ints += 2 * cells;
+      Q.boxes.push_back(box);
+      Q.plane_ints += 2 * cells;
       chunks += box.nchunk;
-      d.insert(d.end(), h, h + 2);
+      H.insert(H.end(), h, h + 2);
     }
-    H.plane_ints = ints;
-    H.halves = true;
-    have_h = pair_panel_layout(d, sc, true, &H);
+    use_h = chunks <= INT32_MAX && panel_values(H, sc, true, &vh);
+    if (!use_h && !have_p) return false;
   }
-  if (!have_p && !have_h) return false;
-  // (The halves' estimate leaves out their second start per panel and their
-  // meeting: measured, they had to be ahead by 3 % on single waves, 25 % on wave
-  // pairs. 16 triplets of 800-1200 residues: 2.84 ms by halves, 3.10 in pairs;
-  // four of 1000: 1.27 and 1.11; 2000 of 100-400: 8.5 and 6.6.)
-  bool use_h = have_h;
-  if (have_h && have_p) {
-    const PkTime h = pk_panel_time(H), p = pk_panel_time(P);
-    use_h = std::min(h.single_us * 1.03, h.wave_pair_us * 1.25) < std::min(p.single_us, p.wave_pair_us);
-  }
-  if (whole && have_p) {
-    const BatchForm form = batch_form(*whole, P, use_h, waves);
+  if (unsplit && have_p) {
+    Layout W;
+    const BatchForm form = batch_form(P, use_h, *unsplit, sc, waves, &W);
     if (form == kWhole) {
-      *L = *whole;
+      *L = std::move(W);
       return true;
     }
     if (form == kPairs) use_h = false;
   }
-  Layout& Q = use_h ? H : P;
+  if (use_h) {
+    Q.halves = true;
+    for (const SplitDesc& box : Q.boxes) {
+      Q.plane_off.push_back(box.fwd);
+      Q.plane_off.push_back(box.bwd);
+      Q.chunk_box.insert(Q.chunk_box.end(), box.nchunk, (uint32_t)(&box - Q.boxes.data()));
+    }
+  } else {
+    Q.boxes.clear();
+    Q.plane_ints = 0;
+  }
+  if (!panel_jobs(std::move(use_h ? H : P), sc, use_h, use_h ? vh : vp, &Q)) return false;
   Q.cells = L->cells;
   Q.engine = L->engine;  // (reported: which triplets the split rule of the options calls split)
   *L = std::move(Q);
@@ -1023,15 +1098,24 @@ trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
   L->cells = cells;
   L->face_stride = (stride + 63) / 64 * 64;
   L->pool_ints = pool;
+  L->packed = false;
+
+  // A batch of packed panel jobs needs nothing of the int32 job queue. (Whole
+  // pairs are looked at where the split rule splits none of the batch.)
+  const bool default_shape = (o.tile_rows == 0 || o.tile_rows == 4) && (o.tile_cols == 0 || o.tile_cols == 4) &&
+                             (o.waves_per_simd == 0 || o.waves_per_simd == 2) && o.lane_exchange != 2 && o.staging != 2;
+  const bool any_shape = o.tile_rows || o.tile_cols || o.waves_per_simd || o.lane_exchange || o.staging;
+  if (packed_panels && !planes && n > 1 && o.engine == -1 && !o.grid && ks.group == 1 &&
+      (o.packed == 2 ? default_shape : o.packed == 0 && !any_shape) &&
+      packed_batch_layout(lens, off, n, sc, L, L->modes == 1 ? L : nullptr, std::max(4, waves_hint)))
+    return TRIOSEQ_OK;
 
   // Job order: split triplets' panels first, by anti-diagonal d = pj + pk
   // across all split triplets (largest first within a diagonal), so every
   // panel comes after the panels it reads from and several split triplets
   // fill their pipelines together; then whole triplets longest first so the
   // queue drains with short ones.
-  std::vector<size_t> idx(n);
-  std::iota(idx.begin(), idx.end(), 0);
-  std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+  const std::vector<uint32_t> idx = sorted_by(n, [&](size_t t) { return SortKey{{~cost[t], 0, 0}}; });
   L->jobs.clear();
   L->jobs.reserve(n + panels);
   uint32_t diagonals = 0;
@@ -1056,17 +1140,6 @@ trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
   // Packed pairs when asked for (any lane tile a packed kernel exists for),
   // or by default when the tile is left to the library (4 x 4, two waves per
   // SIMD); the batch keeps int32 lanes when it does not qualify (pair_up).
-  L->packed = false;
-  const bool default_shape = (o.tile_rows == 0 || o.tile_rows == 4) && (o.tile_cols == 0 || o.tile_cols == 4) &&
-                             (o.waves_per_simd == 0 || o.waves_per_simd == 2) && o.lane_exchange != 2 && o.staging != 2;
-  const bool any_shape = o.tile_rows || o.tile_cols || o.waves_per_simd || o.lane_exchange || o.staging;
-  if (packed_panels && !planes && n > 1 && o.engine == -1 && !o.grid && ks.group == 1 &&
-      (o.packed == 2 ? default_shape : o.packed == 0 && !any_shape)) {
-    // (Whole pairs exist where the split rule splits none of the batch.)
-    Layout whole = *L;
-    const bool pairs = pair_up(&whole, sc, KernelShape{4, 4, 2});
-    if (packed_batch_layout(lens, off, n, sc, L, pairs ? &whole : nullptr, std::max(4, waves_hint))) return TRIOSEQ_OK;
-  }
   if (o.packed == 2) {
     KernelShape pks{o.tile_rows ? o.tile_rows : 4, o.tile_cols ? o.tile_cols : 4,
                     o.waves_per_simd ? o.waves_per_simd : 2};

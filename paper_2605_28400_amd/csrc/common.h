@@ -127,11 +127,11 @@ bool self_pair(int kind, const uint32_t* lens);
 bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 bool packed_self_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 // Lays out a batch as packed panel jobs of pairs: neighbours by size, or the
-// halves of every triplet. False if a value could leave the 16-bit range. whole:
-// the batch as whole pairs, taken where they are faster on that many waves (null
-// if there is no such form).
+// halves of every triplet. False if a value could leave the 16-bit range.
+// unsplit (may be L itself): the triplets of a batch that the split rule leaves
+// whole; it becomes whole pairs where those are faster on that many waves.
 bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L,
-                         const Layout* whole = nullptr, int waves = 0);
+                         const Layout* unsplit = nullptr, int waves = 0);
 // Pairs per workgroup of panel-only plans unless the options say otherwise.
 constexpr int kDefaultPanelGroup = 1;
 // Lane exchange (KernelShape::xch) unless the options say otherwise.

@@ -84,3 +84,27 @@ def test_only_short_lone_triplets_of_the_other_kinds_pair_with_themselves(probe)
     for kind in (ts.GLOBAL, ts.LOCAL):
         for lens, pair in (((127, 120, 126), 1), ((128, 120, 126), 0), ((20000, 20, 20), 0), ((1000, 900, 950), 0)):
             assert probe.probe_lone((ctypes.c_uint32 * 3)(*lens), kind) >> 1 == pair
+
+
+def descriptors(probe, lens, sc=None):
+    lens = np.ascontiguousarray(np.asarray(lens, dtype=np.uint32).reshape(-1))
+    info = np.zeros(len(FIELDS), dtype=np.int64)
+    desc = np.zeros((2 * lens.size, 7), dtype=np.int64)
+    probe.probe_layout(lens.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(lens.size // 3),
+                       ctypes.byref(sc or ts.scoring()), info.ctypes.data_as(ctypes.c_void_p),
+                       desc.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(len(desc)))
+    got = dict(zip(FIELDS, info.tolist()))
+    return got, desc[:got["descs"]]
+
+
+@pytest.mark.parametrize("n", [255, 256, 257, 1001, 4096])  # sorted by comparison, or byte by byte
+def test_panel_pairs_are_neighbours_by_panels_then_slices(probe, n):
+    rng = np.random.default_rng(n)
+    lens = rng.integers(150, 250, (n, 3))
+    got, desc = descriptors(probe, lens)
+    assert got["modes"] == PK_PANEL and not got["halves"] and got["descs"] == n + n % 2
+    pj, pk = desc[:, 1] // 32 + 1, desc[:, 2] // 32 + 1
+    keys = list(zip((pj * pk).tolist(), pj.tolist(), desc[:, 0].tolist()))
+    assert keys == sorted(keys, reverse=True)
+    assert sorted(desc[:n, 3].tolist()) == list(range(n)) and desc[-1, 3] == desc[n - 1, 3]
+    assert (np.sort(desc[:n, :3], axis=1) == np.sort(lens[desc[:n, 3]], axis=1)).all()
