@@ -182,10 +182,13 @@ hipError_t launch_fill_packed_sentinel(uint32_t* p, uint64_t n, hipStream_t s);
 constexpr int kPkPanel = 32;  // panel rows and columns
 // Rows of a pair's panel faces, and ints of all its faces: two buffers per
 // panel column of kPkPanel bottom entries a row, two per panel row of kPkPanel
-// right entries and a corner a row, (value, tag) each.
+// right entries and a corner a row, (value, tag) each; one where only the first
+// of two panels writes, none where there is one.
 __host__ __device__ inline uint64_t pk_face_rows(uint32_t n0) { return (face_rows(n0) + 7u) & ~7u; }
+__host__ __device__ inline uint64_t pk_face_buffers(uint64_t panels) { return panels > 2 ? 2 : panels - 1; }
 inline uint64_t pk_pair_ints(uint32_t n0, uint64_t PJ, uint64_t PK) {
-  return 2 * pk_face_rows(n0) * (PK * 2 * kPkPanel + PJ * (2 * kPkPanel + 2));
+  return pk_face_rows(n0) *
+         (pk_face_buffers(PJ) * PK * 2 * kPkPanel + pk_face_buffers(PK) * PJ * (2 * kPkPanel + 2));
 }
 // self: single-wave workgroups that move their own faces, instead of a
 // computing and a memory wave. count: finished

@@ -63,7 +63,8 @@ struct PkPanelLds {
 };
 
 // A panel's faces. A pair has two bottom-face buffers per panel column and two
-// right-face buffers (corner face behind them) per panel row, written in turn:
+// right-face buffers (corner face behind them) per panel row (fewer where a
+// column or row has fewer panels that write), written in turn:
 // a panel reads the one its neighbour wrote and overwrites the one written two
 // panels before. 260 buffers instead of two for each of 4225 panels of a
 // 2048-residue triplet: the faces stay in the caches (1024 x 1000 x 1048: 711
@@ -696,12 +697,14 @@ k_panel_pk(SweepArgs a, uint32_t off, uint32_t kc, uint32_t count) {
     const int pj = (int)(p / (uint32_t)PK), pk = (int)(p % (uint32_t)PK);
     int* pool = a.pface + ta.face_off;
     PkPanelIO io;
+    // (The buffer a panel at the edge would read or write may not exist: it is
+    // an empty resource then.)
     const uint64_t cs = rows * (2 * kPkPanel), rs = rows * (2 * kPkPanel + 2);
-    int* rpool = pool + (uint64_t)PK * 2 * cs;
-    io.col_in = pool + (uint64_t)(2 * pk + ((pj & 1) ^ 1)) * cs;
-    io.col_out = pool + (uint64_t)(2 * pk + (pj & 1)) * cs;
-    io.row_in = rpool + (uint64_t)(2 * pj + ((pk & 1) ^ 1)) * rs;
-    io.row_out = rpool + (uint64_t)(2 * pj + (pk & 1)) * rs;
+    int* rpool = pool + pk_face_buffers((uint64_t)PJ) * (uint64_t)PK * cs;
+    io.col_in = pool + (uint64_t)(((pj & 1) ^ 1) * PK + pk) * cs;
+    io.col_out = pool + (uint64_t)((pj & 1) * PK + pk) * cs;
+    io.row_in = rpool + (uint64_t)(((pk & 1) ^ 1) * PJ + pj) * rs;
+    io.row_out = rpool + (uint64_t)((pk & 1) * PJ + pj) * rs;
     io.has_top = pj > 0;
     io.has_left = pk > 0;
     io.bot = pj + 1 < PJ;

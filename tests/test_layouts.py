@@ -108,3 +108,20 @@ def test_panel_pairs_are_neighbours_by_panels_then_slices(probe, n):
     assert keys == sorted(keys, reverse=True)
     assert sorted(desc[:n, 3].tolist()) == list(range(n)) and desc[-1, 3] == desc[n - 1, 3]
     assert (np.sort(desc[:n, :3], axis=1) == np.sort(lens[desc[:n, 3]], axis=1)).all()
+
+
+@pytest.mark.parametrize("lens,columns,rows", [((90, 31, 31), 0, 0), ((200, 40, 31), 0, 1), ((200, 31, 40), 1, 0),
+                                               ((200, 40, 40), 1, 1), ((200, 64, 40), 1, 2), ((200, 95, 95), 2, 2)])
+def test_a_pair_has_only_the_face_buffers_its_panels_write(probe, lens, columns, rows):
+    # Halves of a lone pair of equal triplets: two pairs in one group. columns:
+    # bottom-face buffers a panel column has, rows: right-face buffers a panel row.
+    got, desc = descriptors(probe, [lens] * 2)
+    assert got["modes"] == PK_PANEL and got["halves"]
+    want = 0
+    for n0, n1, n2 in desc[::2, :3].tolist():
+        n0 = max(n0, lens[0] - n0)
+        face_rows = (n0 + 1 + 14 + 16 + 7) // 8 * 8
+        pj, pk = n1 // 32 + 1, n2 // 32 + 1
+        assert (min(pj - 1, 2), min(pk - 1, 2)) in ((columns, rows), (rows, columns))
+        want += face_rows * (min(pj - 1, 2) * pk * 64 + min(pk - 1, 2) * pj * 66)
+    assert got["pool"] == want
