@@ -899,7 +899,7 @@ static BatchForm batch_form(const std::vector<TripletDesc>& P, bool halves, cons
 }
 
 bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L,
-                         const Layout* unsplit, int waves) {
+                         PackedPanels allow, const Layout* unsplit, int waves) {
   // Panel pairs: neighbours by size (the panels of the common grid, then the
   // slices; the largest first), or each triplet's own two halves, whichever the
   // times above make shorter.
@@ -936,8 +936,10 @@ bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, co
   const PkTime pt = pk_panel_time(P);
   PanelValues vp, vh;
   const bool have_p = panel_values(P, sc, false, &vp);
-  bool use_h = !have_p || std::min(ht.single_us() * 1.03, ht.wave_pair_us() * 1.25) <
-                              std::min(pt.single_us(), pt.wave_pair_us());
+  bool use_h = allow == PackedPanels::kAny &&
+               (!have_p || std::min(ht.single_us() * 1.03, ht.wave_pair_us() * 1.25) <
+                               std::min(pt.single_us(), pt.wave_pair_us()));
+  if (!use_h && !have_p) return false;
   Layout Q;
   std::vector<TripletDesc> H;
   if (use_h) {
@@ -959,7 +961,7 @@ bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, co
       chunks += box.nchunk;
       H.insert(H.end(), h, h + 2);
     }
-    use_h = chunks <= INT32_MAX && panel_values(H, sc, true, &vh);
+    use_h = chunks <= INT32_MAX && Q.plane_ints * 4 <= kHalvesBytes && panel_values(H, sc, true, &vh);
     if (!use_h && !have_p) return false;
   }
   if (unsplit && have_p) {
@@ -991,7 +993,7 @@ bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, co
 
 trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
                             const trioseq_scoring& sc, const trioseq_plan_options& o, int waves_hint,
-                            Layout* L, bool planes, bool packed_panels) {
+                            Layout* L, bool planes, PackedPanels panels_allowed) {
   if (n && !lens) return fail(TRIOSEQ_ERR_INVALID_ARG, "lens is NULL");
   if (n > (size_t)INT32_MAX) return fail(TRIOSEQ_ERR_TOO_LARGE, "too many triplets");
   trioseq_status st = validate_scoring(&sc);
@@ -1105,9 +1107,9 @@ trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
   const bool default_shape = (o.tile_rows == 0 || o.tile_rows == 4) && (o.tile_cols == 0 || o.tile_cols == 4) &&
                              (o.waves_per_simd == 0 || o.waves_per_simd == 2) && o.lane_exchange != 2 && o.staging != 2;
   const bool any_shape = o.tile_rows || o.tile_cols || o.waves_per_simd || o.lane_exchange || o.staging;
-  if (packed_panels && !planes && n > 1 && o.engine == -1 && !o.grid && ks.group == 1 &&
+  if (panels_allowed != PackedPanels::kNone && !planes && n > 1 && o.engine == -1 && !o.grid && ks.group == 1 &&
       (o.packed == 2 ? default_shape : o.packed == 0 && !any_shape) &&
-      packed_batch_layout(lens, off, n, sc, L, L->modes == 1 ? L : nullptr, std::max(4, waves_hint)))
+      packed_batch_layout(lens, off, n, sc, L, panels_allowed, L->modes == 1 ? L : nullptr, std::max(4, waves_hint)))
     return TRIOSEQ_OK;
 
   // Job order: split triplets' panels first, by anti-diagonal d = pj + pk
@@ -1314,9 +1316,10 @@ bool half_split_choice(const uint32_t* lens, const uint64_t* word_off, size_t n,
 
 }  // namespace trioseq
 
-static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* word_off, size_t n,
+// panels: the packed panel jobs a batch may use; left at those it does use.
+static trioseq_status plan_create_with(const uint32_t* lens, const uint64_t* word_off, size_t n,
                                        const trioseq_scoring* scp, const trioseq_plan_options* opts,
-                                       trioseq_plan** out, const PlanMemory* mem = nullptr) {
+                                       trioseq_plan** out, const PlanMemory* mem, PackedPanels* panels) {
   if (!out) return fail(TRIOSEQ_ERR_INVALID_ARG, "plan_create: plan output is NULL");
   if (!scp) return fail(TRIOSEQ_ERR_INVALID_ARG, "plan_create: scoring is NULL");
   trioseq_plan_options o{-1, 0, 0, 0, 0, 0};
@@ -1332,8 +1335,7 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   // layout is redone if the device's size changes the split rule's hint.
   Layout L;
   int hint = 256 * kWavesPerCuHint;
-  const bool panels = mem == nullptr;  // (a carved plan keeps to the int32 layout's memory limits)
-  trioseq_status st = build_layout(lens, word_off, n, *scp, o, hint, &L, false, panels);
+  trioseq_status st = build_layout(lens, word_off, n, *scp, o, hint, &L, false, *panels);
   if (st != TRIOSEQ_OK) return st;
   // A lone global or local triplet under the automatic options is scored by
   // halves (local: the best of the two halves' own bests and of the paths
@@ -1347,9 +1349,11 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   if (half || dp.cus * kWavesPerCuHint != hint) {
     hint = dp.cus * kWavesPerCuHint;
     st = half ? build_layout(hs.lens, hs.offs, 2, *scp, ho, hint, &L, true)
-              : build_layout(lens, word_off, n, *scp, o, hint, &L, false, panels);
+              : build_layout(lens, word_off, n, *scp, o, hint, &L, false, *panels);
     if (st != TRIOSEQ_OK) return st;
   }
+  if (n < 2 || L.modes != kModePkPanel) *panels = PackedPanels::kNone;
+  else if (!L.halves) *panels = PackedPanels::kPairs;
   // A batch carved from a region whose pool cannot hold its split triplets'
   // faces sweeps every triplet whole instead (same scores, no face pool).
   if (mem && !half && n > 1 && o.engine == -1 && L.pool_ints * sizeof(int) > mem->pool_bytes) {
@@ -1584,6 +1588,23 @@ static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* wor
   }
   *out = p;
   return TRIOSEQ_OK;
+}
+
+// A batch whose packed panel jobs do not fit the device's free memory takes the
+// next smaller form: pairs instead of halves (whose planes are all held at
+// once), then whole triplets.
+static trioseq_status plan_create_impl(const uint32_t* lens, const uint64_t* word_off, size_t n,
+                                       const trioseq_scoring* scp, const trioseq_plan_options* opts,
+                                       trioseq_plan** out, const PlanMemory* mem = nullptr) {
+  // (A carved plan keeps to the int32 layout's memory limits.)
+  PackedPanels panels = mem ? PackedPanels::kNone : PackedPanels::kAny;
+  for (;;) {
+    PackedPanels used = panels;
+    const trioseq_status st = plan_create_with(lens, word_off, n, scp, opts, out, mem, &used);
+    if (st != TRIOSEQ_ERR_NOMEM || used == PackedPanels::kNone) return st;
+    (void)hipGetLastError();  // the failed allocation's
+    panels = used == PackedPanels::kAny ? PackedPanels::kPairs : PackedPanels::kNone;
+  }
 }
 
 namespace trioseq {

@@ -112,10 +112,11 @@ struct Layout {
 // Touches no device state.
 // waves_hint: wavefronts the launch will have (for the split rule).
 // planes: the layout of a traceback plane run (axes kept as given, S0 swept).
-// packed_panels: packed panel jobs may be used (packed_batch_layout).
+// panels: which packed panel jobs may be used (packed_batch_layout).
+enum class PackedPanels { kNone, kPairs, kAny };
 trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
                             const trioseq_scoring& sc, const trioseq_plan_options& o, int waves_hint,
-                            Layout* L, bool planes = false, bool packed_panels = false);
+                            Layout* L, bool planes = false, PackedPanels panels = PackedPanels::kNone);
 // Lays out pairs (desc entries 2p, 2p + 1, axes assigned) as packed panel jobs
 // in dependency order; false if a pair's values could leave the 16-bit range
 // under this scoring.
@@ -127,11 +128,15 @@ bool self_pair(int kind, const uint32_t* lens);
 bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 bool packed_self_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 // Lays out a batch as packed panel jobs of pairs: neighbours by size, or the
-// halves of every triplet. False if a value could leave the 16-bit range.
+// halves of every triplet (allow kAny, and while their planes and faces take at
+// most kHalvesBytes, a quarter of the device's memory: the pairs' faces are
+// bounded, the planes of all triplets are held at once). False if a value could
+// leave the 16-bit range.
 // unsplit (may be L itself): the triplets of a batch that the split rule leaves
 // whole; it becomes whole pairs where those are faster on that many waves.
+constexpr uint64_t kHalvesBytes = 72ull << 30;
 bool packed_batch_layout(const uint32_t* lens, const uint64_t* off, size_t n, const trioseq_scoring& sc, Layout* L,
-                         const Layout* unsplit = nullptr, int waves = 0);
+                         PackedPanels allow = PackedPanels::kAny, const Layout* unsplit = nullptr, int waves = 0);
 // Pairs per workgroup of panel-only plans unless the options say otherwise.
 constexpr int kDefaultPanelGroup = 1;
 // Lane exchange (KernelShape::xch) unless the options say otherwise.

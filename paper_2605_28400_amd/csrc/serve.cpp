@@ -197,7 +197,13 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
         L.jobs.size() <= sl.h_jobs_cap && L.desc.size() <= sl.h_desc_cap && meet_bytes(L) <= sl.h_meet_cap &&
         n <= sl.max_batch)
       break;
-    // A slot holds at least the int32 layout of any one request.
+    // The planes of halves grow with the round, the faces of pairs do not. A slot
+    // holds at least the int32 layout of any one request.
+    if (packed && n > 1 && L.halves &&
+        packed_batch_layout(lens.data(), offs.data(), n, s->sc, &L, PackedPanels::kPairs)) {
+      if (!alone) L.pk_self = true;
+      continue;
+    }
     if (packed && n == 1) {
       packed = false;
       continue;

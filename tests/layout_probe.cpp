@@ -6,17 +6,18 @@
 
 using namespace trioseq;
 
-// The layout of a plan (default options, packed panel jobs allowed). info:
+// The layout of a plan (default options, the packed panel jobs allowed: 0 none, 1
+// pairs, 2 any). info:
 // [0] status, [1] modes, [2] packed, [3] halves, [4] longest sweep, [5] panels
 // reported, [6] jobs, [7] descriptors, [8] face pool ints, [9] plane ints,
 // [10] single-wave workgroups, [11] engine reported. desc (7 per descriptor,
 // up to cap: lens, out, start of the sweep, direction, longest sweep's
 // sequence) may be null.
-extern "C" void probe_layout(const uint32_t* lens, size_t n, const trioseq_scoring* sc, int64_t* info, int64_t* desc,
-                             size_t cap) {
+extern "C" void probe_layout(const uint32_t* lens, size_t n, const trioseq_scoring* sc, int panels, int64_t* info,
+                             int64_t* desc, size_t cap) {
   const trioseq_plan_options o{-1, 0, 0, 0, 0, 0};
   Layout L;
-  info[0] = build_layout(lens, nullptr, n, *sc, o, 256 * kWavesPerCuHint, &L, false, true);
+  info[0] = build_layout(lens, nullptr, n, *sc, o, 256 * kWavesPerCuHint, &L, false, (PackedPanels)panels);
   info[1] = L.modes;
   info[2] = L.packed;
   info[3] = L.halves;

@@ -28,11 +28,12 @@ def probe(tmp_path_factory):
     return ctypes.CDLL(out)
 
 
-def layout(probe, lens, sc=None):
+def layout(probe, lens, sc=None, panels=2):
     lens = np.ascontiguousarray(np.asarray(lens, dtype=np.uint32).reshape(-1))
     info = np.zeros(len(FIELDS), dtype=np.int64)
     probe.probe_layout(lens.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(lens.size // 3),
-                       ctypes.byref(sc or ts.scoring()), info.ctypes.data_as(ctypes.c_void_p), None, ctypes.c_size_t(0))
+                       ctypes.byref(sc or ts.scoring()), ctypes.c_int(panels), info.ctypes.data_as(ctypes.c_void_p),
+                       None, ctypes.c_size_t(0))
     return dict(zip(FIELDS, info.tolist()))
 
 
@@ -91,7 +92,7 @@ def descriptors(probe, lens, sc=None):
     info = np.zeros(len(FIELDS), dtype=np.int64)
     desc = np.zeros((2 * lens.size, 7), dtype=np.int64)
     probe.probe_layout(lens.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(lens.size // 3),
-                       ctypes.byref(sc or ts.scoring()), info.ctypes.data_as(ctypes.c_void_p),
+                       ctypes.byref(sc or ts.scoring()), ctypes.c_int(2), info.ctypes.data_as(ctypes.c_void_p),
                        desc.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(len(desc)))
     got = dict(zip(FIELDS, info.tolist()))
     return got, desc[:got["descs"]]
@@ -125,3 +126,19 @@ def test_a_pair_has_only_the_face_buffers_its_panels_write(probe, lens, columns,
         assert (min(pj - 1, 2), min(pk - 1, 2)) in ((columns, rows), (rows, columns))
         want += face_rows * (min(pj - 1, 2) * pk * 64 + min(pk - 1, 2) * pj * 66)
     assert got["pool"] == want
+
+
+def test_halves_keep_to_a_quarter_of_the_device(probe):
+    # Independent lengths, which halves suit: their planes (two of rows x columns
+    # for every triplet, all at once) grow with the batch, the pairs' faces do not.
+    rng = np.random.default_rng(5)
+    lens = rng.integers(200, 2401, (12000, 3))
+    few = layout(probe, lens[:600])
+    assert few["halves"] == 1 and few["planes"] * 4 > 4e9
+    many = layout(probe, lens)
+    assert many["modes"] == PK_PANEL and many["halves"] == 0 and many["planes"] == 0
+    assert many["pool"] * 4 < 64e9
+    # What a plan or a served round falls back to where even the few do not fit.
+    pairs = layout(probe, lens[:600], panels=1)
+    assert pairs["modes"] == PK_PANEL and pairs["halves"] == 0 and pairs["planes"] == 0
+    assert layout(probe, lens[:600], panels=0)["modes"] != PK_PANEL
