@@ -113,6 +113,16 @@ namespace {
 
 uint64_t align256(uint64_t v) { return (v + 255) / 256 * 256; }
 
+// Rounds that do not fit their slot in packed lanes are halved down to this many
+// requests before int32 lanes are tried.
+constexpr size_t kPackedRound = 64;
+// A slot's tagged region holds the faces of a round's panel jobs: at least those
+// of the largest request in int32 lanes, else a quarter of the slot up to this
+// (8192 triplets of 100-400 residues need 3.3 GB). Sized for that one request
+// alone it made rounds of short requests tiny: 3000 requests of 30-120 residues
+// at max_len 128 took 145 ms.
+constexpr uint64_t kTaggedBytes = 4ull << 30;
+
 // Bytes of a round's meeting tables (boxes, plane offsets, chunks, counters).
 uint64_t meet_bytes(const Layout& L) {
   return L.halves ? L.boxes.size() * (sizeof(SplitDesc) + 20) + L.chunk_box.size() * 4 : 0;
@@ -198,13 +208,14 @@ trioseq_status launch_round(trioseq_server* s, Slot& sl, std::vector<Request>& b
         n <= sl.max_batch)
       break;
     // The planes of halves grow with the round, the faces of pairs do not. A slot
-    // holds at least the int32 layout of any one request.
+    // holds at least the int32 layout of any one request; a round is not made
+    // much smaller for packed lanes than it would be without them.
     if (packed && n > 1 && L.halves &&
         packed_batch_layout(lens.data(), offs.data(), n, s->sc, &L, PackedPanels::kPairs)) {
       if (!alone) L.pk_self = true;
       continue;
     }
-    if (packed && n == 1) {
+    if (packed && n <= kPackedRound) {
       packed = false;
       continue;
     }
@@ -433,9 +444,8 @@ static trioseq_status trioseq_serve_create_body(const trioseq_serve_config* cfg,
   }
   uint64_t budget = cfg->max_device_bytes ? cfg->max_device_bytes : s->dp.hbm_bytes / 4;
   const uint64_t per_slot = budget / s->cfg.max_inflight / 256 * 256;
-  // The largest single request must fit a slot on its own. A slot's tagged
-  // region is sized for that request's panel faces; the rest of the slot
-  // budget is its arena.
+  // The largest single request must fit a slot on its own, its panel faces in the
+  // tagged region (see kTaggedBytes); the rest of the slot budget is its arena.
   uint64_t tagged_bytes = 0;
   {
     const uint32_t m = cfg->max_len;
@@ -450,11 +460,17 @@ static trioseq_status trioseq_serve_create_body(const trioseq_serve_config* cfg,
       return st;
     }
     tagged_bytes = align256(L.pool_ints * 4);
-    if (tagged_bytes >= per_slot ||
-        arena_need(L, 3ull * ((m + 15) / 16), grid) > per_slot - tagged_bytes) {
+    const uint64_t arena = arena_need(L, 3ull * ((m + 15) / 16), grid);
+    if (tagged_bytes >= per_slot || arena > per_slot - tagged_bytes) {
       delete s;
       return fail(TRIOSEQ_ERR_TOO_LARGE, "serve_create: max_device_bytes too small for max_len");
     }
+    bool packs = true;  // (a negative term keeps every round in int32 lanes)
+    for (const auto& row : sc->sub)
+      for (int32_t v : row) packs = packs && v - 2 * sc->gap >= 0;
+    if (packs)
+      tagged_bytes = std::max(tagged_bytes,
+                              std::min<uint64_t>({kTaggedBytes, per_slot / 4, per_slot - arena}) / 256 * 256);
   }
   auto bail = [&](hipError_t e, const char* what) {
     fail_hip(e, what);

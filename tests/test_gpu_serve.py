@@ -287,3 +287,24 @@ def test_wait_that_gives_up_never_reports_a_wrong_score(gpu):
     assert served["status"] != 0 or served["score"] == want, served
     # Back at the default bound, the same triplet scores correctly.
     assert ts.score(t) == want
+
+
+@pytest.mark.parametrize("kind,okind", [(ts.GLOBAL, oracle.GLOBAL), (ts.SEMI_GLOBAL, oracle.SEMI_GLOBAL),
+                                        (ts.LOCAL, oracle.LOCAL)], ids=["global", "semi-global", "local"])
+@pytest.mark.parametrize("mib", [6, 24, 400])
+def test_rounds_that_do_not_fit_their_slot(gpu, kind, okind, mib):
+    # One slot whose memory holds the largest request's int32 faces (3.5 MB) and
+    # little more: rounds take pairs for halves, fewer requests, int32 lanes.
+    reqs = mixed_requests(41, 250, 8, 150)
+    rng = synth.rng_for(42)
+    reqs += [tuple(synth.uniform_seq(rng, m) for m in n) for n in ((160, 160, 160), (160, 3, 160), (0, 150, 0))]
+    want = oracle.score_batch(reqs, kind=okind)
+    say(f"small slot kind={kind} MiB={mib}")
+    srv = ts.Server(max_len=160, sc=ts.scoring(kind=kind), max_device_bytes=mib << 20, max_inflight=1)
+    ids = [srv.submit(t) for t in reqs]
+    res = [srv.wait(i, timeout_s=60) for i in ids]
+    rounds = srv.stats()["rounds"]
+    srv.close()
+    assert all(r["status"] == 0 for r in res)
+    assert [r["score"] for r in res] == want.tolist()
+    assert rounds >= 2 or mib == 400
