@@ -78,13 +78,14 @@ Split split_of(const Box& b) {
 }
 
 // Takes a level's split points (out[3q] = score, out[3q + 1], out[3q + 2] = the
-// cell of box q's middle slice): the boxes' halves go to `next`.
+// cell of box q's middle slice, negative if the level's sweep gave up): the boxes' halves go to `next`.
 // root_score[t] is set when the box is triplet t's root (its first split).
 trioseq_status take_splits(const std::vector<Box>& boxes, const int* out, std::vector<char>& split_seen,
                            std::vector<int32_t>& root_score, std::vector<Box>& next) {
   for (size_t q = 0; q < boxes.size(); ++q) {
     const Box& b = boxes[q];
     const Split sp = split_of(b);
+    if (out[3 * q + 1] < 0) return fail(TRIOSEQ_ERR_DEVICE, "align: a wait of the sweep gave up");
     const uint32_t p = (uint32_t)out[3 * q + 1], pc = (uint32_t)out[3 * q + 2];
     if (p > b.hi[sp.r] - b.lo[sp.r] || pc > b.hi[sp.c] - b.lo[sp.c])
       return fail(TRIOSEQ_ERR_DEVICE, "align: split point outside its box");
@@ -202,7 +203,7 @@ trioseq_status split_level_packed(PlaneWorkspace& ws, const std::vector<Box>& bo
   a.plane_off = (const uint64_t*)(t + at[2]);
   AL(launch_panel_pk(kGlobal, L.pk_self, a, L.pk_base, L.pk_kc, L.pk_reuse, grid, s));
   AL(launch_split(as<int>(ws.plane), (const SplitDesc*)(t + at[3]), (uint32_t)nb, (const uint32_t*)(t + at[4]),
-                  (uint32_t)nc, as<int>(ws.partial), ws.d_out, s));
+                  (uint32_t)nc, as<int>(ws.partial), ctl + 1, ws.d_out, s));
   // The level's only wait: its split points are needed to lay out the next.
   AL(hipStreamSynchronize(s));
 #undef AL
@@ -264,7 +265,8 @@ trioseq_status split_level(PlaneWorkspace& ws, const std::vector<Box>& boxes,
       (e = hipMemcpyAsync(ws.chunk_box.p, chunk_box.data(), nchunks * 4, hipMemcpyHostToDevice, s)) !=
           hipSuccess ||
       (e = launch_split((const int*)ws.plane.p, as<SplitDesc>(ws.sd), (uint32_t)nb, as<uint32_t>(ws.chunk_box),
-                        (uint32_t)nchunks, as<int>(ws.partial), as<int>(ws.split_out), s)) != hipSuccess ||
+                        (uint32_t)nchunks, as<int>(ws.partial), as<int>(ws.ctl) + 1, as<int>(ws.split_out),
+                        s)) != hipSuccess ||
       (e = hipMemcpyAsync(out.data(), ws.split_out.p, 3 * nb * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
       (e = hipStreamSynchronize(s)) != hipSuccess)
     return hip_err(e, "align: split");

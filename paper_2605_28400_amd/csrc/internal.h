@@ -262,10 +262,11 @@ hipError_t launch_gather(const uint32_t* in, const GatherDesc* d, uint32_t n, ui
 hipError_t launch_meet(const SplitDesc* boxes, const uint32_t* chunk_box, uint32_t nchunks, const int* planes,
                        int* partial, const int* err, const int* own, int own_step, int own_base, int* counters,
                        int32_t* out, hipStream_t s);
-// out[3b] = best F + R of box b, out[3b+1], out[3b+2] = its (p, q).
+// out[3b] = best F + R of box b, out[3b+1], out[3b+2] = its (p, q), or -1 if
+// err[0] is set (a wait of the run gave up).
 // chunk_box[c] = the box of chunk c; partial: 2 ints per chunk.
 hipError_t launch_split(const int* planes, const SplitDesc* boxes, uint32_t n, const uint32_t* chunk_box,
-                        uint32_t nchunks, int* partial, int* out, hipStream_t s);
+                        uint32_t nchunks, int* partial, const int* err, int* out, hipStream_t s);
 hipError_t launch_leaf(const LeafArgs& a, hipStream_t s);
 
 inline int panel_rows(const KernelShape& ks) { return kGJ * ks.rj; }

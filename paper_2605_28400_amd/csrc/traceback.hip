@@ -84,9 +84,10 @@ __global__ void __launch_bounds__(256) k_split_part(const int* __restrict__ plan
 }
 
 // Split, stage 2: one wave per box folds its chunks' results (same order:
-// larger value, then smaller index) into out[3b] = best, (p, q).
+// larger value, then smaller index) into out[3b] = best, (p, q); (-1, -1) if a
+// wait of the run gave up, as the planes are then not to be trusted.
 __global__ void __launch_bounds__(64) k_split_final(const SplitDesc* __restrict__ boxes, uint32_t n,
-                                                    const int* __restrict__ partial,
+                                                    const int* __restrict__ partial, const int* __restrict__ err,
                                                     int* __restrict__ out) {
   const uint32_t b = blockIdx.x;
   if (b >= n) return;
@@ -110,9 +111,10 @@ __global__ void __launch_bounds__(64) k_split_final(const SplitDesc* __restrict_
     }
   }
   if (threadIdx.x == 0) {
+    const bool bad = *err != 0;
     out[3 * b] = best;
-    out[3 * b + 1] = (int)(bidx / d.cols);
-    out[3 * b + 2] = (int)(bidx % d.cols);
+    out[3 * b + 1] = bad ? -1 : (int)(bidx / d.cols);
+    out[3 * b + 2] = bad ? -1 : (int)(bidx % d.cols);
   }
 }
 
@@ -323,11 +325,11 @@ hipError_t launch_meet(const SplitDesc* boxes, const uint32_t* chunk_box, uint32
 }
 
 hipError_t launch_split(const int* planes, const SplitDesc* boxes, uint32_t n, const uint32_t* chunk_box,
-                        uint32_t nchunks, int* partial, int* out, hipStream_t s) {
+                        uint32_t nchunks, int* partial, const int* err, int* out, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_split_part, dim3(nchunks), dim3(256), 0, s, planes, boxes, chunk_box, nchunks,
                      partial);
-  hipLaunchKernelGGL(k_split_final, dim3(n), dim3(64), 0, s, boxes, n, partial, out);
+  hipLaunchKernelGGL(k_split_final, dim3(n), dim3(64), 0, s, boxes, n, partial, err, out);
   return hipGetLastError();
 }
 

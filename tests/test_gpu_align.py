@@ -133,3 +133,35 @@ def test_batch_of_length_8(gpu):
     for q in range(0, len(trips), 7):
         check_alignment(trips[q], got[q][0], got[q][1], want=int(want[q]))
     assert [s for _, s in got] == [int(v) for v in want]
+
+
+def test_batch_of_many_boxes_a_level(gpu):
+    # 5000 boxes above the leaf size in the first level, two by two panels each:
+    # more than two groups of halves share the face buffers.
+    rng = np.random.default_rng(68)
+    trips = [synth.mutated_triplet(rng, int(n), 0.1) for n in rng.integers(40, 60, 5000)]
+    say("align batch of 5000 x length 40-59")
+    got = ts.align_batch(trips)
+    want = oracle.score_batch(trips)
+    assert [s for _, s in got] == [int(v) for v in want]
+    for q in range(0, len(trips), 41):
+        check_alignment(trips[q], got[q][0], got[q][1], want=int(want[q]))
+
+
+@pytest.mark.parametrize("scheme", [(1, -1, -2), (1, -3, -1)], ids=["packed", "int32"])
+def test_a_wait_that_gives_up_is_reported(gpu, scheme):
+    # A wait bound of one clock tick: the sweep of the first level gives up, and
+    # the call says so instead of splitting what its planes hold.
+    rng = np.random.default_rng(69)
+    t = synth.mutated_triplet(rng, 300, 0.05, lens=(300, 280, 290))
+    sc = ts.scoring(*scheme)
+    say(f"align wait limit scheme={scheme}")
+    try:
+        ts.set_wait_limit(10)
+        with pytest.raises(ts.TrioseqError, match="gave up"):
+            ts.align(t, sc)
+    finally:
+        ts.set_wait_limit(0)
+    rows, score = ts.align(t, sc)
+    sub = [[scheme[0] if x == y else scheme[1] for y in range(4)] for x in range(4)]
+    assert score == int(oracle.score_batch([t], sub, scheme[2])[0])
