@@ -260,15 +260,15 @@ trioseq_status trioseq_plan_destroy(trioseq_plan* plan);
 typedef struct trioseq_tune_result {
   trioseq_plan_options best; /* options of the fastest accepted configuration */
   double best_ms;            /* its mean time per run */
-  double reference_ms;       /* the reference configuration's (default options) */
+  double reference_ms;       /* the reference configuration's; for one triplet the library defaults' */
   int32_t tried;             /* configurations timed */
   int32_t rejected;          /* configurations whose scores differed from the reference's */
 } trioseq_tune_result;
 
 /* Times candidate configurations on the caller's batch (lens, word_off and
  * d_words as for plans; reps timed runs each, on hip_stream) and returns the
- * fastest one whose scores equal the reference configuration's (the library
- * defaults), score for score (a candidate that differs is rejected and never
+ * fastest one whose scores equal the reference configuration's (4 x 4 tiles,
+ * int32 lanes), score for score (a candidate that differs is rejected and never
  * chosen). Candidates: every lane tile (panel shape) and register budget,
  * the register lane exchange, split factors 2, 8 and 16, strip workgroups,
  * and for one triplet half-split thresholds 128 and 512 and no half split.

@@ -2089,13 +2089,17 @@ static trioseq_status trioseq_autotune_body(const uint32_t* lens, const uint64_t
   if (n == 0) return fail(TRIOSEQ_ERR_INVALID_ARG, "autotune: empty batch");
   if (reps < 1) reps = 1;
   hipStream_t s = (hipStream_t)hip_stream;
-  // Candidates: the reference (library defaults) first, then every lane tile
-  // (the panel a wave owns is 8 x 8 tiles) and register budget, the register
-  // lane exchange, other split factors (which triplets of a batch become
-  // panel jobs), strip workgroups, and for a lone triplet other half-split
-  // thresholds. Options a layout ignores are not tried.
+  // Candidates: the reference in int32 lanes first, then every lane tile (the
+  // panel a wave owns is 8 x 8 tiles) and register budget, the register lane
+  // exchange, other split factors (which triplets of a batch become panel
+  // jobs), strip workgroups, and for a lone triplet other half-split
+  // thresholds. Options a layout ignores are not tried. A lone triplet's
+  // defaults are packed lanes: a candidate of their own, as 16-bit values are
+  // held against 32-bit ones and not the other way round.
   std::vector<trioseq_plan_options> cands;
-  cands.push_back(trioseq_plan_options{-1, 4, 4, 0, 0, 2});
+  cands.push_back(trioseq_plan_options{-1, 4, 4, 0, 0, 2, 0, 0, 0, 0, n == 1 ? 1 : 0});
+  const size_t defaults = n == 1 ? 1 : 0;  // the candidate that plans without options run as
+  if (n == 1) cands.push_back(trioseq_plan_options{-1, 4, 4, 0, 0, 2});
   const int shapes[][3] = {{4, 4, 4}, {8, 4, 2}, {4, 8, 2}};
   for (const auto& sh : shapes) cands.push_back(trioseq_plan_options{-1, sh[0], sh[1], 0, 0, sh[2]});
   if (sc->kind == kGlobal) {
@@ -2159,7 +2163,7 @@ static trioseq_status trioseq_autotune_body(const uint32_t* lens, const uint64_t
         st = fail_hip(e, "autotune");
         break;
       }
-      r.reference_ms = ms;
+      r.reference_ms = ms;  // (of a lone triplet until its defaults agree)
     } else {
       if ((e = hipMemcpy(got.data(), d_out, n * 4, hipMemcpyDeviceToHost)) != hipSuccess) {
         st = fail_hip(e, "autotune");
@@ -2169,13 +2173,14 @@ static trioseq_status trioseq_autotune_body(const uint32_t* lens, const uint64_t
         ++r.rejected;
         continue;
       }
+      if (c == defaults) r.reference_ms = ms;
     }
     if (ms < r.best_ms) {
       r.best_ms = ms;
       r.best = cands[c];
       r.best.tile_rows = info.tile_rows;
       r.best.tile_cols = info.tile_cols;
-      r.best.waves_per_simd = c == 0 ? 0 : cands[c].waves_per_simd;
+      r.best.waves_per_simd = c == defaults ? 0 : cands[c].waves_per_simd;
     }
     if (std::getenv("TRIOSEQ_TUNE_LOG"))
       std::fprintf(stderr, "autotune: %dx%d wpe %d xch %d group %d split %d half %d packed %d staging %d: %.4f ms\n",

@@ -214,3 +214,25 @@ def test_tags_start_over_before_they_leave_31_bits(torch_cuda):
         assert ctl[:4].tolist() == [first, 0, 0, first + step - 1] and first + step - 1 < always
         assert counter[0] == 0 and counter[32] == 0 and counter[64] == 0
         assert (pool[:ints] == (0 if wraps else last)).all() and (pool[ints:] == last).all()
+
+
+@pytest.mark.parametrize("kind", KINDS, ids=KIND_IDS)
+def test_autotuner_holds_packed_lanes_against_int32(torch_cuda, monkeypatch, capfd, kind):
+    # A lone triplet runs packed by default: its reference is the int32 form, the
+    # defaults a candidate.
+    torch = torch_cuda
+    rng = np.random.default_rng(96)
+    t = synth.mutated_triplet(rng, 600, 0.1, lens=(600, 66, 70))
+    lens, off, words = ts.pack_batch([t])
+    d_words = torch.from_numpy(words.view(np.int32)).cuda()
+    monkeypatch.setenv("TRIOSEQ_TUNE_LOG", "1")
+    print(f"autotune lone kind={kind}", flush=True)
+    capfd.readouterr()
+    res = ts.autotune(lens, off, d_words, sc=ts.scoring(kind=kind), reps=2)
+    log = [line.split() for line in capfd.readouterr().err.splitlines() if line.startswith("autotune:")]
+    packed = [line[line.index("packed") + 1] for line in log]
+    assert packed[:2] == ["0", "1"] and len(log) == res["tried"] and res["rejected"] == 0
+    default_ms = float(log[1][-2])
+    assert abs(res["reference_ms"] - default_ms) < 1e-4 and res["best_ms"] <= res["reference_ms"] + 1e-9
+    outs, _ = run(torch, [t], ts.scoring(kind=kind))  # (with what was remembered)
+    assert (outs[0] == want_scores([t], (1, -1, -2), kind)).all()
