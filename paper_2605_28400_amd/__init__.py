@@ -323,7 +323,8 @@ def triplet_array(triplets):
     kinds = set(map(type, seqs))
     if kinds == {np.ndarray}:
         lens = np.fromiter((s.size for s in seqs), dtype=np.int64, count=3 * n)
-        codes = np.concatenate(seqs).astype(np.uint8, copy=False) if lens.sum() else np.zeros(0, np.uint8)
+        flat = seqs if all(s.ndim == 1 for s in seqs) else [s.reshape(-1) for s in seqs]
+        codes = np.concatenate(flat).astype(np.uint8, copy=False) if lens.sum() else np.zeros(0, np.uint8)
         data = _ASCII[codes] if codes.size else codes
     else:
         parts = seqs if kinds == {bytes} else [_as_bytes(s) for s in seqs]

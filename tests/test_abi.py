@@ -274,3 +274,20 @@ def test_binding_structs_match_the_header(tmp_path):
         assert ctypes.sizeof(cls) == want[(cname, "size")], cname
         for field, _ in cls._fields_:
             assert getattr(cls, field).offset == want[(cname, field)], (cname, field)
+
+
+@pytest.mark.parametrize("seqs", [
+    [np.array([0, 1, 2], dtype=np.uint8), np.array([3]), np.array([], dtype=np.uint8)],
+    [np.array([[0, 1, 2]]), np.array([3, 3]), np.array([[1], [2]])],
+    [np.array(2), np.array([1.0, 3.0]), np.array([True, False])],
+    [np.arange(8).reshape(2, 4).T % 4, np.array([], dtype=np.int64), np.arange(9)[::3] % 4],
+    ["ACG", b"TT", np.array([2, 0])], [bytearray(b"acgt"), [0, 1], (3,)]],
+    ids=["codes", "two axes", "scalars", "strides", "mixed", "sequences"])
+def test_bulk_marshalling_takes_what_single_calls_take(seqs):
+    arr, keep = ts.triplet_array([tuple(seqs), tuple(reversed(seqs))])
+    for q, order in enumerate((seqs, seqs[::-1])):
+        for s in range(3):
+            want = ts._as_bytes(order[s])
+            assert arr[q].len[s] == len(want)
+            ptr = ctypes.cast(ctypes.addressof(arr[q]) + ts.Triplet.seq.offset + 8 * s, ctypes.POINTER(ctypes.c_void_p))
+            assert ctypes.string_at(ptr[0], len(want)) == want
