@@ -366,13 +366,17 @@ trioseq_status align_batch_impl(const trioseq_triplet* t, size_t n, const triose
   }
   PlaneWorkspace& ws = *g_ws;
   struct Release {
+    hipStream_t s;
+    bool done = false;
     ~Release() {
+      // (After an error work may still read the staged tables.)
+      if (!done) (void)hipStreamSynchronize(s);
       if (g_ws && ws_bytes(*g_ws) > kKeepBytes) {
         delete g_ws;
         g_ws = nullptr;
       }
     }
-  } release;
+  } release{s};
   hipError_t e = ws_grow(ws.lwords, words.size() * 4, false, s);
   if (e == hipSuccess && !words.empty())
     e = hipMemcpyAsync(ws.lwords.p, words.data(), words.size() * 4, hipMemcpyHostToDevice, s);
@@ -456,6 +460,7 @@ trioseq_status align_batch_impl(const trioseq_triplet* t, size_t n, const triose
     ncols_out[u] = len[u];
     scores_out[u] = (int32_t)sum[u];
   }
+  release.done = true;
   return TRIOSEQ_OK;
 }
 

@@ -1618,7 +1618,7 @@ PlaneWorkspace::~PlaneWorkspace() {
 }
 
 uint64_t ws_bytes(const PlaneWorkspace& ws) {
-  uint64_t t = 0;
+  uint64_t t = ws.h_stage_bytes + ws.h_out_ints * 4;
   for (const PlaneWorkspace::Buf* b :
        {&ws.ctl, &ws.desc, &ws.jobs, &ws.face, &ws.pool, &ws.bnd, &ws.red, &ws.plane, &ws.plane_off,
         &ws.words, &ws.scores, &ws.sd, &ws.split_out, &ws.chunk_box, &ws.partial, &ws.lwords, &ws.leaves,

@@ -243,7 +243,7 @@ struct PlaneWorkspace {
 // Makes b hold at least `bytes` (contents not kept; a buffer in use is only
 // replaced after the stream drains). zero: clear a new buffer.
 hipError_t ws_grow(PlaneWorkspace::Buf& b, uint64_t bytes, bool zero, hipStream_t s);
-// Bytes the workspace holds on the device.
+// Bytes the workspace holds on the device and in pinned host memory.
 uint64_t ws_bytes(const PlaneWorkspace& ws);
 // Lays out and sweeps n triplets (lens / word offsets on the host, words[0,
 // nwords) packed on the host), leaving the planes in ws.plane (device).

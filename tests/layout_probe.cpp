@@ -42,3 +42,13 @@ extern "C" void probe_layout(const uint32_t* lens, size_t n, const trioseq_scori
 extern "C" int probe_lone(const uint32_t* lens, int kind) {
   return (semi_global_halves(lens) ? 1 : 0) | (self_pair(kind, lens) ? 2 : 0);
 }
+
+// What a traceback workspace counts against the bytes that are kept: pinned
+// staging of `stage` bytes and `out` split-point ints beside `device` bytes.
+extern "C" uint64_t probe_workspace_bytes(uint64_t device, uint64_t stage, uint64_t out) {
+  PlaneWorkspace ws;
+  ws.tables.bytes = device;
+  ws.h_stage_bytes = stage;
+  ws.h_out_ints = out;
+  return ws_bytes(ws);
+}

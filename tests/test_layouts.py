@@ -142,3 +142,9 @@ def test_halves_keep_to_a_quarter_of_the_device(probe):
     pairs = layout(probe, lens[:600], panels=1)
     assert pairs["modes"] == PK_PANEL and pairs["halves"] == 0 and pairs["planes"] == 0
     assert layout(probe, lens[:600], panels=0)["modes"] != PK_PANEL
+
+
+def test_a_kept_workspace_counts_its_pinned_memory(probe):
+    probe.probe_workspace_bytes.restype = ctypes.c_uint64
+    probe.probe_workspace_bytes.argtypes = [ctypes.c_uint64] * 3
+    assert probe.probe_workspace_bytes(5000, 3000, 100) == 5000 + 3000 + 400
