@@ -43,42 +43,29 @@ OPS_PER_CELL_PACKED = OPS_PER_CELL_PACKED_OF["global"]
 
 WORKLOADS = ("single_1k", "single_128", "batch_8192", "single_4k", "served", "traceback")
 
-# HBM bytes per launch of the sweep kernel, from rocprofv3 --pmc FETCH_SIZE and
-# WRITE_SIZE runs scaled by the same counters on a plain 1 GiB copy (summaries
+# Bytes between the L2 and memory (the memory-side cache or HBM) per launch of the
+# sweep kernel, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE runs scaled by the
+# same counters on a plain 1 GiB copy (summaries
 # with the commands are under profiles/). Each figure holds only for the kernel
 # source it was measured on; for any other source the field is null.
-# Keyed by (workload, kind, lane tile, path): the autotuner may pick another
-# tile, and a lone global or local triplet under automatic options is scored by
-# halves.
+# Keyed by (workload, kind, lane tile, path): the int32 kernels of sweep.hip
+# (--engine 1).
 TRAFFIC = {
-    ("batch_8192_len100-400", "global", "4x4", "batch-packed+lds-direct"): (4.8549e10, "121dba023671257b"),
-    ("batch_8192_len100-400", "local", "4x4", "batch-packed"): (4.8426e10, "121dba023671257b"),
-    ("batch_8192_len100-400", "semi-global", "4x4", "batch-packed"): (4.8503e10, "121dba023671257b"),
-    ("single_1024x1000x1048", "global", "4x4", "halves"): (1.5255e9, "121dba023671257b"),
-    ("single_4096x4000x4150", "global", "4x4", "halves"): (7.7745e10, "121dba023671257b"),
-    ("single_128x128x128", "global", "4x4", "halves"): (5.8941e6, "121dba023671257b"),
-    ("single_1024x1000x1048", "local", "4x4", "halves"): (1.6171e9, "121dba023671257b"),
-    ("batch_8192_len100-400", "global", "8x4", "batch"): (7.2410e10, "5b986628d09c52c4"),
-    ("single_1024x1000x1048", "global", "4x4", "split"): (1.5689e9, "5b986628d09c52c4"),
-    ("single_4096x4000x4150", "global", "4x4", "split"): (7.9174e10, "5b986628d09c52c4"),
-    ("single_1024x1000x1048", "local", "4x4", "split"): (1.6522e9, "5b986628d09c52c4"),
-    ("batch_8192_len100-400", "local", "4x4", "batch"): (9.7230e10, "5b986628d09c52c4"),
-    ("single_1024x1000x1048", "semi-global", "4x4", "split"): (1.6210e9, "5b986628d09c52c4"),
-    ("batch_8192_len100-400", "semi-global", "8x4", "batch"): (7.3193e10, "5b986628d09c52c4"),
+    ("single_1024x1000x1048", "global", "4x4", "split"): (1.5718e+09, "40fcdc1b2025b602"),
 }
 
 
 # The same for packed panel jobs, keyed by (workload, kind) and measured on
 # packed_panel.hip.
 PANEL_TRAFFIC = {
-    ("batch_8192_len100-400", "global"): (9.5276e+10, "d9329fd5c13ab027"),
-    ("batch_8192_len100-400", "local"): (9.3463e+10, "d9329fd5c13ab027"),
-    ("single_1024x1000x1048", "local"): (8.8507e+08, "d9329fd5c13ab027"),
-    ("batch_8192_len100-400", "semi-global"): (9.3146e+10, "d9329fd5c13ab027"),
-    ("single_1024x1000x1048", "semi-global"): (9.1998e+08, "d9329fd5c13ab027"),
-    ("single_1024x1000x1048", "global"): (8.6409e+08, "d9329fd5c13ab027"),
-    ("single_128x128x128", "global"): (3.3519e+06, "d9329fd5c13ab027"),
-    ("single_4096x4000x4150", "global"): (4.0278e+10, "d9329fd5c13ab027"),
+    ("batch_8192_len100-400", "global"): (9.5266e+10, "20384a4321d83f19"),
+    ("batch_8192_len100-400", "local"): (9.3460e+10, "20384a4321d83f19"),
+    ("batch_8192_len100-400", "semi-global"): (9.3140e+10, "20384a4321d83f19"),
+    ("single_1024x1000x1048", "global"): (8.6043e+08, "20384a4321d83f19"),
+    ("single_1024x1000x1048", "local"): (8.8058e+08, "20384a4321d83f19"),
+    ("single_1024x1000x1048", "semi-global"): (9.1910e+08, "20384a4321d83f19"),
+    ("single_4096x4000x4150", "global"): (4.0292e+10, "20384a4321d83f19"),
+    ("single_128x128x128", "global"): (3.3532e+06, "20384a4321d83f19"),
 }
 
 
@@ -446,6 +433,8 @@ def main():
     packed = bool(info["packed"])
     panel_jobs = packed and info["panels"] > 0  # packed panel jobs, not whole pairs
     path = scoring_path(trips, args.kind, args.engine, args.tile, packed)
+    if panel_jobs and len(trips) > 1:
+        path = "packed-panels"
     if packed:
         ops = OPS_PER_CELL_PACKED_OF[args.kind]
         # The plan takes the autotuner's choice, staging included.
@@ -485,7 +474,8 @@ def main():
         "config": {"workload": workload.name, "triplets": len(trips), "cells": int(cells),
                    "seed": workload.seed, "scoring": "match +1, mismatch -1, gap -2",
                    "kind": args.kind, "packed_pairs": packed,
-                   "engine": ["whole-triplet", "split", "mixed"][info["engine"]], "path": path,
+                   "engine": ("packed panel jobs" if panel_jobs else
+                              ["whole-triplet", "split", "mixed"][info["engine"]]), "path": path,
                    "tile": f"{info['tile_rows']}x{info['tile_cols']}", "grid": info["grid"],
                    "hip_graph": bool(args.graph), "parallelism": "single GPU"},
         "roofline": {"bound": "alu", "achieved": round(achieved, 3),

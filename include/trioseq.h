@@ -208,7 +208,8 @@ typedef struct trioseq_plan_options {
                              jobs when its cells exceed split_factor times the batch's
                              mean cells per wavefront (or 2.5e8); 0 = default (4).
                              Int32 lanes only: a batch that qualifies for packed
-                             pairs under this engine runs as panel jobs throughout */
+                             pairs under this engine runs as panel jobs throughout,
+                             or in whole pairs */
   int32_t half_split_min; /* automatic engine, one triplet: scored by two concurrent
                              halves when its longest sequence has at least this many
                              residues; -1 = never; 0 = default (128). Local scoring
@@ -222,7 +223,8 @@ typedef struct trioseq_plan_options {
                              does not qualify runs in int32); 0 = default (2 when the
                              lane tile is left to the library, else 1). Under the
                              automatic engine the pairs (for a lone triplet its two
-                             halves) are swept as panel jobs */
+                             halves) are swept as panel jobs, and as whole pairs where
+                             that is faster (many short or thin triplets) */
   int32_t staging;        /* packed pairs: 1 = face rows staged through registers into
                              LDS; 2 = loaded straight into LDS (buffer loads to LDS);
                              0 = default */
@@ -230,9 +232,11 @@ typedef struct trioseq_plan_options {
 
 typedef struct trioseq_plan_info {
   int32_t engine;         /* 0 all whole, 1 all split, 2 mixed, by the options' split
-                             rule (packed panel jobs sweep all of them in panels) */
+                             rule (packed panel jobs sweep all of them in panels,
+                             then panels > 0) */
   int32_t tile_rows, tile_cols, grid, waves_per_cu;
-  int32_t panels;         /* panel jobs of split triplets */
+  int32_t panels;         /* panel jobs of split triplets; of packed panel jobs the
+                             panels of both triplets of every pair */
   int32_t packed;         /* 1: two triplets per lane (16-bit halves); 0: int32 */
   uint64_t workspace_bytes;
   double cells;           /* sum of a*b*c over the batch */

@@ -122,16 +122,16 @@ trioseq_status build_layout(const uint32_t* lens, const uint64_t* off, size_t n,
 // under this scoring.
 bool pair_panel_layout(const std::vector<TripletDesc>& desc, const trioseq_scoring& sc, bool planes, Layout* L);
 // One triplet's halves (longest sequence cut in two) as one packed pair, and
-// one triplet as a pair with itself.
+// one triplet as a pair with itself; which lone triplets take them.
 bool semi_global_halves(const uint32_t* lens);
 bool self_pair(int kind, const uint32_t* lens);
 bool packed_halves_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 bool packed_self_layout(const uint32_t* lens, const uint64_t* off, const trioseq_scoring& sc, Layout* L);
 // Lays out a batch as packed panel jobs of pairs: neighbours by size, or the
-// halves of every triplet (allow kAny, and while their planes and faces take at
-// most kHalvesBytes, a quarter of the device's memory: the pairs' faces are
-// bounded, the planes of all triplets are held at once). False if a value could
-// leave the 16-bit range.
+// halves of every triplet (allow kAny, and while their planes take at most
+// kHalvesBytes, a quarter of the device's memory: the faces are bounded, the
+// planes of all triplets are held at once). False if a value could leave the
+// 16-bit range.
 // unsplit (may be L itself): the triplets of a batch that the split rule leaves
 // whole; it becomes whole pairs where those are faster on that many waves.
 constexpr uint64_t kHalvesBytes = 72ull << 30;

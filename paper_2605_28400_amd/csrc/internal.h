@@ -177,8 +177,9 @@ hipError_t launch_fill_packed_sentinel(uint32_t* p, uint64_t n, hipStream_t s);
 // Packed panel jobs (packed_panel.hip): pairs of triplets, descriptors 2p and
 // 2p + 1, swept panel by panel by many workgroups; 4 x 4 lane tiles. off: the
 // stored value of a panel's base; kc: the offset of semi-global candidates. A
-// plane run (a.plane set) also writes both
-// triplets' last slices (global and local kinds).
+// plane run (a.plane set) also writes both triplets' last slices; its pairs are
+// the halves of one triplet (or box), the second of which starts on its faces
+// under semi-global scoring.
 constexpr int kPkPanel = 32;  // panel rows and columns
 // Rows of a pair's panel faces, and ints of all its faces: two buffers per
 // panel column of kPkPanel bottom entries a row, two per panel row of kPkPanel

@@ -18,7 +18,9 @@ namespace {
 // patterns are positive normal half-precision numbers (0x0400 .. 0x7BFF:
 // no zero, no subnormal, no infinity, no NaN), and for those the float
 // order of the bit patterns is the integer order; a maximum returns one of
-// its inputs unchanged. The additions are plain 16-bit integer additions.
+// its inputs unchanged. The additions are plain 32-bit integer additions of
+// both halves at once, exact as no half passes 65535 and nothing is carried
+// from the low half into the high one.
 // What keeps every value in range (checked on the host per batch, otherwise
 // the batch takes the int32 kernels):
 //  * every substitution term s - 2*gap is >= 0, so no addition lowers a

@@ -67,9 +67,10 @@ struct PkPanelLds {
 // column or row has fewer panels that write), written in turn:
 // a panel reads the one its neighbour wrote and overwrites the one written two
 // panels before. 260 buffers instead of two for each of 4225 panels of a
-// 2048-residue triplet: the faces stay in the caches (1024 x 1000 x 1048: 711
-// us against 734 with faces of its own for every panel; with a single buffer,
-// read and written in the same lines, 764). Nothing that is needed is
+// 2048-residue triplet (1024 x 1000 x 1048: 711 us against 734 with faces of its
+// own for every panel; with a single buffer, read and written in the same
+// lines, 764). Every face byte still leaves the L2, as the device-coherent stores
+// write through: the smaller buffers are for the memory-side cache. Nothing that is needed is
 // overwritten: a panel's row t depends, through its neighbour's row t + 7, on
 // the neighbour having read row t + 14 of the buffer in question. The tag of
 // an entry is gen + 1 + the panel row (bottom faces) or column (right faces)
