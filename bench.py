@@ -45,11 +45,10 @@ WORKLOADS = ("single_1k", "single_128", "batch_8192", "single_4k", "served", "tr
 
 # Bytes between the L2 and memory (the memory-side cache or HBM) per launch of the
 # sweep kernel, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE runs scaled by the
-# same counters on a plain 1 GiB copy (summaries
-# with the commands are under profiles/). Each figure holds only for the kernel
-# source it was measured on; for any other source the field is null.
-# Keyed by (workload, kind, lane tile, path): the int32 kernels of sweep.hip
-# (--engine 1).
+# same counters on a plain 1 GiB copy (summaries with the commands are under
+# profiles/). Each figure holds only for the kernel source it was measured on; for
+# any other source the field is null. Keyed by (workload, kind, lane tile, path):
+# the int32 kernels of sweep.hip (--engine 1).
 TRAFFIC = {
     ("single_1024x1000x1048", "global", "4x4", "split"): (1.5718e+09, "40fcdc1b2025b602"),
 }
@@ -433,7 +432,7 @@ def main():
     packed = bool(info["packed"])
     panel_jobs = packed and info["panels"] > 0  # packed panel jobs, not whole pairs
     path = scoring_path(trips, args.kind, args.engine, args.tile, packed)
-    if panel_jobs and len(trips) > 1:
+    if panel_jobs and path != "halves":
         path = "packed-panels"
     if packed:
         ops = OPS_PER_CELL_PACKED_OF[args.kind]
